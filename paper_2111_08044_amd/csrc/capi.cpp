@@ -47,6 +47,7 @@ int fail_hip(hipError_t e, const char* what) {
 constexpr int kPlanBlock = 16;        // periods per planned block
 constexpr int kMaxGatesPerPass = 96;  // cap on gates the planner puts in one pass
 constexpr int kReduceGrid = 2048;     // workgroups of the persistent reduction kernels
+constexpr int kApplyHGrid = 256;      // workgroups of H0 psi: one per CU (its two tiles fill the LDS)
 constexpr int kAdjGrid = 1024;        // workgroups of the persistent reverse pass
 constexpr int kAdjLowBits = 4;       // low tile bits of the reverse pass (its kernel takes C at run time)
 constexpr int kDense6LowBits = 4;    // low tile bits of the 6-qubit-window forms (their kernel takes C at run time)
@@ -76,7 +77,7 @@ struct fl_ctx {
     double T = 0.0;
     std::vector<cd> h, G;  // FP64, (L-1) x 16
     void* d_gates = nullptr;   // 2 (L-1) gates, 32 reals each, context precision
-    void* d_h = nullptr;       // (L-1) bond Hamiltonians, 32 reals each
+    void* d_h = nullptr;       // H0 psi: the bond Hamiltonians, 32 reals each (single-tile chains), or the window tables
     double* d_h64 = nullptr;   // the same in FP64 (energy contraction on the device)
     double* d_part = nullptr;  // reduction partials [kReduceGrid][L][16]
     double* d_red = nullptr;   // finalized reductions, 2 x L x 16
@@ -114,7 +115,9 @@ struct fl_ctx {
     };
     std::map<std::pair<int, int>, DensePlan> dense_plans;
     std::vector<std::vector<unsigned char>> dense_host;  // host fragments: sources of in-flight uploads
-    std::vector<fl_pass> cover;       // bond cover of the sweep geometry (H0 psi)
+    std::vector<fl_pass> cover;       // bond cover of the sweep geometry (H0 psi of single-tile chains)
+    fl_geom geom_h{};                 // the same tiles with 4-bit windows (longer chains):
+    std::vector<fl_pass> cover_h;     // the cover's bonds packed into windows
     std::vector<fl_pass> cover_rdm;   // bond cover of the reduction geometry
     bool use_grp = false;             // complex64, L >= 14: the reductions run on 13-bit tiles
     fl_geom geom_grp{};               // (L, 13, 5)
@@ -211,6 +214,58 @@ void stage_mats(Staged& st, void* dst, const std::vector<cd>& m, size_t nmat, in
     st.used += (bytes + 255) & ~(size_t)255;
 }
 
+size_t n_h_windows(const fl_ctx* c) {
+    size_t n = 0;
+    for (const fl_pass& p : c->cover_h) n += (size_t)p.ngroups;
+    return n;
+}
+
+// The summed Hamiltonian of every window of the H0 psi cover (FP64 sums,
+// rounded once), in the order apply_h_window reads: 16 diagonal reals, the
+// flips of bit k (rows with bit k clear) by its neighbours' values, the
+// double flips 00 -> 11 and 01 -> 10 of each bond.
+void stage_h_windows(Staged& st, const fl_ctx* c) {
+    unsigned char* p = st.buf + st.used;
+    size_t n = 0;
+    auto put = [&](double x) {
+        if (c->dtype == FL_C64) reinterpret_cast<float*>(p)[n++] = (float)x;
+        else reinterpret_cast<double*>(p)[n++] = x;
+    };
+    auto put2 = [&](cd z) {
+        put(z.real());
+        put(z.imag());
+    };
+    for (const fl_pass& ps : c->cover_h)
+        for (int g = 0; g < ps.ngroups; ++g) {
+            const cd* hw[3] = {nullptr, nullptr, nullptr};   // bond on window bits (j, j + 1)
+            for (int k = 0; k < ps.nops[g]; ++k) hw[ps.opi[g][k]] = &c->h[(size_t)ps.ops[g][k] * 16];
+            for (int m = 0; m < 16; ++m) {
+                double d = 0.0;
+                for (int j = 0; j < 3; ++j)
+                    if (hw[j]) d += hw[j][5 * ((m >> j) & 3)].real();
+                put(d);
+            }
+            for (int k = 0; k < 4; ++k)
+                for (int e = 0; e < (k == 0 || k == 3 ? 2 : 4); ++e) {
+                    const int lo = k == 0 ? 0 : e & 1, hi = k == 0 ? e : e >> 1;
+                    cd z = 0.0;
+                    if (k < 3 && hw[k]) z += hw[k][4 * (2 * hi) + 2 * hi + 1];       // low bit of bond k
+                    if (k > 0 && hw[k - 1]) z += hw[k - 1][4 * lo + lo + 2];         // high bit of bond k - 1
+                    put2(z);
+                }
+            for (int j = 0; j < 3; ++j) {
+                put2(hw[j] ? hw[j][3] : cd(0.0));
+                put2(hw[j] ? hw[j][4 + 2] : cd(0.0));
+            }
+        }
+    const size_t bytes = n * (c->dtype == FL_C64 ? 4 : 8);
+    st.dst[st.n] = c->d_h;
+    st.off[st.n] = st.used;
+    st.len[st.n] = bytes;
+    ++st.n;
+    st.used += (bytes + 255) & ~(size_t)255;
+}
+
 // Enqueue the staged copies on the context stream (after every kernel already
 // enqueued) and mark the slot busy until they have run.
 int stage_commit(fl_ctx* c, const Staged& st) {
@@ -256,7 +311,10 @@ int install_gates(fl_ctx* c) {
     const int rb = c->dtype == FL_C64 ? 4 : 8;
     stage_mats(st, c->d_gates, both, (size_t)2 * nb, rb);
     if (c->have_h) {
-        stage_mats(st, c->d_h, c->h, nb, rb);
+        if (c->cover_h.empty())
+            stage_mats(st, c->d_h, c->h, nb, rb);
+        else
+            stage_h_windows(st, c);
         stage_mats(st, c->d_h64, c->h, nb, 8);
     }
     return stage_commit(c, st);
@@ -550,13 +608,45 @@ void overlap_terms_win4(const fl_ctx* c, const fl_ctx::AdjWin4& aw, const double
     }
 }
 
-int apply_h0(fl_ctx* c, const void* psi, void* out) {
-    bool first = true;
-    for (const fl_pass& p : c->cover) {
-        hipError_t e = fl::launch_apply_h(c->dtype, c->geom, psi, out, c->d_h, p, first ? 1 : 0, c->stream);
-        if (e != hipSuccess) return fail_hip(e, "k_apply_h launch");
-        first = false;
+// out <- H0 psi.  With dots (chains longer than one tile) the last pass also
+// leaves the per-workgroup sums of k_apply_h_tiles there, *grid_out rows.
+int apply_h0(fl_ctx* c, const void* psi, void* out, double* dots, int* grid_out) {
+    if (c->cover_h.empty()) {
+        bool first = true;
+        for (const fl_pass& p : c->cover) {
+            hipError_t e = fl::launch_apply_h(c->dtype, c->geom, psi, out, c->d_h, p, first ? 1 : 0, c->stream);
+            if (e != hipSuccess) return fail_hip(e, "k_apply_h launch");
+            first = false;
+        }
+        return FL_OK;
     }
+    const int grid = (int)std::min<uint32_t>(ntiles(c->geom_h), kApplyHGrid);
+    const size_t wbytes = FL_HWIN_REALS * (c->dtype == FL_C64 ? sizeof(float) : sizeof(double));
+    const unsigned char* tab = static_cast<const unsigned char*>(c->d_h);
+    for (size_t i = 0; i < c->cover_h.size(); ++i) {
+        const fl_pass& p = c->cover_h[i];
+        fl::apply_h_desc d;
+        if (p.ngroups > FL_HWIN_MAX) return fail(FL_EINVAL, "internal: too many H0 windows in a pass");
+        d.h = p.h;
+        d.nwin = p.ngroups;
+        d.first = i == 0 ? 1 : 0;
+        for (int g = 0; g < FL_HWIN_MAX; ++g) d.u0[g] = g < p.ngroups ? p.u0[g] : 0;
+        hipError_t e = fl::launch_apply_h_tiles(c->dtype, c->geom_h, psi, out, tab, d,
+                                                i + 1 == c->cover_h.size() ? dots : nullptr, grid, c->stream);
+        if (e != hipSuccess) return fail_hip(e, "k_apply_h_tiles launch");
+        tab += wbytes * (size_t)p.ngroups;
+    }
+    if (grid_out) *grid_out = grid;
+    return FL_OK;
+}
+
+// The four overlap sums from their partial rows in d_part; synchronises.
+int read_overlap(fl_ctx* c, int grid, double out[4]) {
+    hipError_t e = fl::launch_finalize(c->d_part, grid, 4, c->d_red, c->stream);
+    if (e != hipSuccess) return fail_hip(e, "k_finalize launch");
+    FL_HIP(hipMemcpyAsync(c->h_red, c->d_red, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    FL_HIP(hipStreamSynchronize(c->stream));
+    for (int i = 0; i < 4; ++i) out[i] = c->h_red[i];
     return FL_OK;
 }
 
@@ -629,7 +719,13 @@ int fl_create(fl_ctx** ctx, int L, int dtype, int variant, void* hip_stream) {
                                             : fl::make_geom(L, FL_KMAX_C64, 6, kDense6LowBits);
     c->geom_adj = fl::make_geom(L, FL_KMAX_ADJ, 4, kAdjLowBits);
     c->geom_rdm = fl::make_geom(L, FL_KMAX_RDM, 2);
-    c->cover = fl::plan_cover(c->geom);
+    if (c->geom.W > 0) {
+        c->geom_h = c->geom;
+        c->geom_h.R = 4;
+        c->cover_h = fl::plan_cover_groups(c->geom_h);
+    } else {
+        c->cover = fl::plan_cover(c->geom);
+    }
     c->cover_rdm = fl::plan_cover(c->geom_rdm);
     c->use_grp = FL_RDM_GROUPS && dtype == FL_C64 && L > FL_KMAX_C64;
     if (c->use_grp) {
@@ -640,7 +736,7 @@ int fl_create(fl_ctx** ctx, int L, int dtype, int variant, void* hip_stream) {
     const size_t rb = dtype == FL_C64 ? 4 : 8;
     hipError_t e = hipSuccess;
     if (e == hipSuccess) e = hipMalloc(&c->d_gates, (size_t)2 * nb * 32 * rb);
-    if (e == hipSuccess) e = hipMalloc(&c->d_h, (size_t)nb * 32 * rb);
+    if (e == hipSuccess) e = hipMalloc(&c->d_h, std::max((size_t)nb * 32, n_h_windows(c) * FL_HWIN_REALS) * rb);
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_h64, (size_t)nb * 32 * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_part, (size_t)kReduceGrid * L * 16 * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_red, (size_t)2 * L * 16 * sizeof(double));
@@ -903,12 +999,7 @@ int fl_overlap(fl_ctx* c, const void* phi, int dphi, const void* psi, int dpsi, 
     const int grid = (int)std::min<uint64_t>(want, (uint64_t)kReduceGrid);
     hipError_t e = fl::launch_overlap(dphi, phi, dpsi, psi, n, c->d_part, grid, c->stream);
     if (e != hipSuccess) return fail_hip(e, "k_overlap launch");
-    e = fl::launch_finalize(c->d_part, grid, 4, c->d_red, c->stream);
-    if (e != hipSuccess) return fail_hip(e, "k_finalize launch");
-    FL_HIP(hipMemcpyAsync(c->h_red, c->d_red, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    FL_HIP(hipStreamSynchronize(c->stream));
-    for (int i = 0; i < 4; ++i) out[i] = c->h_red[i];
-    return FL_OK;
+    return read_overlap(c, grid, out);
 }
 
 int fl_energy_spread(fl_ctx* c, const void* psi, void* ws, double out[3]) {
@@ -920,10 +1011,12 @@ int fl_energy_spread(fl_ctx* c, const void* psi, void* ws, double out[3]) {
     if (ws == psi) return fail(FL_EINVAL, "ws must not alias psi");
     if (!out) return fail(FL_EINVAL, "out is NULL");
     if (!c->have_h) return fail(FL_ESTATE, "no bond Hamiltonians: call fl_set_bonds first");
-    rc = apply_h0(c, psi, ws);
+    const bool fused = !c->cover_h.empty();   // the sums come with the last pass
+    int grid = 0;
+    rc = apply_h0(c, psi, ws, fused ? c->d_part : nullptr, &grid);
     if (rc) return rc;
     double ov[4];
-    rc = fl_overlap(c, psi, c->dtype, ws, c->dtype, ov);
+    rc = fused ? read_overlap(c, grid, ov) : fl_overlap(c, psi, c->dtype, ws, c->dtype, ov);
     if (rc) return rc;
     out[0] = ov[0];
     out[1] = ov[3];
@@ -968,7 +1061,7 @@ int fl_grad(fl_ctx* c, void* psi_n, void* const* ckpts, int64_t n, int64_t K, co
     hipError_t e = fl::launch_finalize(c->d_part, grid, L * 16, c->d_red, c->stream);
     if (e != hipSuccess) return fail_hip(e, "k_finalize launch");
     // 2. lambda = H0 psi_n
-    rc = apply_h0(c, psi_n, lam);
+    rc = apply_h0(c, psi_n, lam, nullptr, nullptr);
     if (rc) return rc;
     // 3. reverse replay with checkpoint resets, accumulating D_b
     std::vector<double> Dmx;   // the matrix-core path's bond terms (host FP64)

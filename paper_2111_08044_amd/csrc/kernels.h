@@ -21,8 +21,20 @@ hipError_t launch_energy_contract(const double* red, const double* h64, int L, d
 hipError_t launch_init(int dtype, void* psi, int L, const void* tabs, int a, int b, hipStream_t s);
 hipError_t launch_overlap(int dta, const void* a, int dtb, const void* b, uint64_t n, double* partials, int grid,
                           hipStream_t s);
+// H0 psi of single-tile chains
 hipError_t launch_apply_h(int dtype, const fl_geom& g, const void* psi, void* lam, const void* hmat, const fl_pass& pd,
                           int first, hipStream_t s);
+// one cover pass of H0 psi on full tiles: `first` writes lambda, the others add to it
+#define FL_HWIN_MAX 8       // windows per pass
+#define FL_HWIN_REALS 52    // reals per window: the summed Hamiltonian of its bonds (layout: apply_h_window)
+struct apply_h_desc {
+    int32_t h, nwin, first;
+    int32_t u0[FL_HWIN_MAX];   // first tile bit of each window; the last one >= 4
+};
+// tab: the pass's windows; dots: NULL, or per-workgroup sums [grid][4] of Re <psi|lambda>, 0, <psi|psi>,
+// <lambda|lambda> (of the final lambda: the last pass)
+hipError_t launch_apply_h_tiles(int dtype, const fl_geom& g, const void* psi, void* lam, const void* tab,
+                                const apply_h_desc& pd, double* dots, int grid, hipStream_t s);
 hipError_t launch_adjoint(int dtype, const fl_geom& g, void* psi, void* lam, const void* gates, const fl_pass& pd,
                           double* Mpart, int grid, hipStream_t s);
 // reverse pass of the 4-qubit-window form (complex64, full 13-bit tiles) on

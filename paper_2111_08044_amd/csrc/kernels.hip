@@ -36,6 +36,7 @@ template <> struct CT<float> { typedef float2 c; };
 template <> struct CT<double> { typedef double2 c; };
 
 typedef float fl_f32x4 __attribute__((ext_vector_type(4)));
+typedef double fl_f64x2 __attribute__((ext_vector_type(2)));
 typedef float fl_f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 fl_bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -1342,6 +1343,209 @@ __global__ __launch_bounds__(FL_NT) void k_apply_h(const typename CT<T>::c* __re
     tile_store<T, KT>(lam, base, K, C, h, ll);
 }
 
+// Full tiles (W > 0).  The bonds of a pass come packed into windows of 4
+// consecutive tile bits (up to 3 bonds each), and every thread applies a
+// window's summed Hamiltonian to 2^4 amplitudes at once.  A row of that sum
+// has one real diagonal entry, one entry per flipped bit (the bonds on both
+// sides of the bit share it) and one per flipped neighbour pair, so three
+// bonds cost 30 FMA an amplitude instead of 48; by Hermiticity 52 reals hold
+// them all (layout: apply_h_window), read as scalars.
+//
+// psi sits in LDS for the whole tile; lambda changes layout between windows
+// through a second LDS tile (a thread reads the 16 elements it owns in this
+// window and writes the same ones: one barrier per window).  The last window
+// adds the lambda of earlier passes, loaded straight from HBM in that window's
+// layout, and stores the result the same way.  The two tiles leave room for
+// one workgroup per CU, so the kernel is bound by how well one workgroup hides
+// its HBM phases: persistent workgroups fetch the next tile's psi and lambda
+// into registers before the windows of the current one.
+//
+// DOT: the last pass also sums <psi|lambda>, <lambda|lambda> and <psi|psi>
+// (FP64, of the stored values) into dots[block][4].
+//
+// complex64, L = 25 (3 passes, 256 MiB state), H0 psi and its sums: 0.57 ms,
+// 180 - 206 us a pass (the adding passes move 0.8 GB: 4.5 TB/s).  One bond at
+// a time with a read-modify-write of lambda and a barrier per bond took 513 us
+// a pass, and the sums another 90 us pass over both states: 1.63 ms.
+// lambda += H_w psi on the 16 amplitudes of a window; bit k of m is window bit
+// k.  w: [0..15] diagonal entries of row m; then the single flips of bit k
+// (rows with bit k clear; the set ones take the conjugate), as (re, im) for
+// (bit k-1, bit k+1) = 00, 10, 01, 11 where those bits are in the window
+// (k = 0 and k = 3 have one neighbour, hence two entries); then the flips
+// 00 -> 11 (entry h_03) and 01 -> 10 (h_12) of each bond.
+template <typename T>
+__device__ __forceinline__ void apply_h_window(const T (&pr)[16], const T (&pi)[16], T (&lr)[16], T (&li)[16],
+                                               const T* __restrict__ w) {
+    auto pair_term = [&](int x, int y, T re, T im) {
+        lr[x] = fma(re, pr[y], lr[x]);
+        lr[x] = fma(-im, pi[y], lr[x]);
+        li[x] = fma(re, pi[y], li[x]);
+        li[x] = fma(im, pr[y], li[x]);
+        lr[y] = fma(re, pr[x], lr[y]);
+        lr[y] = fma(im, pi[x], lr[y]);
+        li[y] = fma(re, pi[x], li[y]);
+        li[y] = fma(-im, pr[x], li[y]);
+    };
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+        lr[m] = fma(w[m], pr[m], lr[m]);
+        li[m] = fma(w[m], pi[m], li[m]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int off = k == 0 ? 16 : k == 1 ? 20 : k == 2 ? 28 : 36;
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            if ((m >> k) & 1) continue;
+            const int lo = k > 0 ? (m >> (k - 1)) & 1 : 0, hi = k < 3 ? (m >> (k + 1)) & 1 : 0;
+            const int e = off + 2 * (k == 0 ? hi : lo + 2 * hi);
+            pair_term(m, m | (1 << k), w[e], w[e + 1]);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            if ((m >> (j + 1)) & 1) continue;
+            const int e = 40 + 4 * j + (((m >> j) & 1) ? 2 : 0);   // rows 00 and 01 of the bond (row 01 flips to 10)
+            pair_term(m, m ^ (3 << j), w[e], w[e + 1]);
+        }
+}
+
+template <typename T, int KT, int NT, int CL, bool DOT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 256))) void k_apply_h_tiles(
+    const typename CT<T>::c* __restrict__ psi, typename CT<T>::c* __restrict__ lam, const T* __restrict__ tab, int W,
+    uint32_t ntiles, apply_h_desc pd, double* __restrict__ dots) {
+    typedef typename CT<T>::c cplx;
+    constexpr int R = 4, C = CL, K = KT;
+    static_assert((1 << (K - R)) == NT, "one window of 16 amplitudes per thread");
+    constexpr int APL = sizeof(T) == 4 ? 2 : 1;
+    constexpr int ITER = (1 << K) / (APL * NT);
+    typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
+    __shared__ __attribute__((aligned(16))) cplx lp[1 << K];
+    __shared__ __attribute__((aligned(16))) cplx ll[1 << K];
+    const int h = pd.h, nw = pd.nwin;
+    static_assert((APL * NT) % (1 << C) == 0 && (APL * NT) % 256 == 0, "tile access stride");
+    const uint64_t toff = fl_tile_offset(APL * threadIdx.x, C, h);
+    const uint64_t tstride = (uint64_t)((APL * NT) >> C) << h;
+    const uint32_t l0 = fl_swz(APL * threadIdx.x);
+    // offsets of the last window's elements, relative to the tile base
+    const int ul = pd.u0[nw - 1];
+    const uint64_t ob = fl_tile_offset(fl_spread(threadIdx.x, ul, R), C, h);
+    uint64_t od[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) od[k] = fl_tile_offset(1u << (ul + k), C, h);
+    auto moff = [&](int m) {
+        uint64_t r = 0;
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+            if ((m >> k) & 1) r += od[k];
+        return r;
+    };
+    v16 np[ITER];       // psi of the next tile
+    cplx nl[1 << R];    // lambda of the current tile, in the last window's layout
+    auto fetch_psi = [&](uint32_t tile) {
+        const cplx* src = psi + fl_tile_base(tile, C, W, h) + toff;
+#pragma unroll
+        for (int s = 0; s < ITER; ++s) np[s] = *reinterpret_cast<const v16*>(src + s * tstride);
+    };
+    double dE = 0.0, dL = 0.0, dN = 0.0;
+    // complex128 has no registers left for the next tile's psi
+    constexpr bool PREF = sizeof(T) == 4;
+    if (PREF && blockIdx.x < ntiles) fetch_psi(blockIdx.x);
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        if (!PREF) fetch_psi(tile);
+        cplx* const lbase = lam + fl_tile_base(tile, C, W, h) + ob;
+        if (tile != blockIdx.x) __syncthreads();   // the previous tile's LDS reads are done
+#pragma unroll
+        for (int s = 0; s < ITER; ++s) {
+            const uint32_t l = l0 + s * (APL * NT);
+            if constexpr (sizeof(T) == 4) {
+                lp[l] = make_float2(np[s][0], np[s][1]);
+                lp[l ^ 1] = make_float2(np[s][2], np[s][3]);
+            } else {
+                lp[l] = make_double2(np[s][0], np[s][1]);
+            }
+        }
+        __syncthreads();
+        if (!pd.first) {
+#pragma unroll
+            for (int m = 0; m < (1 << R); ++m) nl[m] = lbase[moff(m)];
+        }
+        if (PREF && tile + gridDim.x < ntiles) fetch_psi(tile + gridDim.x);
+        for (int g = 0; g < nw; ++g) {
+            const int u0 = pd.u0[g];
+            uint32_t la[1 << R];
+            la[0] = fl_swz(fl_spread(threadIdx.x, u0, R)) * (uint32_t)sizeof(cplx);
+#pragma unroll
+            for (int m = 1; m < (1 << R); ++m)
+                la[m] = la[m & (m - 1)] ^ (fl_swz(1u << (u0 + __builtin_ctz(m))) * (uint32_t)sizeof(cplx));
+            char* const pb = reinterpret_cast<char*>(lp);
+            char* const lb = reinterpret_cast<char*>(ll);
+            T pr[16], pi[16], lr[16], li[16];
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                const cplx a = *reinterpret_cast<const cplx*>(pb + la[m]);
+                pr[m] = a.x;
+                pi[m] = a.y;
+                lr[m] = 0;
+                li[m] = 0;
+            }
+            if (g > 0) {
+#pragma unroll
+                for (int m = 0; m < 16; ++m) {
+                    const cplx a = *reinterpret_cast<const cplx*>(lb + la[m]);
+                    lr[m] = a.x;
+                    li[m] = a.y;
+                }
+            }
+            apply_h_window<T>(pr, pi, lr, li, tab + FL_HWIN_REALS * g);
+            if (g + 1 < nw) {
+#pragma unroll
+                for (int m = 0; m < 16; ++m) {
+                    cplx a;
+                    a.x = lr[m];
+                    a.y = li[m];
+                    *reinterpret_cast<cplx*>(lb + la[m]) = a;
+                }
+                __syncthreads();
+            } else {
+#pragma unroll
+                for (int m = 0; m < 16; ++m) {
+                    cplx a;
+                    a.x = lr[m];
+                    a.y = li[m];
+                    if (!pd.first) {
+                        a.x += nl[m].x;
+                        a.y += nl[m].y;
+                    }
+                    lbase[moff(m)] = a;
+                    if constexpr (DOT) {
+                        const double xr = pr[m], xi = pi[m], yr = a.x, yi = a.y;
+                        dE = fma(xr, yr, fma(xi, yi, dE));
+                        dL = fma(yr, yr, fma(yi, yi, dL));
+                        dN = fma(xr, xr, fma(xi, xi, dN));
+                    }
+                }
+            }
+        }
+    }
+    if constexpr (DOT) {
+        double v[4] = {dE, 0.0, dN, dL};   // the order of k_overlap's sums
+        const double r = wave_transpose_reduce<double, 4>(v);
+        double* const wacc = reinterpret_cast<double*>(lp);
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        __syncthreads();
+        if ((lane & 15) == 0) wacc[wave * 4 + (lane >> 4)] = r;
+        __syncthreads();
+        if (threadIdx.x < 4) {
+            double s = 0.0;
+            for (int k = 0; k < NT / 64; ++k) s += wacc[k * 4 + threadIdx.x];
+            dots[(size_t)blockIdx.x * 4 + threadIdx.x] = s;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // reverse pass of the gradient: undo gates on psi and lambda together
 // ---------------------------------------------------------------------------
@@ -2324,20 +2528,42 @@ hipError_t launch_overlap(int dta, const void* a, int dtb, const void* b, uint64
 hipError_t launch_apply_h(int dtype, const fl_geom& g, const void* psi, void* lam, const void* hmat, const fl_pass& pd,
                           int first, hipStream_t s) {
     const dim3 grid(ntiles_of(g)), block(FL_NT);
+    if (dtype == 0)
+        hipLaunchKernelGGL((k_apply_h<float, 0, FL_KMAX_C64>), grid, block, 0, s, (const float2*)psi, (float2*)lam,
+                           (const float*)hmat, g.C, g.W, pd, first);
+    else
+        hipLaunchKernelGGL((k_apply_h<double, 0, FL_KMAX_C128>), grid, block, 0, s, (const double2*)psi,
+                           (double2*)lam, (const double*)hmat, g.C, g.W, pd, first);
+    return hipGetLastError();
+}
+
+hipError_t launch_apply_h_tiles(int dtype, const fl_geom& g, const void* psi, void* lam, const void* tab,
+                                const apply_h_desc& pd, double* dots, int grid, hipStream_t s) {
+    if (g.W == 0 || pd.nwin < 1 || pd.nwin > FL_HWIN_MAX || pd.u0[pd.nwin - 1] < 4 || grid < 1)
+        return hipErrorInvalidValue;
+    for (int k = 0; k < pd.nwin; ++k)
+        if (pd.u0[k] < 0 || pd.u0[k] + 4 > g.K) return hipErrorInvalidValue;
+    const uint32_t nt = ntiles_of(g);
     if (dtype == 0) {
-        if (g.K == FL_KMAX_C64)
-            hipLaunchKernelGGL((k_apply_h<float, FL_KMAX_C64, FL_KMAX_C64>), grid, block, 0, s, (const float2*)psi,
-                               (float2*)lam, (const float*)hmat, g.C, g.W, pd, first);
+        if (g.K != FL_KMAX_C64 || g.C != FL_SWEEP_LOWBITS_C64) return hipErrorInvalidValue;
+        constexpr int K = FL_KMAX_C64, C = FL_SWEEP_LOWBITS_C64;
+        auto* p = (const float2*)psi;
+        auto* l = (float2*)lam;
+        auto* t = (const float*)tab;
+        if (dots)
+            hipLaunchKernelGGL((k_apply_h_tiles<float, K, 512, C, true>), dim3(grid), dim3(512), 0, s, p, l, t, g.W, nt, pd, dots);
         else
-            hipLaunchKernelGGL((k_apply_h<float, 0, FL_KMAX_C64>), grid, block, 0, s, (const float2*)psi,
-                               (float2*)lam, (const float*)hmat, g.C, g.W, pd, first);
+            hipLaunchKernelGGL((k_apply_h_tiles<float, K, 512, C, false>), dim3(grid), dim3(512), 0, s, p, l, t, g.W, nt, pd, dots);
     } else {
-        if (g.K == FL_KMAX_C128)
-            hipLaunchKernelGGL((k_apply_h<double, FL_KMAX_C128, FL_KMAX_C128>), grid, block, 0, s,
-                               (const double2*)psi, (double2*)lam, (const double*)hmat, g.C, g.W, pd, first);
+        if (g.K != FL_KMAX_C128 || g.C != FL_LOWBITS) return hipErrorInvalidValue;
+        constexpr int K = FL_KMAX_C128, C = FL_LOWBITS;
+        auto* p = (const double2*)psi;
+        auto* l = (double2*)lam;
+        auto* t = (const double*)tab;
+        if (dots)
+            hipLaunchKernelGGL((k_apply_h_tiles<double, K, 256, C, true>), dim3(grid), dim3(256), 0, s, p, l, t, g.W, nt, pd, dots);
         else
-            hipLaunchKernelGGL((k_apply_h<double, 0, FL_KMAX_C128>), grid, block, 0, s, (const double2*)psi,
-                               (double2*)lam, (const double*)hmat, g.C, g.W, pd, first);
+            hipLaunchKernelGGL((k_apply_h_tiles<double, K, 256, C, false>), dim3(grid), dim3(256), 0, s, p, l, t, g.W, nt, pd, dots);
     }
     return hipGetLastError();
 }

@@ -1,0 +1,57 @@
+"""Kernels on full tiles at the edges of their ranges against the oracle
+(MI355X only; every call goes through the C ABI)."""
+import sys
+
+import numpy as np
+import pytest
+
+import floquet_inputs as fin
+import oracle as O
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2111_08044_amd as fl  # noqa: E402
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _random_context(L, dtype, seed, variant="plain"):
+    hs = 2.0 * fin.gue_bond_sample(L, seed=seed)
+    ctx = fl.fl_create(L, dtype, variant)
+    fl.fl_set_bonds(ctx, hs, 0.7)
+    psi = fl.new_state(ctx)
+    ref = torch.from_numpy(fin.random_state(L, seed)).to(psi.dtype)
+    psi.copy_(ref)
+    return ctx, hs, psi, ref.to(torch.complex128).numpy()
+
+
+# 2 tiles (the shortest chains of the tiled kernel), one bond left over for a
+# second or third pass, more tiles than workgroups
+@pytest.mark.parametrize("dtype,L", [("c64", 14), ("c64", 15), ("c64", 22), ("c64", 23),
+                                     ("c128", 13), ("c128", 14), ("c128", 19), ("c128", 21)])
+def test_h0_psi_and_its_sums(dtype, L):
+    """Every amplitude of H0 psi for distinct random bond terms.  A row sums
+    8 entries a window and at most 13 windows: about 100 roundings of random
+    sign, 10 units in the last place of the norm."""
+    say(f"case: H0 psi {dtype} L={L}")
+    ctx, hs, psi, ref = _random_context(L, dtype, 70 + L)
+    ws = torch.full_like(psi, float("nan"))
+    E, E2, N = fl.fl_energy_spread(ctx, psi, ws)
+    want = O.apply_h0(ref, L, hs)
+    got = ws.cpu().numpy().astype(np.complex128)
+    ulp = 6e-8 if dtype == "c64" else 1.2e-16
+    assert np.linalg.norm(got - want) < 10 * ulp * np.linalg.norm(want)
+    # the sums are FP64 sums over the stored values
+    assert abs(E - np.vdot(ref, got).real) < 1e-12 * np.linalg.norm(ref) * np.linalg.norm(got)
+    assert abs(E2 - np.vdot(got, got).real) < 1e-12 * E2
+    assert abs(N - np.vdot(ref, ref).real) < 1e-12 * N
+    assert np.array_equal(psi.cpu().numpy(), ref.astype(psi.cpu().numpy().dtype))
