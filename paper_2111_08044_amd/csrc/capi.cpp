@@ -58,12 +58,36 @@ constexpr size_t kStageBytes = 256 << 10;  // bytes per slot: >= 3 x 4096 comple
 
 int kmax_of(int dtype) { return dtype == FL_C64 ? FL_KMAX_C64 : FL_KMAX_C128; }
 
-// Geometry of the plain sweep: complex64 on 13-bit tiles with 4 low bits and
-// 4-bit register groups, complex128 on 12-bit tiles with 6 low bits and 4-bit
-// groups.
+// Full-size tiles: complex64 13 bits with 4 low bits, complex128 12 bits with
+// 6 low bits; 4-bit register groups.
 fl_geom plain_geom(int L, int dtype) {
     return dtype == FL_C64 ? fl::make_geom(L, FL_KMAX_C64, FL_SWEEP_R_C64, FL_SWEEP_LOWBITS_C64)
                            : fl::make_geom(L, FL_KMAX_C128, 4);
+}
+
+// Geometry of the plain sweep of a call of n periods.
+//  - L <= 10: one workgroup holds the state, one quad per thread and gate.
+//  - Short chains: tiles of L - 8 bits, so that 256 workgroups, one per CU,
+//    share the work; a pass is then a serial chain of LDS round trips, and
+//    smaller register groups (2 or 3 bits) spread it over more waves.  Tiles
+//    below 10 (complex128: 9) bits need more passes than they save.  16
+//    periods, against full tiles (us): complex64 L = 14 123 / 201, 17 161 /
+//    257, 18 180 / 275, 19 220 / 299, 20 271 / 345; complex128 L = 13 121 /
+//    189, 17 179 / 292, 18 208 / 321, 19 253 / 362.
+//  - Longer chains: full tiles (complex64 L = 21: 365 on 13 bits, 407 on 12).
+//  - complex128 on 12-bit tiles takes 3 low bits (128-byte runs, a 9-bit
+//    window) for calls of 3 periods and more: 15 passes instead of 27 for 16
+//    periods at L = 23, 2.12 against 2.42 ms.  For one or two periods the two
+//    are within 3 to 12% (L = 24, n = 2: 4 passes in 665 us, 5 in 686 us) and
+//    the call keeps 6.
+fl_geom sweep_geom(int L, int dtype, int64_t n) {
+    if (L <= FL_KMAX_ONE) return fl::make_geom(L, FL_KMAX_ONE, 2, 3);
+    const bool c64 = dtype == FL_C64;
+    const int k = std::max(L - 8, c64 ? 10 : 9);
+    if (k <= 10) return fl::make_geom(L, k, 2, 3);
+    if (k == 11 || (k == 12 && c64)) return fl::make_geom(L, k, 3, 3);
+    if (!c64 && n >= 3) return fl::make_geom(L, FL_KMAX_C128, 4, 3);
+    return plain_geom(L, dtype);
 }
 size_t amp_bytes(int dtype) { return dtype == FL_C64 ? 8 : 16; }
 
@@ -107,7 +131,11 @@ struct fl_ctx {
     bool stage_used[kStageSlots] = {};
     int stage_next = 0;
     hipEvent_t ev_switch = nullptr;    // orders work across a change of stream
-    std::map<std::pair<int, int>, std::vector<fl_pass>> plans;
+    struct SweepPlan {
+        fl_geom g{};
+        std::vector<fl_pass> passes;
+    };
+    std::map<std::pair<int, int>, SweepPlan> plans;
     std::map<int, std::vector<fl_pass>> adj_plans;
     struct DensePlan {
         std::vector<fl_pass> passes;   // opg[g][0] = window matrix index
@@ -128,13 +156,16 @@ namespace {
 
 uint32_t ntiles(const fl_geom& g) { return 1u << (g.L - g.K); }
 
-const std::vector<fl_pass>& get_plan(fl_ctx* c, int n, bool dagger) {
-    auto key = std::make_pair(n, dagger ? 1 : 0);
+// The plan of a block of m periods of a call of n.
+const fl_ctx::SweepPlan& get_plan(fl_ctx* c, int m, int64_t n, bool dagger) {
+    const fl_geom g = sweep_geom(c->L, c->dtype, n);
+    auto key = std::make_pair(m, (dagger ? 1 : 0) | (g.C << 1));
     auto it = c->plans.find(key);
     if (it != c->plans.end()) return it->second;
-    auto& v = c->plans[key];
-    v = fl::plan_sweep(c->geom, n, dagger, false, kMaxGatesPerPass);
-    return v;
+    fl_ctx::SweepPlan p;
+    p.g = g;
+    p.passes = fl::plan_sweep(g, m, dagger, false, kMaxGatesPerPass);
+    return c->plans[key] = std::move(p);
 }
 
 const std::vector<fl_pass>& get_adj_plan(fl_ctx* c, int n) {
@@ -452,21 +483,18 @@ int run_dense(fl_ctx* c, void* psi, int64_t n, bool dagger) {
 int run_periods(fl_ctx* c, void* psi, int64_t n, bool dagger) {
     if (is_dense(c)) return run_dense(c, psi, n, dagger);
     const int64_t q = n / kPlanBlock, r = n % kPlanBlock;
-    if (q > 0) {
-        const auto& pb = get_plan(c, kPlanBlock, dagger);
-        for (int64_t i = 0; i < q; ++i)
-            for (const fl_pass& p : pb) {
-                hipError_t e = fl::launch_sweep(c->dtype, c->geom, psi, c->d_gates, p, c->stream);
-                if (e != hipSuccess) return fail_hip(e, "k_sweep launch");
-            }
-    }
-    if (r > 0) {
-        const auto& pr = get_plan(c, (int)r, dagger);
-        for (const fl_pass& p : pr) {
-            hipError_t e = fl::launch_sweep(c->dtype, c->geom, psi, c->d_gates, p, c->stream);
-            if (e != hipSuccess) return fail_hip(e, "k_sweep launch");
+    auto go = [&](const fl_ctx::SweepPlan& plan) -> int {
+        for (const fl_pass& p : plan.passes) {
+            hipError_t e = fl::launch_sweep(c->dtype, plan.g, psi, c->d_gates, p, c->stream);
+            if (e != hipSuccess) return fail_hip(e, "sweep kernel launch");
         }
+        return FL_OK;
+    };
+    for (int64_t i = 0; i < q; ++i) {
+        int rc = go(get_plan(c, kPlanBlock, n, dagger));
+        if (rc) return rc;
     }
+    if (r > 0) return go(get_plan(c, (int)r, n, dagger));
     return FL_OK;
 }
 
@@ -1309,7 +1337,7 @@ int fl_plan_query(int L, int dtype, int kind, int64_t n, int dagger, int32_t* bu
     std::vector<fl_pass> plan;
     fl_geom g;
     if (kind == 0) {
-        g = plain_geom(L, dtype);
+        g = sweep_geom(L, dtype, n);
         const int64_t q = n / kPlanBlock, r = n % kPlanBlock;
         std::vector<fl_pass> pb, pr;
         if (q > 0) pb = fl::plan_sweep(g, kPlanBlock, dagger != 0, false, kMaxGatesPerPass);

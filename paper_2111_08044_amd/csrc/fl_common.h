@@ -39,18 +39,14 @@
 #define FL_WIN4_NT 512         // threads of the 4-qubit-window reverse pass (13-bit tiles of two states)
 #define FL_KMAX_RDM 12       // tile bits of the energy / density-matrix reduction
 #define FL_MAX_SLOTS 16      // distinct reduction slots per pass
-#define FL_MAX_GATE_TABLE 66 // gates of the largest chain (L = 34): G_b and G_b^dagger per bond
-#ifndef FL_SWEEP_NT_C64
-#define FL_SWEEP_NT_C64 512  // threads per workgroup of the complex64 full-tile sweep
-#endif
+#define FL_KMAX_ONE 10       // longest chain whose sweep runs in one workgroup
+#define FL_SWEEP_WORDS 144   // words of a sweep pass's descriptor in words form: groups + ops + 1
+#define FL_MAX_GATE_TABLE 33 // gates of one direction (G_b or G_b^dagger) of the largest chain (L = 34)
 #ifndef FL_SWEEP_LOWBITS_C64
 #define FL_SWEEP_LOWBITS_C64 4  // C of the complex64 sweep: 16-amplitude (128-byte) runs, a 9-bit window
 #endif
 #ifndef FL_SWEEP_R_C64
 #define FL_SWEEP_R_C64 4     // register bits per group of the complex64 sweep
-#endif
-#ifndef FL_SWEEP_LDS_GATES
-#define FL_SWEEP_LDS_GATES 1  // complex64 sweep: gates in vector registers, read from an LDS copy of the table
 #endif
 #define FL_RDM_NT_C64 256    // threads per workgroup of the complex64 bond reduction on 13-bit tiles
 #define FL_RDM_R_C64 5       // register bits per group of that reduction
@@ -78,6 +74,14 @@ struct fl_pass {
     int8_t opi[FL_MAX_GROUPS][FL_MAX_OPS];   // op acts on register bits (i, i+1)
     int16_t opg[FL_MAX_GROUPS][FL_MAX_OPS];  // gate-table index, -1 = no gate
     int16_t ops[FL_MAX_GROUPS][FL_MAX_OPS];  // reduction slot (index into sbond), -1 = none
+};
+
+// A sweep pass as a kernel that keeps its descriptor in LDS takes it.
+struct fl_sweep_words {
+    int32_t h, ngroups;
+    int32_t ufirst, ulast;       // first bits of the first and the last group (-1: no group)
+    int32_t nwords;
+    uint32_t w[FL_SWEEP_WORDS];  // per group u0 | nops << 8, then per op bit | gate << 8, then 0
 };
 
 #ifdef __cplusplus

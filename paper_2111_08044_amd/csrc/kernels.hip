@@ -46,44 +46,8 @@ typedef __bf16 fl_bf16x8 __attribute__((ext_vector_type(8)));
 
 // out_i = sum_j G_ij a_j on the four amplitudes whose register index has bits
 // (I, I+1) = local index (2*bit(I+1) + bit(I)), for every value of the other
-// R-2 register bits.  G holds 16 complex entries, row-major, (re, im) pairs.
-template <typename T, int R, int I>
-__device__ __forceinline__ void apply_pair(T (&vr)[1 << R], T (&vi)[1 << R], const T* __restrict__ G) {
-    __asm__ volatile("; gate on register bits %0" ::"i"(I));
-    T g[32];
-#pragma unroll
-    for (int k = 0; k < 32; ++k) g[k] = G[k];
-#pragma unroll
-    for (int c = 0; c < (1 << (R - 2)); ++c) {
-        const int b = (c & ((1 << I) - 1)) | ((c >> I) << (I + 2));
-        T ar[4], ai[4];
-#pragma unroll
-        for (int l = 0; l < 4; ++l) {
-            ar[l] = vr[b | (l << I)];
-            ai[l] = vi[b | (l << I)];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            T sr = g[8 * i] * ar[0];
-            T si = g[8 * i] * ai[0];
-            sr = fma(-g[8 * i + 1], ai[0], sr);
-            si = fma(g[8 * i + 1], ar[0], si);
-#pragma unroll
-            for (int j = 1; j < 4; ++j) {
-                sr = fma(g[8 * i + 2 * j], ar[j], sr);
-                sr = fma(-g[8 * i + 2 * j + 1], ai[j], sr);
-                si = fma(g[8 * i + 2 * j], ai[j], si);
-                si = fma(g[8 * i + 2 * j + 1], ar[j], si);
-            }
-            vr[b | (i << I)] = sr;
-            vi[b | (i << I)] = si;
-        }
-    }
-    __asm__ volatile("; end gate on register bits %0" ::"i"(I));
-}
-
-// Same, with the 16 complex gate entries already in registers (SGPRs: the
-// gate is uniform across the workgroup), updating the amplitudes in place.
+// R-2 register bits.  G holds 16 complex entries, row-major, (re, im) pairs, in
+// registers; the amplitudes are updated in place.
 // Every output first sums the seven terms that do not hold its own input
 // amplitude; the last FMA of output (re|im)_i then adds the diagonal term
 // Re(G_ii) (re|im)_i.  That FMA is the last read of its input, so it can
@@ -158,53 +122,6 @@ __device__ __forceinline__ void with_bit(int i, F&& f) {
 template <typename T, int R>
 __device__ __forceinline__ void apply_op_g(T (&vr)[1 << R], T (&vi)[1 << R], int i, const T (&g)[32]) {
     with_bit<R>(i, [&](auto I) { apply_pair_g<T, R, decltype(I)::value>(vr, vi, g); });
-}
-
-// Out-of-place form: reads every amplitude of (sr, si) and writes the result
-// to (dr, di).  All variants write the same destination registers, so the
-// run-time choice of I needs no register moves where the variants rejoin.
-template <typename T, int R, int I>
-__device__ __forceinline__ void apply_pair_to(const T (&sr)[1 << R], const T (&si)[1 << R], T (&dr)[1 << R],
-                                              T (&di)[1 << R], const T (&g)[32]) {
-    __asm__ volatile("; gate on register bits %0 (out of place)" ::"i"(I));
-#pragma unroll
-    for (int c = 0; c < (1 << (R - 2)); ++c) {
-        const int b = (c & ((1 << I) - 1)) | ((c >> I) << (I + 2));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            T ar = g[8 * i] * sr[b];
-            T ai = g[8 * i] * si[b];
-            ar = fma(-g[8 * i + 1], si[b], ar);
-            ai = fma(g[8 * i + 1], sr[b], ai);
-#pragma unroll
-            for (int j = 1; j < 4; ++j) {
-                ar = fma(g[8 * i + 2 * j], sr[b | (j << I)], ar);
-                ar = fma(-g[8 * i + 2 * j + 1], si[b | (j << I)], ar);
-                ai = fma(g[8 * i + 2 * j], si[b | (j << I)], ai);
-                ai = fma(g[8 * i + 2 * j + 1], sr[b | (j << I)], ai);
-            }
-            dr[b | (i << I)] = ar;
-            di[b | (i << I)] = ai;
-        }
-    }
-    __asm__ volatile("; end gate on register bits %0 (out of place)" ::"i"(I));
-}
-
-template <typename T, int R>
-__device__ __forceinline__ void apply_op_to(const T (&sr)[1 << R], const T (&si)[1 << R], T (&dr)[1 << R],
-                                            T (&di)[1 << R], int i, const T (&g)[32]) {
-    if constexpr (R >= 2) if (i == 0) { apply_pair_to<T, R, 0>(sr, si, dr, di, g); return; }
-    if constexpr (R >= 3) if (i == 1) { apply_pair_to<T, R, 1>(sr, si, dr, di, g); return; }
-    if constexpr (R >= 4) if (i == 2) { apply_pair_to<T, R, 2>(sr, si, dr, di, g); return; }
-    if constexpr (R >= 5) if (i == 3) { apply_pair_to<T, R, 3>(sr, si, dr, di, g); return; }
-}
-
-template <typename T, int R>
-__device__ __forceinline__ void apply_op(T (&vr)[1 << R], T (&vi)[1 << R], int i, const T* __restrict__ G) {
-    if constexpr (R >= 2) if (i == 0) { apply_pair<T, R, 0>(vr, vi, G); return; }
-    if constexpr (R >= 3) if (i == 1) { apply_pair<T, R, 1>(vr, vi, G); return; }
-    if constexpr (R >= 4) if (i == 2) { apply_pair<T, R, 2>(vr, vi, G); return; }
-    if constexpr (R >= 5) if (i == 3) { apply_pair<T, R, 3>(vr, vi, G); return; }
 }
 
 // ---------------------------------------------------------------------------
@@ -297,44 +214,68 @@ __device__ __forceinline__ void tile_store(typename CT<T>::c* __restrict__ psi, 
 // fused sweep
 // ---------------------------------------------------------------------------
 
-template <typename T, int R, int KT, int KMAX>
-__global__ __launch_bounds__(FL_NT) void k_sweep(typename CT<T>::c* __restrict__ psi, const T* __restrict__ gates,
-                                                 int C, int W, fl_pass pd) {
-    typedef typename CT<T>::c cplx;
-    __shared__ cplx lds[1 << KMAX];
-    const int K = KT > 0 ? KT : C + W;
-    const int h = pd.h;
-    const uint64_t base = fl_tile_base(blockIdx.x, C, W, h);
-    tile_load<T, KT>(psi, base, K, C, h, lds);
-    __syncthreads();
-    const uint32_t nsub = 1u << (K - R);
-    for (int g = 0; g < pd.ngroups; ++g) {
-        const int u0 = pd.u0[g];
-        const int nops = pd.nops[g];
-        for (uint32_t o = threadIdx.x; o < nsub; o += FL_NT) {
-            const uint32_t b0 = fl_spread(o, u0, R);
-            T vr[1 << R], vi[1 << R];
+// Reads one gate (32 reals, one address for the whole wave: broadcasts) from
+// the workgroup's LDS copy of the gate table.
+template <typename T>
+__device__ __forceinline__ void load_gate_lds(const T* src, T (&gv)[32]) {
+    typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
+    constexpr int PER = 16 / sizeof(T);
 #pragma unroll
-            for (int m = 0; m < (1 << R); ++m) {
+    for (int k = 0; k < 32 / PER; ++k) {
+        const v16 v = reinterpret_cast<const v16*>(src)[k];
+#pragma unroll
+        for (int e = 0; e < PER; ++e) gv[PER * k + e] = v[e];
+    }
+}
+
+// Chains of at most FL_KMAX_ONE sites: one workgroup holds the whole state in
+// LDS, one quad of amplitudes per thread and gate.  A serial chain of LDS
+// round trips: nothing but its latency matters, so the descriptor words and
+// the gates sit in LDS beside the state.
+template <typename T>
+__global__ __launch_bounds__(FL_NT) void k_sweep_one(typename CT<T>::c* __restrict__ psi, const T* __restrict__ gates,
+                                                     int L, fl_sweep_words pd) {
+    typedef typename CT<T>::c cplx;
+    __shared__ __attribute__((aligned(16))) T lg[FL_KMAX_ONE * 32];
+    __shared__ uint32_t meta[FL_SWEEP_WORDS];
+    __shared__ cplx lds[1 << FL_KMAX_ONE];
+    static_assert((1 << FL_KMAX_ONE) / 4 <= FL_NT, "one quad per thread");
+    for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) lds[fl_swz(j)] = psi[j];
+    for (int t = threadIdx.x; t < (L - 1) * 32; t += FL_NT) lg[t] = gates[t];
+    for (int t = threadIdx.x; t < pd.nwords; t += FL_NT) meta[t] = pd.w[t];
+    __syncthreads();
+    const bool active = threadIdx.x < (1u << (L - 2));
+    const int ng = pd.ngroups;
+    int pos = ng;
+    for (int g = 0; g < ng; ++g) {
+        const uint32_t head = meta[g];
+        const int u0 = head & 255, nops = head >> 8;
+        if (active) {
+            const uint32_t b0 = fl_spread(threadIdx.x, u0, 2);
+            T vr[4], vi[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
                 const cplx a = lds[fl_swz(b0 | ((uint32_t)m << u0))];
                 vr[m] = a.x;
                 vi[m] = a.y;
             }
             for (int q = 0; q < nops; ++q) {
-                const int gi = pd.opg[g][q];
-                if (gi >= 0) apply_op<T, R>(vr, vi, pd.opi[g][q], gates + 32 * gi);
+                T gv[32];
+                load_gate_lds<T>(lg + 32 * (meta[pos + q] >> 8), gv);
+                apply_pair_g<T, 2, 0>(vr, vi, gv);
             }
 #pragma unroll
-            for (int m = 0; m < (1 << R); ++m) {
+            for (int m = 0; m < 4; ++m) {
                 cplx a;
                 a.x = vr[m];
                 a.y = vi[m];
                 lds[fl_swz(b0 | ((uint32_t)m << u0))] = a;
             }
         }
+        pos += nops;
         __syncthreads();
     }
-    tile_store<T, KT>(psi, base, K, C, h, lds);
+    for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) psi[j] = lds[fl_swz(j)];
 }
 
 // Op q of group g as (gate-table index, register bit), read as aligned 32-bit
@@ -363,88 +304,34 @@ __device__ __forceinline__ int pass_bit(const fl_pass& pd, int g, int q) {
 // lgkmcnt(0) with no wait on the vector-memory and export counters.
 #define FL_WAIT_LGKM0 0xc07f
 
-// The ops of register group g applied to the SUB register groups of a
-// thread.  Ops run two per iteration (the register copies that LLVM places on
-// a loop back edge after the 4-way choice of gate bits are then not needed at
-// all).  The next op's gate (32 scalar registers) is fetched while the
-// current one is applied; an explicit lgkmcnt(0) before each fetch waits for
-// the previous one, so that no wait inside an apply ever covers the fetch in
-// flight.  gc holds the group's first gate on entry and the next group's
-// first gate on return: that fetch overlaps the LDS exchange between the two
-// groups instead of stalling the start of the next group.
-template <typename T, int R, int SUB>
-__device__ __forceinline__ void sweep_group_ops(T (&vr)[SUB][1 << R], T (&vi)[SUB][1 << R], const fl_pass& pd, int g,
-                                                const T* __restrict__ gates, T (&gc)[32]) {
-    const int nops = pass_nops(pd, g);
-    const int ng = pd.ngroups;
-    auto gate_of = [&](int q) {
-        const int idx = q < nops ? pass_gate(pd, g, q) : (g + 1 < ng ? pass_gate(pd, g + 1, 0) : pass_gate(pd, g, nops - 1));
-        return gates + 32 * idx;
-    };
-    int i = pass_bit(pd, g, 0);
-    T g1[32];
-    for (int q = 0; q < nops; q += 2) {
-        __builtin_amdgcn_s_waitcnt(FL_WAIT_LGKM0);
-        const int i1 = pass_bit(pd, g, q + 1 < nops ? q + 1 : q);
-        {
-            const T* G = gate_of(q + 1);
-#pragma unroll
-            for (int k = 0; k < 32; ++k) g1[k] = G[k];
-        }
-#pragma unroll
-        for (int s = 0; s < SUB; ++s) apply_op_g<T, R>(vr[s], vi[s], i, gc);
-        if (q + 1 < nops) {
-            __builtin_amdgcn_s_waitcnt(FL_WAIT_LGKM0);
-            i = pass_bit(pd, g, q + 2 < nops ? q + 2 : q + 1);
-            {
-                const T* G = gate_of(q + 2);
-#pragma unroll
-                for (int k = 0; k < 32; ++k) gc[k] = G[k];
-            }
-#pragma unroll
-            for (int s = 0; s < SUB; ++s) apply_op_g<T, R>(vr[s], vi[s], i1, g1);
-        }
-    }
-    if (nops & 1) {
-#pragma unroll
-        for (int k = 0; k < 32; ++k) gc[k] = g1[k];
-    }
-}
-
-// The same with the gates in vector registers, read from the workgroup's LDS
-// copy of the gate table (lg, 32 floats per gate): FP32 FMAs whose operands
-// all sit in vector registers can issue two per cycle per SIMD on gfx950 when
-// two waves have one ready, where an FMA that reads a scalar register issues
-// alone.  All lanes read the same address, so each 16-byte read is a
-// broadcast.
-template <typename T, int R, int SUB>
-__device__ __forceinline__ void sweep_group_ops_lg(T (&vr)[SUB][1 << R], T (&vi)[SUB][1 << R], const fl_pass& pd,
-                                                   int g, const float* lg) {
+// The ops of register group g applied to the thread's register group, the
+// gates read from the workgroup's LDS copy of the table (lg, 32 reals per
+// gate) into vector registers: FP32 FMAs whose operands all sit in vector
+// registers can issue two per cycle per SIMD on gfx950 when two waves have one
+// ready, where an FMA that reads a scalar register issues alone.  (complex128:
+// two 64-register gates do not fit the scalar registers; fetched one ahead
+// they spilled 231 of them, 2970 us for 16 periods at L = 23 against 2420.)
+// Ops run two per iteration: the register copies that LLVM places on a loop
+// back edge after the choice of gate bits are then not needed at all.
+template <typename T, int R>
+__device__ __forceinline__ void sweep_group_ops(T (&vr)[1 << R], T (&vi)[1 << R], const fl_pass& pd, int g,
+                                                const T* lg, int gofs) {
     const int nops = pass_nops(pd, g);
     // op metadata (bit, gate index) is read with scalar loads one op ahead;
     // LDS and scalar loads share one wait counter, so the next op's scalar
     // loads are issued only after this op's gate has arrived from LDS, and
     // they complete under the op's FMAs.
-    int bit = pass_bit(pd, g, 0), idx = pass_gate(pd, g, 0);
+    int bit = pass_bit(pd, g, 0), idx = pass_gate(pd, g, 0) - gofs;
     auto run = [&](int q) {
         __builtin_amdgcn_s_waitcnt(FL_WAIT_LGKM0);
-        const float4* src = reinterpret_cast<const float4*>(lg + 32 * idx);
         T gv[32];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float4 v = src[k];
-            gv[4 * k] = v.x;
-            gv[4 * k + 1] = v.y;
-            gv[4 * k + 2] = v.z;
-            gv[4 * k + 3] = v.w;
-        }
+        load_gate_lds<T>(lg + 32 * idx, gv);
         __builtin_amdgcn_s_waitcnt(FL_WAIT_LGKM0);
         const int i = bit;
         const int qn = q + 1 < nops ? q + 1 : q;
         bit = pass_bit(pd, g, qn);
-        idx = pass_gate(pd, g, qn);
-#pragma unroll
-        for (int s = 0; s < SUB; ++s) apply_op_g<T, R>(vr[s], vi[s], i, gv);
+        idx = pass_gate(pd, g, qn) - gofs;
+        apply_op_g<T, R>(vr, vi, i, gv);
     };
     for (int q = 0; q < nops; q += 2) {
         run(q);
@@ -452,12 +339,13 @@ __device__ __forceinline__ void sweep_group_ops_lg(T (&vr)[SUB][1 << R], T (&vi)
     }
 }
 
-// Full-size tiles (K = KT), one tile per workgroup.  Every thread holds SUB
-// register groups of 2^R amplitudes and applies each gate to all of them.
-// With LG (complex64) each op reads its gate from the workgroup's LDS copy of
-// the gate table into vector registers; otherwise (complex128) the next
-// gate's matrix is fetched into scalar registers while the current one is
-// applied.
+// Tiles of 2^KT amplitudes, one per workgroup; every thread holds one register
+// group of 2^R amplitudes.  D is the descriptor: fl_pass, read with scalar
+// loads (many workgroups per CU: the loads hit the scalar cache and other
+// waves fill the wait), or fl_sweep_words, copied to LDS (short chains with at
+// most one workgroup per CU, where a scalar-cache miss per group or op would
+// add to a serial chain: 16 periods at L = 17 on 10-bit tiles take 170 us
+// against 192 with scalar loads).
 //
 // The first group is loaded straight from HBM into its register layout, and
 // the last group stored straight back, when the group's lowest bit u0 is at
@@ -465,41 +353,25 @@ __device__ __forceinline__ void sweep_group_ops_lg(T (&vr)[SUB][1 << R], T (&vi)
 // contiguous amplitudes (>= 128 bytes), so every access coalesces.  This
 // saves one LDS round trip and one barrier at each end of the pass.  Groups
 // starting lower go through the LDS transpose, as every middle group does.
-//
-// LDS slots of 13-bit complex64 tiles with 5-bit register groups (the bond
-// reduction's layout, and the sweep's with 256-thread workgroups).  Each run
-// of 16 lanes of an 8-byte LDS access must hit 16 distinct slots modulo 16.
-// In a register group with first bit u0 the 16 lanes vary the four lowest
-// tile bits outside [u0, u0 + 5): bits 5..8 for u0 = 0, {0, 6, 7, 8} for
-// u0 = 1, and so on.  fl_swz (bits 4..7 into bits 0..3) misses bit 8 and gives
-// two-way conflicts for u0 < 4; XOR-ing bits 5..8 into bits 0..3 and bit 4
-// into bit 0 keeps every one of these patterns and the pairwise tile
-// loads (lanes varying bits 1..4) conflict-free.  Like fl_swz it is linear
-// over XOR, its added term depends on none of bits 0..3, and it leaves every
-// bit from 9 up alone.
-// Sweeps with 4-bit register groups (complex64 with 512-thread workgroups,
-// complex128) keep fl_swz, which serves every u0 of a 4-bit group.
-template <typename T, int R>
-__device__ __forceinline__ uint32_t sweep_swz(uint32_t j) {
-    if constexpr (sizeof(T) == 4 && R == 5) return j ^ ((j >> 5) & 15u) ^ ((j >> 4) & 1u);
-    else return fl_swz(j);
-}
-
-template <typename T, int R, int KT, int NT, int CL, bool LG>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * 2 / 256))) void k_sweep_tiles(typename CT<T>::c* __restrict__ psi,
-                                                    const T* __restrict__ gates, int W, fl_pass pd, int ngates) {
+template <typename T, int R, int KT, int NT, int CL, int WPE, typename D>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void k_sweep_tiles(
+    typename CT<T>::c* __restrict__ psi, const T* __restrict__ gates, int W, D pd, int ngates, int gofs) {
     typedef typename CT<T>::c cplx;
-    static_assert(!LG || sizeof(T) == 4, "LDS gate table: complex64 only");
-    __shared__ __attribute__((aligned(16))) float lg[LG ? FL_MAX_GATE_TABLE * 32 : 4];
-    if constexpr (LG) {
-        const float4* src = reinterpret_cast<const float4*>(gates);
-        for (int t = threadIdx.x; t < ngates * 8; t += NT) reinterpret_cast<float4*>(lg)[t] = src[t];
-    }
+    constexpr bool LM = std::is_same<D, fl_sweep_words>::value;
+    __shared__ __attribute__((aligned(16))) T lg[FL_MAX_GATE_TABLE * 32];
+    __shared__ uint32_t meta[LM ? FL_SWEEP_WORDS : 1];
+    // gates of the pass's direction: table entries gofs .. gofs + ngates - 1
+    auto copy_tables = [&]() {
+        const fl_f32x4* src = reinterpret_cast<const fl_f32x4*>(gates + 32 * gofs);
+        for (int t = threadIdx.x; t < ngates * (int)(32 * sizeof(T) / 16); t += NT)
+            reinterpret_cast<fl_f32x4*>(lg)[t] = src[t];
+        if constexpr (LM)
+            for (int t = threadIdx.x; t < pd.nwords; t += NT) meta[t] = pd.w[t];
+    };
     constexpr int C = CL;
-    static_assert(C >= FL_DIRECT_MIN_U0, "direct register transfers need 2^FL_DIRECT_MIN_U0 contiguous amplitudes");
+    constexpr int DMIN = C < FL_DIRECT_MIN_U0 ? C : FL_DIRECT_MIN_U0;   // lowest group bit for direct transfers
     constexpr int K = KT;
-    constexpr int SUB = (1 << (K - R)) / NT;
-    static_assert(SUB >= 1, "tile too small for the workgroup");
+    static_assert((1 << (K - R)) == NT, "one register group per thread");
     constexpr int APL = (sizeof(T) == 4) ? 2 : 1;           // amplitudes per 16-byte access
     constexpr int ITER = (1 << K) / (APL * NT);
     typedef typename std::conditional<sizeof(T) == 4, float4, double2>::type v16;
@@ -509,31 +381,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * 2 / 256
     cplx* const base = psi + fl_tile_base(blockIdx.x, C, W, h);
     // Element j = APL (tid + s NT) of a tile sits at toff + s * tstride: APL NT
     // is a multiple of 2^C, so s only moves the window part of the offset.
-    static_assert((APL * NT) % (1 << C) == 0 && (APL * NT) % 256 == 0, "tile access stride");
+    static_assert((APL * NT) % (1 << C) == 0, "tile access stride");
     const uint64_t toff = fl_tile_offset(APL * threadIdx.x, C, h);
     const uint64_t tstride = (uint64_t)((APL * NT) >> C) << h;
-    // LDS slot of element j + s APL NT is sweep_swz(j) + s APL NT (the
-    // swizzle only mixes bits 0..8), and sweep_swz(j + 1) = sweep_swz(j) ^ 1
-    // for even j.
-    const uint32_t l0 = sweep_swz<T, R>(APL * threadIdx.x);
-    const bool din = ng > 0 && pass_u0(pd, 0) >= FL_DIRECT_MIN_U0;
-    const bool dout = ng > 0 && pass_u0(pd, ng - 1) >= FL_DIRECT_MIN_U0;
+    // LDS slot of element j + s APL NT is fl_swz(j) ^ fl_swz(s APL NT) (the
+    // swizzle is linear over XOR, the two have disjoint bits), and
+    // fl_swz(j + 1) = fl_swz(j) ^ 1 for even j.
+    const uint32_t l0 = fl_swz(APL * threadIdx.x);
+    int ufirst = -1, ulast = -1;   // first bits of the first and the last group
+    if constexpr (LM) {
+        ufirst = pd.ufirst;
+        ulast = pd.ulast;
+    } else if (ng > 0) {
+        ufirst = pass_u0(pd, 0);
+        ulast = pass_u0(pd, ng - 1);
+    }
+    const bool din = ufirst >= DMIN;
+    const bool dout = ulast >= DMIN;
 
-    T vr[SUB][1 << R], vi[SUB][1 << R];
-    uint32_t b0[SUB];
+    T vr[1 << R], vi[1 << R];
     // HBM offsets of a register group: element b0 | (m << u0) of the tile sits
     // at off(b0) + sum over the set bits k of m of d[k].
-    auto group_offsets = [&](int u0, uint64_t (&o)[SUB], uint64_t (&d)[R]) {
+    auto group_offsets = [&](int u0, uint64_t& o, uint64_t (&d)[R]) {
 #pragma unroll
         for (int k = 0; k < R; ++k) {
             const int q = u0 + k;
             d[k] = q < C ? (1ull << q) : (1ull << (h + q - C));
         }
-#pragma unroll
-        for (int s = 0; s < SUB; ++s) {
-            b0[s] = fl_spread(threadIdx.x + s * NT, u0, R);
-            o[s] = fl_tile_offset(b0[s], C, h);
-        }
+        o = fl_tile_offset(fl_spread(threadIdx.x, u0, R), C, h);
     };
     auto moff = [&](const uint64_t (&d)[R], int m) {
         uint64_t r = 0;
@@ -547,60 +422,54 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * 2 / 256
     // slot(b0 | m << u0) = slot(b0) ^ slot(m << u0), and slot(m << u0) is the
     // XOR of the (uniform) slots of m's set bits: one VALU XOR per element.
     // Kept for the group's write-back.
-    uint32_t la[SUB][1 << R];
+    uint32_t la[1 << R];
     auto lds_addrs = [&](int u0) {
         uint32_t bk[R];
 #pragma unroll
-        for (int k = 0; k < R; ++k) bk[k] = sweep_swz<T, R>(1u << (u0 + k)) * (uint32_t)sizeof(cplx);
+        for (int k = 0; k < R; ++k) bk[k] = fl_swz(1u << (u0 + k)) * (uint32_t)sizeof(cplx);
+        la[0] = fl_swz(fl_spread(threadIdx.x, u0, R)) * (uint32_t)sizeof(cplx);
 #pragma unroll
-        for (int s = 0; s < SUB; ++s) {
-            b0[s] = fl_spread(threadIdx.x + s * NT, u0, R);
-            la[s][0] = sweep_swz<T, R>(b0[s]) * (uint32_t)sizeof(cplx);
-#pragma unroll
-            for (int m = 1; m < (1 << R); ++m) la[s][m] = la[s][m & (m - 1)] ^ bk[__builtin_ctz(m)];
-        }
+        for (int m = 1; m < (1 << R); ++m) la[m] = la[m & (m - 1)] ^ bk[__builtin_ctz(m)];
     };
     char* const lbytes = reinterpret_cast<char*>(lds);
     auto lds_to_regs = [&]() {
 #pragma unroll
-        for (int s = 0; s < SUB; ++s)
-#pragma unroll
-            for (int m = 0; m < (1 << R); ++m) {
-                const cplx a = *reinterpret_cast<const cplx*>(lbytes + la[s][m]);
-                vr[s][m] = a.x;
-                vi[s][m] = a.y;
-            }
+        for (int m = 0; m < (1 << R); ++m) {
+            const cplx a = *reinterpret_cast<const cplx*>(lbytes + la[m]);
+            vr[m] = a.x;
+            vi[m] = a.y;
+        }
     };
     auto regs_to_lds = [&]() {
 #pragma unroll
-        for (int s = 0; s < SUB; ++s)
-#pragma unroll
-            for (int m = 0; m < (1 << R); ++m) {
-                cplx a;
-                a.x = vr[s][m];
-                a.y = vi[s][m];
-                *reinterpret_cast<cplx*>(lbytes + la[s][m]) = a;
-            }
+        for (int m = 0; m < (1 << R); ++m) {
+            cplx a;
+            a.x = vr[m];
+            a.y = vi[m];
+            *reinterpret_cast<cplx*>(lbytes + la[m]) = a;
+        }
     };
 
+    // The tile's loads are issued before those of the tables, so that their
+    // latencies overlap.
     if (din) {
-        uint64_t o[SUB], d[R];
-        group_offsets(pass_u0(pd, 0), o, d);
+        uint64_t o, d[R];
+        group_offsets(ufirst, o, d);
 #pragma unroll
-        for (int s = 0; s < SUB; ++s)
-#pragma unroll
-            for (int m = 0; m < (1 << R); ++m) {
-                const cplx a = base[o[s] + moff(d, m)];
-                vr[s][m] = a.x;
-                vi[s][m] = a.y;
-            }
+        for (int m = 0; m < (1 << R); ++m) {
+            const cplx a = base[o + moff(d, m)];
+            vr[m] = a.x;
+            vi[m] = a.y;
+        }
+        copy_tables();
     } else {
         v16 nxt[ITER];
 #pragma unroll
         for (int s = 0; s < ITER; ++s) nxt[s] = *reinterpret_cast<const v16*>(base + toff + s * tstride);
+        copy_tables();
 #pragma unroll
         for (int s = 0; s < ITER; ++s) {
-            const uint32_t l = l0 + s * (APL * NT);
+            const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
             if constexpr (sizeof(T) == 4) {
                 lds[l] = make_float2(nxt[s].x, nxt[s].y);
                 lds[l ^ 1] = make_float2(nxt[s].z, nxt[s].w);
@@ -610,49 +479,64 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * 2 / 256
         }
         __syncthreads();
         if (ng > 0) {
-            lds_addrs(pass_u0(pd, 0));
+            lds_addrs(ufirst);
             lds_to_regs();
         }
     }
 
-    // the first gate of the pass (later groups find theirs fetched by the
-    // previous group's op loop)
-    T gx[32];
-    if (!LG && ng > 0) {
-        const T* G = gates + 32 * pass_gate(pd, 0, 0);
-#pragma unroll
-        for (int k = 0; k < 32; ++k) gx[k] = G[k];
-    }
-    if (LG && din) __syncthreads();   // the gate table (other paths pass a barrier after the tile load)
-    for (int g = 0; g < ng; ++g) {
-        const int u0 = pass_u0(pd, g);
-        if (g > 0 || din) lds_addrs(u0);
-        if (g > 0) lds_to_regs();
-        if constexpr (LG)
-            sweep_group_ops_lg<T, R, SUB>(vr, vi, pd, g, lg);
-        else
-            sweep_group_ops<T, R, SUB>(vr, vi, pd, g, gates, gx);
-        if (g == ng - 1 && dout) break;
-        regs_to_lds();
-        __syncthreads();
+    if (din) __syncthreads();   // the tables (the other path passed a barrier after the tile load)
+    if constexpr (LM) {
+        auto word_at = [&](int k) { return (uint32_t)__builtin_amdgcn_readfirstlane(meta[k]); };
+        int pos = ng;   // the ops' words follow the groups' heads
+        uint32_t head = word_at(0);
+        if (din) lds_addrs(head & 255);
+        for (int g = 0; g < ng; ++g) {
+            const int nops = head >> 8;
+            uint32_t word = word_at(pos);
+            head = word_at(g + 1);   // past the last group: the first op's word, unused
+            auto run = [&]() {
+                T gv[32];
+                load_gate_lds<T>(lg + 32 * (word >> 8), gv);
+                const int i = word & 255;
+                const uint32_t next = meta[++pos];
+                apply_op_g<T, R>(vr, vi, i, gv);
+                word = __builtin_amdgcn_readfirstlane(next);
+            };
+            for (int q = 0; q < nops; q += 2) {
+                run();
+                if (q + 1 < nops) run();
+            }
+            if (g == ng - 1 && dout) break;
+            regs_to_lds();
+            if (g + 1 < ng) lds_addrs(head & 255);
+            __syncthreads();
+            if (g + 1 < ng) lds_to_regs();
+        }
+    } else {
+        for (int g = 0; g < ng; ++g) {
+            if (g > 0 || din) lds_addrs(pass_u0(pd, g));
+            if (g > 0) lds_to_regs();
+            sweep_group_ops<T, R>(vr, vi, pd, g, lg, gofs);
+            if (g == ng - 1 && dout) break;
+            regs_to_lds();
+            __syncthreads();
+        }
     }
 
     if (dout) {
-        uint64_t o[SUB], d[R];
-        group_offsets(pass_u0(pd, ng - 1), o, d);
+        uint64_t o, d[R];
+        group_offsets(ulast, o, d);
 #pragma unroll
-        for (int s = 0; s < SUB; ++s)
-#pragma unroll
-            for (int m = 0; m < (1 << R); ++m) {
-                cplx a;
-                a.x = vr[s][m];
-                a.y = vi[s][m];
-                base[o[s] + moff(d, m)] = a;
-            }
+        for (int m = 0; m < (1 << R); ++m) {
+            cplx a;
+            a.x = vr[m];
+            a.y = vi[m];
+            base[o + moff(d, m)] = a;
+        }
     } else {
 #pragma unroll
         for (int s = 0; s < ITER; ++s) {
-            const uint32_t l = l0 + s * (APL * NT);
+            const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
             if constexpr (sizeof(T) == 4) {
                 const float2 a = lds[l], b = lds[l ^ 1];
                 *reinterpret_cast<float4*>(base + toff + s * tstride) = make_float4(a.x, a.y, b.x, b.y);
@@ -1024,6 +908,19 @@ __device__ __forceinline__ void group_bond_sums(const double (&vr)[1 << R], cons
     __asm__ volatile("; end bond sums on register bits %0" ::"i"(I));
 }
 
+// LDS slots of 13-bit complex64 tiles with 5-bit register groups (the bond
+// reduction).  Each run of 16 lanes of an 8-byte LDS access must hit 16
+// distinct slots modulo 16.
+// In a register group with first bit u0 the 16 lanes vary the four lowest
+// tile bits outside [u0, u0 + 5): bits 5..8 for u0 = 0, {0, 6, 7, 8} for
+// u0 = 1, and so on.  fl_swz (bits 4..7 into bits 0..3) misses bit 8 and gives
+// two-way conflicts for u0 < 4; XOR-ing bits 5..8 into bits 0..3 and bit 4
+// into bit 0 keeps every one of these patterns and the pairwise tile
+// loads (lanes varying bits 1..4) conflict-free.  Like fl_swz it is linear
+// over XOR, its added term depends on none of bits 0..3, and it leaves every
+// bit from 9 up alone.
+__device__ __forceinline__ uint32_t rdm_swz(uint32_t j) { return j ^ ((j >> 5) & 15u) ^ ((j >> 4) & 1u); }
+
 // Bond reductions of complex64 states over full 13-bit tiles with 5-bit
 // register groups (the layout of the complex64 sweep): a cover pass's bonds
 // come packed into groups of R consecutive tile bits, every thread reads a
@@ -1054,10 +951,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * 2 / 256
     double nrm = 0.0;
     static_assert((2 * NT) % (1 << C) == 0, "tile access stride");
     // element 2 (tid + s NT) of a tile sits at toff + s tstride, LDS slot
-    // sweep_swz(j) + s 2 NT, and sweep_swz(j + 1) = sweep_swz(j) ^ 1
+    // rdm_swz(j) + s 2 NT, and rdm_swz(j + 1) = rdm_swz(j) ^ 1
     const uint64_t toff = fl_tile_offset(2 * threadIdx.x, C, h);
     const uint64_t tstride = (uint64_t)((2 * NT) >> C) << h;
-    const uint32_t l0 = sweep_swz<float, R>(2 * threadIdx.x);
+    const uint32_t l0 = rdm_swz(2 * threadIdx.x);
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const float2* src = psi + fl_tile_base(tile, C, W, h) + toff;
         float4 v[ITER];
@@ -1089,9 +986,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * 2 / 256
             // slot(b0 | m << u0) = slot(b0) ^ XOR of the slots of m's set bits
             uint32_t bk[R];
 #pragma unroll
-            for (int k = 0; k < R; ++k) bk[k] = sweep_swz<float, R>(1u << (u0 + k)) * 8u;
+            for (int k = 0; k < R; ++k) bk[k] = rdm_swz(1u << (u0 + k)) * 8u;
             uint32_t la[1 << R];
-            la[0] = sweep_swz<float, R>(fl_spread(threadIdx.x, u0, R)) * 8u;
+            la[0] = rdm_swz(fl_spread(threadIdx.x, u0, R)) * 8u;
 #pragma unroll
             for (int m = 1; m < (1 << R); ++m) la[m] = la[m & (m - 1)] ^ bk[__builtin_ctz(m)];
             double vr[1 << R], vi[1 << R];
@@ -2410,41 +2307,79 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 2)
 
 static inline uint32_t ntiles_of(const fl_geom& g) { return 1u << (g.L - g.K); }
 
-hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd,
-                        hipStream_t s) {
-    const dim3 grid(ntiles_of(g)), block(FL_NT);
-    if (dtype == 0) {
-        float2* p = (float2*)psi;
-        const float* G = (const float*)gates;
-        if (g.K == FL_KMAX_C64 && g.W > 0) {
-            if (g.C != FL_SWEEP_LOWBITS_C64) return hipErrorInvalidValue;
-            if (2 * (g.L - 1) > FL_MAX_GATE_TABLE) return hipErrorInvalidValue;
-            hipLaunchKernelGGL(
-                (k_sweep_tiles<float, FL_SWEEP_R_C64, FL_KMAX_C64, FL_SWEEP_NT_C64, FL_SWEEP_LOWBITS_C64, FL_SWEEP_LDS_GATES != 0>), grid,
-                dim3(FL_SWEEP_NT_C64), 0, s, p, G, g.W, pd, 2 * (g.L - 1));
-        } else if (g.R == 5)
-            hipLaunchKernelGGL((k_sweep<float, 5, 0, FL_KMAX_C64>), grid, block, 0, s, p, G, g.C, g.W, pd);
-        else if (g.R == 4)
-            hipLaunchKernelGGL((k_sweep<float, 4, 0, FL_KMAX_C64>), grid, block, 0, s, p, G, g.C, g.W, pd);
-        else if (g.R == 3)
-            hipLaunchKernelGGL((k_sweep<float, 3, 0, FL_KMAX_C64>), grid, block, 0, s, p, G, g.C, g.W, pd);
-        else
-            hipLaunchKernelGGL((k_sweep<float, 2, 0, FL_KMAX_C64>), grid, block, 0, s, p, G, g.C, g.W, pd);
+// The words form of a pass's descriptor, gates relative to table entry gofs.
+static bool sweep_words(const fl_pass& pd, int gofs, fl_sweep_words& w) {
+    int n = pd.ngroups;
+    for (int g = 0; g < pd.ngroups; ++g) n += pd.nops[g];
+    if (n + 1 > FL_SWEEP_WORDS) return false;
+    w.h = pd.h;
+    w.ngroups = pd.ngroups;
+    w.ufirst = pd.ngroups > 0 ? pd.u0[0] : -1;
+    w.ulast = pd.ngroups > 0 ? pd.u0[pd.ngroups - 1] : -1;
+    n = 0;
+    for (int g = 0; g < pd.ngroups; ++g) w.w[n++] = (uint32_t)pd.u0[g] | (uint32_t)pd.nops[g] << 8;
+    for (int g = 0; g < pd.ngroups; ++g)
+        for (int k = 0; k < pd.nops[g]; ++k)
+            w.w[n++] = (uint32_t)pd.opi[g][k] | (uint32_t)(pd.opg[g][k] - gofs) << 8;
+    w.w[n++] = 0;   // read one op ahead
+    w.nwords = n;
+    return true;
+}
+
+template <typename T, int R, int K, int C, int WPE, typename D>
+static hipError_t launch_tiles(const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int gofs,
+                               hipStream_t s) {
+    typedef typename CT<T>::c cplx;
+    constexpr int NT = 1 << (K - R);
+    const dim3 grid(ntiles_of(g)), block(NT);
+    if constexpr (std::is_same<D, fl_sweep_words>::value) {
+        fl_sweep_words w;
+        if (!sweep_words(pd, gofs, w)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_sweep_tiles<T, R, K, NT, C, WPE, D>), grid, block, 0, s, (cplx*)psi, (const T*)gates, g.W,
+                           w, g.L - 1, gofs);
     } else {
-        double2* p = (double2*)psi;
-        const double* G = (const double*)gates;
-        if (g.K == FL_KMAX_C128 && g.W > 0) {
-            if (g.C != FL_LOWBITS) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((k_sweep_tiles<double, 4, FL_KMAX_C128, 256, FL_LOWBITS, false>), grid, dim3(256), 0, s,
-                               p, G, g.W, pd, 0);
-        } else if (g.R == 4)
-            hipLaunchKernelGGL((k_sweep<double, 4, 0, FL_KMAX_C128>), grid, block, 0, s, p, G, g.C, g.W, pd);
-        else if (g.R == 3)
-            hipLaunchKernelGGL((k_sweep<double, 3, 0, FL_KMAX_C128>), grid, block, 0, s, p, G, g.C, g.W, pd);
-        else
-            hipLaunchKernelGGL((k_sweep<double, 2, 0, FL_KMAX_C128>), grid, block, 0, s, p, G, g.C, g.W, pd);
+        hipLaunchKernelGGL((k_sweep_tiles<T, R, K, NT, C, WPE, D>), grid, block, 0, s, (cplx*)psi, (const T*)gates, g.W,
+                           pd, g.L - 1, gofs);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd,
+                        hipStream_t s) {
+    // a pass applies gates of one direction: G_b (table entries 0 .. L-2) or G_b^dagger
+    const int nb = g.L - 1;
+    if (nb > FL_MAX_GATE_TABLE) return hipErrorInvalidValue;
+    int gofs = 0;
+    for (int q = 0; q < pd.ngroups; ++q)
+        if (pd.nops[q] > 0) gofs = pd.opg[q][0] >= nb ? nb : 0;
+    for (int q = 0; q < pd.ngroups; ++q)
+        for (int k = 0; k < pd.nops[q]; ++k)
+            if (pd.opg[q][k] < gofs || pd.opg[q][k] >= gofs + nb) return hipErrorInvalidValue;
+    if (g.W == 0) {
+        if (g.L < 2 || g.L > FL_KMAX_ONE || g.R != 2) return hipErrorInvalidValue;
+        fl_sweep_words w;
+        if (!sweep_words(pd, gofs, w)) return hipErrorInvalidValue;
+        if (dtype == 0)
+            hipLaunchKernelGGL(k_sweep_one<float>, dim3(1), dim3(FL_NT), 0, s, (float2*)psi,
+                               (const float*)gates + 32 * gofs, g.L, w);
+        else
+            hipLaunchKernelGGL(k_sweep_one<double>, dim3(1), dim3(FL_NT), 0, s, (double2*)psi,
+                               (const double*)gates + 32 * gofs, g.L, w);
+        return hipGetLastError();
+    }
+    // the geometries of sweep_geom
+    const int key = (dtype << 12) | (g.K << 8) | (g.C << 4) | g.R;
+    auto code = [](int dt, int K, int C, int R) { return (dt << 12) | (K << 8) | (C << 4) | R; };
+    if (key == code(0, 13, 4, 4)) return launch_tiles<float, 4, 13, 4, 4, fl_pass>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 12, 3, 3)) return launch_tiles<float, 3, 12, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 11, 3, 3)) return launch_tiles<float, 3, 11, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 10, 3, 2)) return launch_tiles<float, 2, 10, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 12, 6, 4)) return launch_tiles<double, 4, 12, 6, 2, fl_pass>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 12, 3, 4)) return launch_tiles<double, 4, 12, 3, 2, fl_pass>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 11, 3, 3)) return launch_tiles<double, 3, 11, 3, 2, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 10, 3, 2)) return launch_tiles<double, 2, 10, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 9, 3, 2)) return launch_tiles<double, 2, 9, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,

@@ -55,3 +55,30 @@ def test_h0_psi_and_its_sums(dtype, L):
     assert abs(E2 - np.vdot(got, got).real) < 1e-12 * E2
     assert abs(N - np.vdot(ref, ref).real) < 1e-12 * N
     assert np.array_equal(psi.cpu().numpy(), ref.astype(psi.cpu().numpy().dtype))
+
+
+# one workgroup (L <= 10), then each tile size of the short chains at its
+# shortest chain (two or more tiles) and its longest, and the first chain on
+# full tiles; a call of 2 periods and one of 3 (another geometry in complex128)
+@pytest.mark.parametrize("dagger", [False, True])
+@pytest.mark.parametrize("dtype,L,n", [("c64", 3, 5), ("c64", 10, 5), ("c64", 11, 5), ("c64", 18, 3), ("c64", 19, 3),
+                                       ("c64", 20, 3), ("c64", 21, 2), ("c128", 3, 5), ("c128", 10, 5), ("c128", 11, 5),
+                                       ("c128", 17, 3), ("c128", 18, 3), ("c128", 19, 3), ("c128", 20, 2),
+                                       ("c128", 20, 3), ("c128", 21, 18)])
+def test_sweep_at_the_edges_of_its_tile_sizes(dtype, L, n, dagger):
+    """Every amplitude after n periods of distinct Haar-random gates.  An
+    amplitude passes n (L-1) gates: a rounding of a gate's entries shifts the
+    state by up to one unit in the last place each (they add up in line at
+    worst), the FMAs by random ones."""
+    say(f"case: sweep {dtype} L={L} n={n} dagger={dagger}")
+    G = fin.random_unitaries(L - 1, 4, 500 + L)
+    ctx = fl.fl_create(L, dtype)
+    fl.fl_set_gates(ctx, G)
+    psi = fl.new_state(ctx)
+    psi.copy_(torch.from_numpy(fin.random_state(L, L)).to(psi.dtype))
+    ref = psi.cpu().numpy().astype(np.complex128)
+    want = O.evolve(ref, L, G, n, dagger=dagger)
+    fl.fl_apply_period(ctx, psi, n, dagger=dagger)
+    got = psi.cpu().numpy().astype(np.complex128)
+    ulp = 6e-8 if dtype == "c64" else 1.2e-16
+    assert np.linalg.norm(got - want) < n * (L - 1) * ulp * np.linalg.norm(want)
