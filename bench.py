@@ -613,7 +613,7 @@ def main():
     periods_per_s = periods / wall
 
     step_passes = plan_passes(fl, L, m)
-    readout_passes = int(fl.fl_plan_query(L, "c64", 6 if L > 13 else 2, 1, False)[3])
+    readout_passes = int(fl.fl_plan_query(L, "c64", 2, 1, False)[3])
     # ---- the energy readout alone (fl_expect_energy synchronises; best of five)
     readout_ms = float("inf")
     for _ in range(5):

@@ -257,11 +257,12 @@ int fl_host_window_matrix(const double *G, const int *pos, int nops, int mode, d
 int fl_host_window_overlaps(const double *Q, const double *G, const int *pos, int nops, double *out);
 
 /* The plan fl_apply_period would run for n periods (kind 0 = sweep,
- * 1 = reverse sweep of the gradient, 2 = energy / density-matrix cover on
- * 12-bit tiles (complex128, and complex64 with L <= 13), 3 = cover used for
- * H0 psi by a plain-sweep context, 4 = dense 6-qubit-window sweep, 5 = dense 4-qubit-window sweep,
- * 6 = energy / density-matrix cover of complex64 states with L >= 14: 13-bit
- * tiles, bonds packed into 5-bit register groups), flattened as int32:
+ * 1 = reverse sweep of the gradient, 2 = energy / density-matrix cover (the
+ * bonds of each pass; full tiles with 4 low bits from L = 13 complex64, 12
+ * complex128), 3 = cover used for H0 psi by a plain-sweep context, 4 = dense
+ * 6-qubit-window sweep, 5 = dense 4-qubit-window sweep, 6 = a cover of
+ * complex64 states with L >= 14 on 13-bit tiles with 6 low bits, bonds packed
+ * into 5-bit register groups), flattened as int32:
  * [C, W, R, npasses, {h, ngroups, flags, {u0, nops, {i, gate, slot}*}*}*].
  * Writes at most cap words to buf (may be NULL) and the required count to
  * *needed. */

@@ -10,6 +10,7 @@
 #include <complex>
 #include <cstdio>
 #include <cstring>
+#include <algorithm>
 #include <array>
 #include <map>
 #include <string>
@@ -46,7 +47,8 @@ int fail_hip(hipError_t e, const char* what) {
 
 constexpr int kPlanBlock = 16;        // periods per planned block
 constexpr int kMaxGatesPerPass = 96;  // cap on gates the planner puts in one pass
-constexpr int kReduceGrid = 2048;     // workgroups of the persistent reduction kernels
+constexpr int kReduceGrid = 2048;     // most workgroups of the reduction kernels (rows of the partials)
+constexpr int kRdmGrid = 512;          // workgroups of the bond reductions: two per CU, persistent
 constexpr int kApplyHGrid = 256;      // workgroups of H0 psi: one per CU (its two tiles fill the LDS)
 constexpr int kAdjGrid = 1024;        // workgroups of the persistent reverse pass
 constexpr int kAdjLowBits = 4;       // low tile bits of the reverse pass (its kernel takes C at run time)
@@ -88,6 +90,58 @@ fl_geom sweep_geom(int L, int dtype, int64_t n) {
     if (k == 11 || (k == 12 && c64)) return fl::make_geom(L, k, 3, 3);
     if (!c64 && n >= 3) return fl::make_geom(L, FL_KMAX_C128, 4, 3);
     return plain_geom(L, dtype);
+}
+// Geometry of the energy / density-matrix reduction: full tiles with 4 low
+// bits (a chain of exactly one full tile takes them as 4 low bits plus a
+// window too); shorter chains in one tile.
+fl_geom rdm_geom(int L, int dtype) {
+    const int kmax = kmax_of(dtype);
+    if (L < kmax) return fl::make_geom(L, FL_KMAX_RDM, 2);
+    fl_geom g;
+    g.L = L;
+    g.C = FL_RDM_LOWBITS;
+    g.W = kmax - FL_RDM_LOWBITS;
+    g.K = kmax;
+    g.R = 2;
+    return g;
+}
+
+// The bond cover of g with each pass's bonds in 1, 2 or 4 windows of 4 tile
+// bits (the kernel shares its waves among the windows evenly): as few as hold
+// the bonds at three each, and the bonds spread over them evenly (8 bonds: 4
+// windows of 2, not 3, 3, 2 and an idle quarter).
+std::vector<fl::rdm_desc> cover_windows(const fl_geom& g) {
+    std::vector<fl::rdm_desc> out;
+    for (const fl_pass& p : fl::plan_cover(g)) {
+        std::vector<std::pair<int, int>> bonds;   // (tile bit, bond)
+        for (int k = 0; k < p.ngroups; ++k) bonds.emplace_back((int)p.u0[k], (int)p.ops[k][0]);
+        std::sort(bonds.begin(), bonds.end());
+        size_t done = 0;
+        bool first = true;
+        while (done < bonds.size()) {
+            const size_t left = std::min<size_t>(bonds.size() - done, 12);
+            fl::rdm_desc d;
+            std::memset(&d, 0, sizeof(d));
+            d.h = p.h;
+            d.flags = first ? p.flags : 0;
+            d.nwin = left <= 3 ? 1 : left <= 6 ? 2 : 4;
+            const size_t end = done + left;
+            for (int w = 0; w < d.nwin; ++w) {
+                const size_t share = (end - done + (size_t)(d.nwin - w) - 1) / (size_t)(d.nwin - w);
+                if (share == 0) continue;   // an empty window: mask 0
+                d.u0[w] = std::min(bonds[done].first, g.K - 4);
+                for (size_t k = 0; k < share && bonds[done].first + 1 < d.u0[w] + 4; ++k) {
+                    const int j = bonds[done].first - d.u0[w];
+                    d.mask[w] |= 1 << j;
+                    d.bond[w][j] = bonds[done].second;
+                    if (++done == end) break;
+                }
+            }
+            first = false;
+            out.push_back(d);   // bonds that no window reached come in another pass
+        }
+    }
+    return out;
 }
 size_t amp_bytes(int dtype) { return dtype == FL_C64 ? 8 : 16; }
 
@@ -146,10 +200,8 @@ struct fl_ctx {
     std::vector<fl_pass> cover;       // bond cover of the sweep geometry (H0 psi of single-tile chains)
     fl_geom geom_h{};                 // the same tiles with 4-bit windows (longer chains):
     std::vector<fl_pass> cover_h;     // the cover's bonds packed into windows
-    std::vector<fl_pass> cover_rdm;   // bond cover of the reduction geometry
-    bool use_grp = false;             // complex64, L >= 14: the reductions run on 13-bit tiles
-    fl_geom geom_grp{};               // (L, 13, 5)
-    std::vector<fl_pass> cover_grp;   // bond cover of geom_grp in register groups
+    std::vector<fl_pass> cover_rdm;   // bond cover of the reductions of chains shorter than a full tile
+    std::vector<fl::rdm_desc> cover_win;   // the cover of longer chains, in windows (geom_rdm: full tiles)
 };
 
 namespace {
@@ -369,16 +421,11 @@ void rho_from16(const double* v, cd* rho) {
 
 // The bond reductions of psi into partials[grid][L][16] (grid <= maxgrid).
 int launch_cover_rdm(fl_ctx* c, const void* psi, double* partials, int maxgrid, int* grid_out) {
-    if (c->use_grp) {
-        const int grid = (int)std::min<uint32_t>(ntiles(c->geom_grp), (uint32_t)maxgrid);
-        for (const fl_pass& p : c->cover_grp) {
-            hipError_t e = fl::launch_rdm_groups(c->geom_grp, psi, p, partials, grid, c->L, c->stream);
-            if (e != hipSuccess) return fail_hip(e, "k_rdm_groups launch");
-        }
-        *grid_out = grid;
-        return FL_OK;
+    const int grid = (int)std::min<uint32_t>(ntiles(c->geom_rdm), (uint32_t)std::min(maxgrid, kRdmGrid));
+    for (const fl::rdm_desc& p : c->cover_win) {
+        hipError_t e = fl::launch_rdm_windows(c->dtype, c->geom_rdm, psi, p, partials, grid, c->L, c->stream);
+        if (e != hipSuccess) return fail_hip(e, "k_rdm_windows launch");
     }
-    const int grid = (int)std::min<uint32_t>(ntiles(c->geom_rdm), (uint32_t)maxgrid);
     for (const fl_pass& p : c->cover_rdm) {
         hipError_t e = fl::launch_rdm(c->dtype, c->geom_rdm, psi, p, partials, grid, c->L, c->stream);
         if (e != hipSuccess) return fail_hip(e, "k_rdm launch");
@@ -746,7 +793,6 @@ int fl_create(fl_ctx** ctx, int L, int dtype, int variant, void* hip_stream) {
               : (variant == FL_DENSE4_FP32) ? fl::make_geom(L, FL_KMAX_C64, 4, FL_DENSE4_LOWBITS)
                                             : fl::make_geom(L, FL_KMAX_C64, 6, kDense6LowBits);
     c->geom_adj = fl::make_geom(L, FL_KMAX_ADJ, 4, kAdjLowBits);
-    c->geom_rdm = fl::make_geom(L, FL_KMAX_RDM, 2);
     if (c->geom.W > 0) {
         c->geom_h = c->geom;
         c->geom_h.R = 4;
@@ -754,12 +800,11 @@ int fl_create(fl_ctx** ctx, int L, int dtype, int variant, void* hip_stream) {
     } else {
         c->cover = fl::plan_cover(c->geom);
     }
-    c->cover_rdm = fl::plan_cover(c->geom_rdm);
-    c->use_grp = FL_RDM_GROUPS && dtype == FL_C64 && L > FL_KMAX_C64;
-    if (c->use_grp) {
-        c->geom_grp = fl::make_geom(L, FL_KMAX_C64, FL_RDM_R_C64);
-        c->cover_grp = fl::plan_cover_groups(c->geom_grp);
-    }
+    c->geom_rdm = rdm_geom(L, dtype);
+    if (c->geom_rdm.W > 0)
+        c->cover_win = cover_windows(c->geom_rdm);
+    else
+        c->cover_rdm = fl::plan_cover(c->geom_rdm);
     const int nb = L - 1;
     const size_t rb = dtype == FL_C64 ? 4 : 8;
     hipError_t e = hipSuccess;
@@ -1353,7 +1398,7 @@ int fl_plan_query(int L, int dtype, int kind, int64_t n, int dagger, int32_t* bu
         for (int64_t i = 0; i < q; ++i) plan.insert(plan.end(), pb.begin(), pb.end());
         plan.insert(plan.end(), pr.begin(), pr.end());
     } else if (kind == 2) {
-        g = fl::make_geom(L, FL_KMAX_RDM, 2);
+        g = rdm_geom(L, dtype);
         plan = fl::plan_cover(g);
     } else if (kind == 4 || kind == 5) {
         if (dtype != FL_C64 || L < (kind == 4 ? 11 : FL_KMAX_C64))
@@ -1372,7 +1417,7 @@ int fl_plan_query(int L, int dtype, int kind, int64_t n, int dagger, int32_t* bu
         plan = fl::plan_cover(g);
     } else if (kind == 6) {
         if (dtype != FL_C64 || L <= FL_KMAX_C64) return fail(FL_EINVAL, "the grouped cover needs complex64 and L >= 14");
-        g = fl::make_geom(L, FL_KMAX_C64, FL_RDM_R_C64);
+        g = fl::make_geom(L, FL_KMAX_C64, 5);
         plan = fl::plan_cover_groups(g);
     } else {
         return fail(FL_EINVAL, "kind must be 0..6");

@@ -37,7 +37,7 @@
 #define FL_KMAX_ADJ 12       // tile bits of the two-state adjoint pass (complex64)
 #define FL_WIN4_MAX_GROUPS 14  // register groups per pass of a 4-qubit-window plan (the reverse pass keeps one window-overlap sum per group)
 #define FL_WIN4_NT 512         // threads of the 4-qubit-window reverse pass (13-bit tiles of two states)
-#define FL_KMAX_RDM 12       // tile bits of the energy / density-matrix reduction
+#define FL_KMAX_RDM 12       // tile bits of the reduction of chains shorter than a full tile
 #define FL_MAX_SLOTS 16      // distinct reduction slots per pass
 #define FL_KMAX_ONE 10       // longest chain whose sweep runs in one workgroup
 #define FL_SWEEP_WORDS 144   // words of a sweep pass's descriptor in words form: groups + ops + 1
@@ -48,11 +48,7 @@
 #ifndef FL_SWEEP_R_C64
 #define FL_SWEEP_R_C64 4     // register bits per group of the complex64 sweep
 #endif
-#define FL_RDM_NT_C64 256    // threads per workgroup of the complex64 bond reduction on 13-bit tiles
-#define FL_RDM_R_C64 5       // register bits per group of that reduction
-#ifndef FL_RDM_GROUPS
-#define FL_RDM_GROUPS 1      // complex64 reductions on 13-bit tiles with register groups (L >= 14)
-#endif
+#define FL_RDM_LOWBITS 4     // C of the energy / density-matrix reduction on full tiles
 #ifndef FL_DENSE4_LOWBITS
 #define FL_DENSE4_LOWBITS 4  // C of the 4-qubit-window form (forward and reverse pass)
 #endif

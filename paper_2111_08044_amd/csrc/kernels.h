@@ -8,12 +8,19 @@
 namespace fl {
 
 hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, hipStream_t s);
+// single-tile chains shorter than a full tile
 hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,
                       int nslot, hipStream_t s);
-// complex64 bond reductions over full 13-bit tiles; pd from plan_cover_groups
-// of geometry (L, 13, 5) (L >= 14)
-hipError_t launch_rdm_groups(const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,
-                             int nslot, hipStream_t s);
+// bond reductions over full tiles (13 bits complex64, 12 bits complex128): a
+// pass's bonds in 1, 2 or 4 windows of 4 tile bits, a bond on window bits
+// (j, j + 1) where mask bit j is set; flags & 1: also the norm
+struct rdm_desc {
+    int32_t h, flags, nwin;
+    int32_t u0[4], mask[4];
+    int32_t bond[4][3];
+};
+hipError_t launch_rdm_windows(int dtype, const fl_geom& g, const void* psi, const rdm_desc& pd, double* partials,
+                              int grid, int nslot, hipStream_t s);
 hipError_t launch_finalize(const double* partials, int nblocks, int nvals, double* out, hipStream_t s);
 // <H0> and the norm from finalized bond sums red[L*16] and FP64 bond terms h64[(L-1)*32]:
 // out[0] = <H0>, out[1] = <psi|psi>; rdm (may be NULL) = [L-1][4][4] complex

@@ -3,7 +3,7 @@
 //  k_sweep_tiles / k_sweep
 //             fused gate sweep: one HBM read + write of the state applies
 //             every gate of a pass (Sec. II Eq. (2), fused as in Sec. II).
-//  k_rdm_groups / k_rdm_tiles / k_rdm
+//  k_rdm_windows / k_rdm
 //             two-site reduced density matrices of the bonds of a pass (plus
 //             the norm): exact products of the stored amplitudes, FP64 sums
 //             (Sec. II Eq. (1); Sec. IV Eq. (10)).
@@ -677,7 +677,6 @@ __device__ __forceinline__ T wave_transpose_reduce(T (&v)[NV]) {
 // partials layout: [gridDim.x][nslot][16] doubles, slot = bond, slot L-1 = norm.
 
 #define FL_RDM_MAXG 16
-#define FL_RDM_TILE_MAXG 13   // bond slots of a full-tile cover pass (K-1 <= 12) + the norm
 
 // Adds one quad (amplitudes a_0..a_3 of a bond's local index) to the 16
 // density-matrix sums: [0..3] |a_l|^2, then for each pair l < m the real and
@@ -779,270 +778,198 @@ __global__ __launch_bounds__(FL_NT) void k_rdm(const typename CT<T>::c* __restri
     }
 }
 
-// Full-size tiles: persistent workgroups with the next tile prefetched into
-// registers (as in k_sweep_tiles).  All sums are FP64: complex64 amplitudes
-// are widened to FP64, so every product of two of them is exact and only the
-// FP64 additions round; complex128 states use FP64 throughout.
-template <typename T, int KT, int NT>
-__global__ __launch_bounds__(NT) void k_rdm_tiles(const typename CT<T>::c* __restrict__ psi, int W, uint32_t ntiles,
-                                                  fl_pass pd, double* __restrict__ partials, int nslot) {
+// Full tiles (W > 0, or one tile of exactly 2^K amplitudes).  The bonds of a
+// pass come in 1, 2 or 4 windows of 4 consecutive tile bits (up to 3 bonds
+// each); wave w sums window w mod nwin over all tiles of its workgroup, so a
+// lane keeps a window's sums in registers from tile to tile and the wave trees
+// run once every FL_RDM_FLUSH tiles instead of once per tile and bond.
+//
+// A window's bonds share their products.  The 16 |a_m|^2 give every diagonal
+// entry (and the norm); the products of amplitude pairs that differ in bit k
+// are summed by the values of the bits beside k, and give the entries 01, 23
+// of the bond above and 02, 13 of the bond below; pairs that differ in both
+// bits of a bond give 03 and 12.  That is 16 FMA an amplitude for three bonds
+// (8 each when every bond forms its own 16 sums).
+//
+// All sums are FP64: complex64 amplitudes are widened first, so every product
+// of two of them is exact and only the FP64 additions round, in chains of at
+// most FL_RDM_FLUSH tiles and trees above them.
+//
+// Bound by the vector ALUs: at L = 27 the three passes issue 1.69e8, 1.35e8
+// and 0.86e8 instructions, 87%, 77% and 60% of their 437, 390 and 320 us at
+// the 2.3 ns a wave instruction takes here (the last pass, 6 bonds, waits for
+// its reads the rest).  Readout at L = 27: 1.09 ms (1.54 with 16 sums per bond
+// reduced per tile, on four passes of 7-bit windows), L = 30: 11.9 ms (13.4),
+// complex128 L = 26: 0.70 ms (1.21).  3 low bits (64-byte runs) would save a
+// pass at L = 30 but read slower: 11.8 ms there, 1.25 ms at L = 27.
+// partials as in k_rdm.
+#define FL_RDM_FLUSH 16
+
+template <typename T, int K, int CL, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_rdm_windows(
+    const typename CT<T>::c* __restrict__ psi, int W, uint32_t ntiles, rdm_desc pd, double* __restrict__ partials,
+    int nslot) {
     typedef typename CT<T>::c cplx;
-    constexpr int C = FL_LOWBITS;
-    constexpr int K = KT;
-    constexpr int APL = (sizeof(T) == 4) ? 2 : 1;
+    constexpr int C = CL, NW = NT / 64;
+    constexpr int APL = sizeof(T) == 4 ? 2 : 1;
     constexpr int ITER = (1 << K) / (APL * NT);
-    constexpr int NW = NT / 64;
-    constexpr int NG = FL_RDM_TILE_MAXG;
-    typedef typename std::conditional<sizeof(T) == 4, float4, double2>::type v16;
-    __shared__ cplx lds[1 << K];
-    __shared__ double wacc[NW][NG][16];
-    const int h = pd.h;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int t = threadIdx.x; t < NW * NG * 16; t += NT) (&wacc[0][0][0])[t] = 0.0;
-    double nrm = 0.0;
+    constexpr int UNITS = (1 << (K - 4)) / 64;   // wave-sized parts of a window's register groups
+    static_assert(NW % 4 == 0 && UNITS % NW == 0, "1, 2 or 4 windows share the waves evenly");
+    constexpr bool PREF = sizeof(T) == 4;   // complex128 has no registers left for the next tile
+    typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
+    __shared__ __attribute__((aligned(16))) cplx lds[1 << K];
+    __shared__ double wacc[NW][4][16];   // per wave: the window's three bonds, and the norm
+    const int h = pd.h, nwin = pd.nwin;
+    // readfirstlane: everything that hangs on the window is uniform
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int win = wave & (nwin - 1), part = wave / nwin, nunit = UNITS * nwin / NW;
+    const int u0 = pd.u0[win], mask = pd.mask[win];   // bit j of mask: a bond on window bits (j, j + 1)
+    for (int t = threadIdx.x; t < NW * 4 * 16; t += NT) (&wacc[0][0][0])[t] = 0.0;
+    __syncthreads();
     static_assert((APL * NT) % (1 << C) == 0 && (APL * NT) % 256 == 0, "tile access stride");
     const uint64_t toff = fl_tile_offset(APL * threadIdx.x, C, h);
     const uint64_t tstride = (uint64_t)((APL * NT) >> C) << h;
-    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint32_t l0 = fl_swz(APL * threadIdx.x);
+    uint32_t bk[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bk[k] = fl_swz(1u << (u0 + k)) * (uint32_t)sizeof(cplx);
+
+    double P[16], S[24], D[12];   // S: bit k's sums at 0, 4, 12, 20, (re, im) by its neighbours; D: 03, 12 of each bond
+    auto clear = [&]() {
+#pragma unroll
+        for (int m = 0; m < 16; ++m) P[m] = 0.0;
+#pragma unroll
+        for (int m = 0; m < 24; ++m) S[m] = 0.0;
+#pragma unroll
+        for (int m = 0; m < 12; ++m) D[m] = 0.0;
+    };
+    clear();
+    // the lanes' sums to the wave's accumulators, as the 16 reals of each bond
+    auto flush = [&]() {
+        auto add = [&](int row, double (&r)[16]) {
+            const double red = wave_transpose_reduce<double, 16>(r);   // lane l: the sum of value l >> 2
+            if ((lane & 3) == 0) wacc[wave][row][lane >> 2] += red;
+        };
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            if ((mask >> j) & 1) {
+                double r[16];
+#pragma unroll
+                for (int l = 0; l < 4; ++l) {
+                    r[l] = 0.0;
+#pragma unroll
+                    for (int m = 0; m < 16; ++m)
+                        if (((m >> j) & 3) == l) r[l] += P[m];
+                }
+                // bit k's sum at neighbour values (lo, hi); entries 01, 23: bit j by
+                // its upper neighbour; 02, 13: bit j + 1 by its lower neighbour
+                auto single = [&](int k, int lo, int hi, int c) {
+                    const int off = k == 0 ? 0 : k == 1 ? 4 : k == 2 ? 12 : 20;
+                    return S[off + 2 * (k == 0 ? hi : k == 3 ? lo : lo + 2 * hi) + c];
+                };
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    r[4 + c] = j == 0 ? single(0, 0, 0, c) : single(j, 0, 0, c) + single(j, 1, 0, c);
+                    r[14 + c] = j == 0 ? single(0, 0, 1, c) : single(j, 0, 1, c) + single(j, 1, 1, c);
+                    r[6 + c] = j == 2 ? single(3, 0, 0, c) : single(j + 1, 0, 0, c) + single(j + 1, 0, 1, c);
+                    r[12 + c] = j == 2 ? single(3, 1, 0, c) : single(j + 1, 1, 0, c) + single(j + 1, 1, 1, c);
+                    r[8 + c] = D[4 * j + c];
+                    r[10 + c] = D[4 * j + 2 + c];
+                }
+                add(j, r);
+            }
+        if (win == 0 && (pd.flags & 1)) {
+            double n[1] = {0.0};
+#pragma unroll
+            for (int m = 0; m < 16; ++m) n[0] += P[m];
+            const double red = wave_transpose_reduce<double, 1>(n);
+            if (lane == 0) wacc[wave][3][0] += red;
+        }
+        clear();
+    };
+    v16 v[ITER];
+    auto fetch = [&](uint32_t tile) {
         const cplx* src = psi + fl_tile_base(tile, C, W, h) + toff;
-        v16 v[ITER];
+        // streaming: each amplitude is read once per pass
 #pragma unroll
-        for (int s = 0; s < ITER; ++s) v[s] = *reinterpret_cast<const v16*>(src + s * tstride);
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < ITER; ++s) {
-            const uint32_t j = APL * (threadIdx.x + s * NT);
-            if constexpr (sizeof(T) == 4) {
-                lds[fl_swz(j)] = make_float2(v[s].x, v[s].y);
-                lds[fl_swz(j + 1)] = make_float2(v[s].z, v[s].w);
-                nrm = fma((double)v[s].x, (double)v[s].x, fma((double)v[s].y, (double)v[s].y, nrm));
-                nrm = fma((double)v[s].z, (double)v[s].z, fma((double)v[s].w, (double)v[s].w, nrm));
-            } else {
-                lds[fl_swz(j)] = v[s];
-                nrm = fma(v[s].x, v[s].x, fma(v[s].y, v[s].y, nrm));
-            }
-        }
-        __syncthreads();
-        for (int g = 0; g < pd.ngroups; ++g) {
-            const int u = pass_u0(pd, g);
-            double r[16];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) r[k] = 0.0;
-            // slot(spread(tid + NT s) | l << u) = slot(spread(tid)) ^ slot(spread(NT s)) ^ slot(l << u)
-            // (the swizzle is linear over XOR; the three parts have disjoint
-            // bits), the last two uniform: one VALU XOR per read
-            const uint32_t vb = fl_swz(fl_spread(threadIdx.x, u, 2)) * (uint32_t)sizeof(cplx);
-            constexpr int NS = (1 << (K - 2)) / NT;
-            // all reads of the group first, so that their latencies overlap
-            cplx q[NS][4];
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const uint32_t us = fl_swz(fl_spread((uint32_t)(s * NT), u, 2)) * (uint32_t)sizeof(cplx);
-#pragma unroll
-                for (int l = 0; l < 4; ++l) {
-                    const uint32_t ul = us ^ (fl_swz((uint32_t)l << u) * (uint32_t)sizeof(cplx));
-                    q[s][l] = *reinterpret_cast<const cplx*>(reinterpret_cast<const char*>(lds) + (vb ^ ul));
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                double ar[4], ai[4];
-#pragma unroll
-                for (int l = 0; l < 4; ++l) {
-                    ar[l] = (double)q[s][l].x;
-                    ai[l] = (double)q[s][l].y;
-                }
-                rdm_quad<double>(ar, ai, r);
-            }
-            // lane l holds the sum of value l >> 2; one lane of each four adds
-            // it, the others add zero (an LDS atomic with every lane active)
-            const double red = wave_transpose_reduce<double, 16>(r);
-            __hip_atomic_fetch_add(&wacc[wave][g][lane >> 2], (lane & 3) == 0 ? red : 0.0, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-    }
-    double nv[1] = {nrm};
-    const double ntot = wave_transpose_reduce<double, 1>(nv);
-    __syncthreads();
-    if (lane == 0) wacc[wave][NG - 1][0] = ntot;   // the norm uses the last slot row
-    __syncthreads();
-    for (int t = threadIdx.x; t < (pd.ngroups + 1) * 16; t += NT) {
-        const int g = t >> 4, v = t & 15;
-        const int gg = (g < pd.ngroups) ? g : NG - 1;
-        if (g == pd.ngroups && v > 0) continue;
-        double sum = 0.0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) sum += wacc[w][gg][v];
-        if (g < pd.ngroups) {
-            partials[((size_t)blockIdx.x * nslot + pd.ops[g][0]) * 16 + v] = sum;
-        } else if (pd.flags & 1) {
-            partials[((size_t)blockIdx.x * nslot + (nslot - 1)) * 16] = sum;
-        }
-    }
-}
-
-template <int A, int B, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (A < B) {
-        f(std::integral_constant<int, A>{});
-        static_for<A + 1, B>(f);
-    }
-}
-
-// Density-matrix sums of the bond on register bits (I, I+1) of a register group.
-template <int R, int I>
-__device__ __forceinline__ void group_bond_sums(const double (&vr)[1 << R], const double (&vi)[1 << R], double (&r)[16]) {
-    // (immediate-operand markers keep the bit variants apart, as in apply_pair_g)
-    __asm__ volatile("; bond sums on register bits %0" ::"i"(I));
-#pragma unroll
-    for (int c = 0; c < (1 << R) / 4; ++c) {
-        const int b = (c & ((1 << I) - 1)) | ((c >> I) << (I + 2));
-        double ar[4], ai[4];
-#pragma unroll
-        for (int l = 0; l < 4; ++l) {
-            ar[l] = vr[b | (l << I)];
-            ai[l] = vi[b | (l << I)];
-        }
-        rdm_quad<double>(ar, ai, r);
-    }
-    __asm__ volatile("; end bond sums on register bits %0" ::"i"(I));
-}
-
-// LDS slots of 13-bit complex64 tiles with 5-bit register groups (the bond
-// reduction).  Each run of 16 lanes of an 8-byte LDS access must hit 16
-// distinct slots modulo 16.
-// In a register group with first bit u0 the 16 lanes vary the four lowest
-// tile bits outside [u0, u0 + 5): bits 5..8 for u0 = 0, {0, 6, 7, 8} for
-// u0 = 1, and so on.  fl_swz (bits 4..7 into bits 0..3) misses bit 8 and gives
-// two-way conflicts for u0 < 4; XOR-ing bits 5..8 into bits 0..3 and bit 4
-// into bit 0 keeps every one of these patterns and the pairwise tile
-// loads (lanes varying bits 1..4) conflict-free.  Like fl_swz it is linear
-// over XOR, its added term depends on none of bits 0..3, and it leaves every
-// bit from 9 up alone.
-__device__ __forceinline__ uint32_t rdm_swz(uint32_t j) { return j ^ ((j >> 5) & 15u) ^ ((j >> 4) & 1u); }
-
-// Bond reductions of complex64 states over full 13-bit tiles with 5-bit
-// register groups (the layout of the complex64 sweep): a cover pass's bonds
-// come packed into groups of R consecutive tile bits, every thread reads a
-// group's 2^R amplitudes from LDS once and forms the sums of all the group's
-// bonds from registers (8 quads per bond and thread), so each LDS word is read
-// once per group rather than once per bond.  The group's amplitudes are
-// widened to FP64 when they leave LDS, so each product of two FP32 values is
-// exact; each lane sums its quads in FP64, the wave tree is FP64 and its
-// result goes into FP64 per-wave LDS accumulators.  The norm is an FP64 sum
-// as well.  Persistent workgroups; partials as in k_rdm_tiles.
-template <int R, int KT, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT * 2 / 256))) void k_rdm_groups(
-    const float2* __restrict__ psi, int W, uint32_t ntiles, fl_pass pd, double* __restrict__ partials, int nslot) {
-    constexpr int C = FL_LOWBITS;
-    constexpr int K = KT;
-    static_assert((1 << (K - R)) == NT, "one register group per thread");
-    constexpr int ITER = (1 << K) / (2 * NT);
-    constexpr int NW = NT / 64;
-    constexpr int NS = FL_RDM_TILE_MAXG;   // bond rows (K - 1 at most) + the norm
-    static_assert(K - 1 < NS, "bond rows");
-    __shared__ __attribute__((aligned(16))) float2 lds[1 << K];
-    __shared__ double wacc[NW][NS][16];
-    const char* const lb = reinterpret_cast<const char*>(lds);
-    const int h = pd.h;
-    const int ng = pd.ngroups;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int t = threadIdx.x; t < NW * NS * 16; t += NT) (&wacc[0][0][0])[t] = 0.0;
-    double nrm = 0.0;
-    static_assert((2 * NT) % (1 << C) == 0, "tile access stride");
-    // element 2 (tid + s NT) of a tile sits at toff + s tstride, LDS slot
-    // rdm_swz(j) + s 2 NT, and rdm_swz(j + 1) = rdm_swz(j) ^ 1
-    const uint64_t toff = fl_tile_offset(2 * threadIdx.x, C, h);
-    const uint64_t tstride = (uint64_t)((2 * NT) >> C) << h;
-    const uint32_t l0 = rdm_swz(2 * threadIdx.x);
+        for (int s = 0; s < ITER; ++s) v[s] = __builtin_nontemporal_load(reinterpret_cast<const v16*>(src + s * tstride));
+    };
+        if (PREF && blockIdx.x < ntiles) fetch(blockIdx.x);
+    int held = 0;
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const float2* src = psi + fl_tile_base(tile, C, W, h) + toff;
-        float4 v[ITER];
+        if (!PREF) fetch(tile);
+        __syncthreads();   // the previous tile's LDS reads are done
 #pragma unroll
         for (int s = 0; s < ITER; ++s) {
-            // streaming: each amplitude is read once per pass
-            const fl_f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const fl_f32x4*>(src + s * tstride));
-            v[s] = make_float4(t[0], t[1], t[2], t[3]);
-        }
-        __syncthreads();   // the previous tile's LDS reads (and the accumulator reset) are done
-#pragma unroll
-        for (int s = 0; s < ITER; ++s) {
-            const uint32_t l = l0 + s * (2 * NT);
-            lds[l] = make_float2(v[s].x, v[s].y);
-            lds[l ^ 1] = make_float2(v[s].z, v[s].w);
-        }
-        if (pd.flags & 1) {
-#pragma unroll
-            for (int s = 0; s < ITER; ++s) {
-                nrm = fma((double)v[s].x, (double)v[s].x, fma((double)v[s].y, (double)v[s].y, nrm));
-                nrm = fma((double)v[s].z, (double)v[s].z, fma((double)v[s].w, (double)v[s].w, nrm));
+            const uint32_t l = l0 + s * (APL * NT);
+            if constexpr (sizeof(T) == 4) {
+                lds[l] = make_float2(v[s][0], v[s][1]);
+                lds[l ^ 1] = make_float2(v[s][2], v[s][3]);
+            } else {
+                lds[l] = make_double2(v[s][0], v[s][1]);
             }
         }
         __syncthreads();
-        int row = 0;
-        for (int g = 0; g < ng; ++g) {
-            const int u0 = pass_u0(pd, g);
-            const int nops = pass_nops(pd, g);
-            // slot(b0 | m << u0) = slot(b0) ^ XOR of the slots of m's set bits
-            uint32_t bk[R];
+        if (PREF && tile + gridDim.x < ntiles) fetch(tile + gridDim.x);
+        for (int q = 0; q < nunit; ++q) {
+            const uint32_t o = (uint32_t)(part * nunit + q) * 64 + lane;
+            uint32_t la[16];
+            la[0] = fl_swz(fl_spread(o, u0, 4)) * (uint32_t)sizeof(cplx);
 #pragma unroll
-            for (int k = 0; k < R; ++k) bk[k] = rdm_swz(1u << (u0 + k)) * 8u;
-            uint32_t la[1 << R];
-            la[0] = rdm_swz(fl_spread(threadIdx.x, u0, R)) * 8u;
+            for (int m = 1; m < 16; ++m) la[m] = la[m & (m - 1)] ^ bk[__builtin_ctz(m)];
+            double ar[16], ai[16];
 #pragma unroll
-            for (int m = 1; m < (1 << R); ++m) la[m] = la[m & (m - 1)] ^ bk[__builtin_ctz(m)];
-            double vr[1 << R], vi[1 << R];
-#pragma unroll
-            for (int m = 0; m < (1 << R); ++m) {
-                const float2 a = *reinterpret_cast<const float2*>(lb + la[m]);
-                vr[m] = (double)a.x;
-                vi[m] = (double)a.y;
+            for (int m = 0; m < 16; ++m) {
+                const cplx a = *reinterpret_cast<const cplx*>(reinterpret_cast<const char*>(lds) + la[m]);
+                ar[m] = (double)a.x;
+                ai[m] = (double)a.y;
             }
-            // the group's bonds sit on pair bits i (ops in increasing i): one
-            // compile-time code block per pair position, run when present
-            uint32_t present = 0;
-            for (int k = 0; k < nops; ++k) present |= 1u << pass_bit(pd, g, k);
-            static_for<0, R - 1>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                if ((present >> i) & 1u) {
-                    double r[16];
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) r[q] = 0.0;
-                    group_bond_sums<R, i>(vr, vi, r);
-                    // lane l holds the sum of value l >> 2; one lane of each four
-                    // adds it, the others add zero (an LDS atomic with every lane active)
-                    const double red = wave_transpose_reduce<double, 16>(r);
-                    const int rw = row + __builtin_popcount(present & ((1u << i) - 1u));
-                    __hip_atomic_fetch_add(&wacc[wave][rw][lane >> 2], (lane & 3) == 0 ? red : 0.0,
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (int m = 0; m < 16; ++m) P[m] = fma(ar[m], ar[m], fma(ai[m], ai[m], P[m]));
+            // (re, im) of a_x conj(a_y)
+            auto pair_sum = [&](int x, int y, double& re, double& im) {
+                re = fma(ar[x], ar[y], fma(ai[x], ai[y], re));
+                im = fma(ai[x], ar[y], fma(-ar[x], ai[y], im));
+            };
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (mask & (k == 0 ? 1 : k == 1 ? 3 : k == 2 ? 6 : 4)) {
+                    const int off = k == 0 ? 0 : k == 1 ? 4 : k == 2 ? 12 : 20;
+#pragma unroll
+                    for (int m = 0; m < 16; ++m) {
+                        if ((m >> k) & 1) continue;
+                        const int lo = k > 0 ? (m >> (k - 1)) & 1 : 0, hi = k < 3 ? (m >> (k + 1)) & 1 : 0;
+                        const int e = off + 2 * (k == 0 ? hi : k == 3 ? lo : lo + 2 * hi);
+                        pair_sum(m, m | (1 << k), S[e], S[e + 1]);
+                    }
                 }
-            });
-            row += nops;
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if ((mask >> j) & 1) {
+#pragma unroll
+                    for (int m = 0; m < 16; ++m) {
+                        if ((m >> (j + 1)) & 1) continue;
+                        const int e = 4 * j + (((m >> j) & 1) ? 2 : 0);
+                        pair_sum(m, m ^ (3 << j), D[e], D[e + 1]);
+                    }
+                }
+        }
+        if (++held == FL_RDM_FLUSH) {
+            flush();
+            held = 0;
         }
     }
-    double nv[1] = {nrm};
-    const double ntot = wave_transpose_reduce<double, 1>(nv);
+    flush();
     __syncthreads();
-    if (lane == 0) wacc[wave][NS - 1][0] = ntot;
-    __syncthreads();
-    // rows of the pass in group order -> partials[block][bond][16]
-    int nrows = 0;
-    for (int g = 0; g < ng; ++g) nrows += pass_nops(pd, g);
-    for (int t = threadIdx.x; t < (nrows + 1) * 16; t += NT) {
-        const int row = t >> 4, v = t & 15;
-        if (row == nrows && v > 0) continue;
-        const int rr = row < nrows ? row : NS - 1;
+    // the waves of a window in order -> partials[block][bond][16]
+    for (int t = threadIdx.x; t < nwin * 64; t += NT) {
+        const int w = t >> 6, row = (t >> 4) & 3, x = t & 15;
         double sum = 0.0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) sum += wacc[w][rr][v];
-        if (row < nrows) {
-            // the bond of row `row`: walk the groups
-            int gg = 0, k = row;
-            while (k >= pass_nops(pd, gg)) k -= pass_nops(pd, gg++);
-            partials[((size_t)blockIdx.x * nslot + pd.ops[gg][k]) * 16 + v] = sum;
-        } else if (pd.flags & 1) {
+        for (int k = w; k < NW; k += nwin) sum += wacc[k][row][x];
+        if (row < 3 && ((pd.mask[w] >> row) & 1))
+            partials[((size_t)blockIdx.x * nslot + pd.bond[w][row]) * 16 + x] = sum;
+        else if (row == 3 && w == 0 && x == 0 && (pd.flags & 1))
             partials[((size_t)blockIdx.x * nslot + (nslot - 1)) * 16] = sum;
-        }
     }
 }
 
@@ -2385,31 +2312,29 @@ hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gate
 hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,
                       int nslot, hipStream_t s) {
     const uint32_t nt = ntiles_of(g);
-    if (dtype == 0) {
-        const float2* p = (const float2*)psi;
-        if (g.K == FL_KMAX_RDM && g.W > 0)
-            hipLaunchKernelGGL((k_rdm_tiles<float, FL_KMAX_RDM, 256>), dim3(grid), dim3(256), 0, s, p, g.W, nt, pd,
-                               partials, nslot);
-        else
-            hipLaunchKernelGGL((k_rdm<float, 0, FL_KMAX_RDM>), dim3(grid), dim3(FL_NT), 0, s, p, g.C, g.W, nt, pd,
-                               partials, nslot);
-    } else {
-        const double2* p = (const double2*)psi;
-        if (g.K == FL_KMAX_RDM && g.W > 0)
-            hipLaunchKernelGGL((k_rdm_tiles<double, FL_KMAX_RDM, 256>), dim3(grid), dim3(256), 0, s, p, g.W, nt, pd,
-                               partials, nslot);
-        else
-            hipLaunchKernelGGL((k_rdm<double, 0, FL_KMAX_RDM>), dim3(grid), dim3(FL_NT), 0, s, p, g.C, g.W, nt, pd,
-                               partials, nslot);
-    }
+    if (dtype == 0)
+        hipLaunchKernelGGL((k_rdm<float, 0, FL_KMAX_RDM>), dim3(grid), dim3(FL_NT), 0, s, (const float2*)psi, g.C, g.W,
+                           nt, pd, partials, nslot);
+    else
+        hipLaunchKernelGGL((k_rdm<double, 0, FL_KMAX_RDM>), dim3(grid), dim3(FL_NT), 0, s, (const double2*)psi, g.C,
+                           g.W, nt, pd, partials, nslot);
     return hipGetLastError();
 }
 
-hipError_t launch_rdm_groups(const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,
-                             int nslot, hipStream_t s) {
-    if (g.K != FL_KMAX_C64 || g.R != FL_RDM_R_C64 || g.W == 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_rdm_groups<FL_RDM_R_C64, FL_KMAX_C64, FL_RDM_NT_C64>), dim3(grid), dim3(FL_RDM_NT_C64), 0,
-                       s, (const float2*)psi, g.W, ntiles_of(g), pd, partials, nslot);
+hipError_t launch_rdm_windows(int dtype, const fl_geom& g, const void* psi, const rdm_desc& pd, double* partials,
+                              int grid, int nslot, hipStream_t s) {
+    const int kmax = dtype == 0 ? FL_KMAX_C64 : FL_KMAX_C128;
+    if (g.K != kmax || g.C != FL_RDM_LOWBITS || (pd.nwin != 1 && pd.nwin != 2 && pd.nwin != 4) || grid < 1)
+        return hipErrorInvalidValue;
+    for (int w = 0; w < pd.nwin; ++w)
+        if (pd.u0[w] < 0 || pd.u0[w] + 4 > g.K) return hipErrorInvalidValue;
+    const uint32_t nt = ntiles_of(g);
+    if (dtype == 0)
+        hipLaunchKernelGGL((k_rdm_windows<float, FL_KMAX_C64, FL_RDM_LOWBITS, 256>), dim3(grid), dim3(256), 0, s,
+                           (const float2*)psi, g.W, nt, pd, partials, nslot);
+    else
+        hipLaunchKernelGGL((k_rdm_windows<double, FL_KMAX_C128, FL_RDM_LOWBITS, 256>), dim3(grid), dim3(256), 0, s,
+                           (const double2*)psi, g.W, nt, pd, partials, nslot);
     return hipGetLastError();
 }
 

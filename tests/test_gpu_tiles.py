@@ -82,3 +82,30 @@ def test_sweep_at_the_edges_of_its_tile_sizes(dtype, L, n, dagger):
     got = psi.cpu().numpy().astype(np.complex128)
     ulp = 6e-8 if dtype == "c64" else 1.2e-16
     assert np.linalg.norm(got - want) < n * (L - 1) * ulp * np.linalg.norm(want)
+
+
+# one full tile; 2 tiles; window shares of 1, 2 and 3 bonds, one and two bonds
+# left for a last pass, more tiles than fit between two flushes of the sums
+@pytest.mark.parametrize("dtype,L", [("c64", 13), ("c64", 15), ("c64", 20), ("c64", 22), ("c64", 23), ("c64", 26),
+                                     ("c128", 12), ("c128", 13), ("c128", 17), ("c128", 20), ("c128", 23)])
+def test_bond_density_matrices_in_windows(dtype, L):
+    """Every bond density matrix and the norm of a random state, against plain
+    torch FP64 sums over the same stored amplitudes.  FP64 chains of at most
+    16 tiles x 4 parts x 4 terms a lane, and trees above them: 1e-13 of the
+    norm."""
+    say(f"case: rdm windows {dtype} L={L}")
+    ctx = fl.fl_create(L, dtype)
+    fl.fl_set_bonds(ctx, 2.0 * fin.gue_bond_sample(L, seed=3), 0.7)
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    psi = torch.randn(1 << L, dtype=ctx.torch_dtype, device="cuda", generator=gen)
+    E, N, rho = fl.fl_expect_energy(ctx, psi, rdm=True)
+    v = psi.to(torch.complex128)
+    norm = v.abs().square().sum().item()
+    assert abs(N - norm) < 1e-13 * norm
+    for b in range(L - 1):
+        x = v.view(1 << b, 4, 1 << (L - 2 - b))
+        for i in range(4):
+            for j in range(i, 4):
+                want = (x[:, i] * x[:, j].conj()).sum().item()
+                assert abs(rho[b, i, j] - want) < 1e-13 * norm, (b, i, j)
+                assert rho[b, j, i] == np.conj(rho[b, i, j])
