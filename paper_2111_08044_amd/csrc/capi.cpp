@@ -50,8 +50,8 @@ constexpr int kMaxGatesPerPass = 96;  // cap on gates the planner puts in one pa
 constexpr int kReduceGrid = 2048;     // most workgroups of the reduction kernels (rows of the partials)
 constexpr int kRdmGrid = 512;          // workgroups of the bond reductions: two per CU, persistent
 constexpr int kApplyHGrid = 256;      // workgroups of H0 psi: one per CU (its two tiles fill the LDS)
-constexpr int kAdjGrid = 1024;        // workgroups of the persistent reverse pass
-constexpr int kAdjLowBits = 4;       // low tile bits of the reverse pass (its kernel takes C at run time)
+constexpr int kAdjGrid = 512;         // workgroups of the persistent reverse pass: two per CU
+constexpr int kAdjLowBits = 4;       // low tile bits of the reverse pass on 12-bit tiles
 constexpr int kDense6LowBits = 4;    // low tile bits of the 6-qubit-window forms (their kernel takes C at run time)
 constexpr int kWin4Grid = 256;        // workgroups of the 4-qubit-window reverse pass (one per CU)
 constexpr int kMinNoallocGrid = 256;  // fewest reduction workgroups fl_expect_energy_noalloc runs
@@ -91,6 +91,22 @@ fl_geom sweep_geom(int L, int dtype, int64_t n) {
     if (!c64 && n >= 3) return fl::make_geom(L, FL_KMAX_C128, 4, 3);
     return plain_geom(L, dtype);
 }
+// Geometry of the gradient's reverse pass, by the same reasons as the sweep's:
+// one workgroup up to L = 10, then tiles of L - 8 bits (256 workgroups) of at
+// least 9 bits, up to the 12 bits whose two tiles leave room for two workgroups
+// per CU.  fl_grad over 50 periods, against 12-bit tiles with 4-bit groups
+// (us): complex64 L = 12 827 / 1263, 14 985 / 1684, 18 1472 / 2268, 19 1838 /
+// 2450, 20 2328 / 2661 (L = 21: 4317 / 3542); complex128 L = 14 1076 / 2070,
+// 18 1679 / 2817, 19 2123 / 3058.
+fl_geom adjoint_geom(int L, int dtype) {
+    if (L <= FL_KMAX_ONE) return fl::make_geom(L, FL_KMAX_ONE, 2, 3);
+    const int k = std::max(L - 8, 9);
+    if (k <= 10) return fl::make_geom(L, k, 2, 3);
+    if (k == 11) return fl::make_geom(L, k, 3, 3);
+    if (k == 12 && dtype == FL_C64) return fl::make_geom(L, FL_KMAX_ADJ, 3, kAdjLowBits);
+    return fl::make_geom(L, FL_KMAX_ADJ, 4, kAdjLowBits);
+}
+
 // Geometry of the energy / density-matrix reduction: full tiles with 4 low
 // bits (a chain of exactly one full tile takes them as 4 low bits plus a
 // window too); shorter chains in one tile.
@@ -792,7 +808,7 @@ int fl_create(fl_ctx** ctx, int L, int dtype, int variant, void* hip_stream) {
     c->geom = (variant == FL_PLAIN)         ? plain_geom(L, dtype)
               : (variant == FL_DENSE4_FP32) ? fl::make_geom(L, FL_KMAX_C64, 4, FL_DENSE4_LOWBITS)
                                             : fl::make_geom(L, FL_KMAX_C64, 6, kDense6LowBits);
-    c->geom_adj = fl::make_geom(L, FL_KMAX_ADJ, 4, kAdjLowBits);
+    c->geom_adj = adjoint_geom(L, dtype);
     if (c->geom.W > 0) {
         c->geom_h = c->geom;
         c->geom_h.R = 4;
@@ -1390,7 +1406,7 @@ int fl_plan_query(int L, int dtype, int kind, int64_t n, int dagger, int32_t* bu
         for (int64_t i = 0; i < q; ++i) plan.insert(plan.end(), pb.begin(), pb.end());
         plan.insert(plan.end(), pr.begin(), pr.end());
     } else if (kind == 1) {
-        g = fl::make_geom(L, FL_KMAX_ADJ, 4, kAdjLowBits);
+        g = adjoint_geom(L, dtype);
         const int64_t q = n / kPlanBlock, r = n % kPlanBlock;
         std::vector<fl_pass> pb, pr;
         if (q > 0) pb = fl::plan_sweep(g, kPlanBlock, true, true, kMaxGatesPerPass);

@@ -80,6 +80,13 @@ struct fl_sweep_words {
     uint32_t w[FL_SWEEP_WORDS];  // per group u0 | nops << 8, then per op bit | gate << 8, then 0
 };
 
+// The same for a reverse pass of the gradient.
+struct fl_adj_words {
+    int32_t h, ngroups, nslots, nwords;
+    int8_t sbond[FL_MAX_SLOTS];
+    uint32_t w[FL_SWEEP_WORDS];  // per group u0 | nops << 8, then per op bit | slot << 8 | gate << 16
+};
+
 #ifdef __cplusplus
 // Kernels read the per-op arrays as aligned 32-bit words (scalar loads).
 static_assert(offsetof(fl_pass, u0) % 4 == 0 && sizeof(((fl_pass*)0)->u0) % 4 == 0, "u0 not word aligned");

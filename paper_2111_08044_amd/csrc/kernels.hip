@@ -1420,122 +1420,287 @@ __device__ __forceinline__ void adj_overlap(const T (&pr)[1 << R], const T (&pi)
     }
 }
 
-// One reverse op on register bits (I, I+1): the overlap terms of the op's
-// slot (before the gate), then the gate on psi and on lambda.  Every op of a
-// reverse plan has both a slot and a gate (the host checks this), so the
-// variants hold no further branches.
-template <typename T, int R, int I>
-__device__ __forceinline__ void adj_op(T (&pr)[1 << R], T (&pi)[1 << R], T (&lr)[1 << R], T (&li)[1 << R],
-                                       const T (&g)[32], T (&d)[16]) {
-    __asm__ volatile("; adjoint op on register bits %0" ::"i"(I));
-    adj_overlap<T, R, I>(pr, pi, lr, li, d);
-    apply_pair_g<T, R, I>(pr, pi, g);
-    apply_pair_g<T, R, I>(lr, li, g);
+// One reverse op on a register group: the overlap terms of the op's slot
+// (before the gate), summed over the wave into acc[16], then the gate (read
+// from LDS at lgate) on both states.  Every op of a reverse plan has both a
+// slot and a gate.  The overlap is reduced before the gate is read, which
+// keeps the registers of the two apart.
+template <typename T, int R, typename F>
+__device__ __forceinline__ void adj_op(T (&pr)[1 << R], T (&pi)[1 << R], T (&lr)[1 << R], T (&li)[1 << R], int i,
+                                       const T* lgate, double (&acc)[16], int lane, F&& next_op) {
+    {
+        T d[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) d[k] = 0;
+        with_bit<R>(i, [&](auto I) {
+            __asm__ volatile("; overlap on register bits %0" ::"i"(decltype(I)::value));
+            adj_overlap<T, R, decltype(I)::value>(pr, pi, lr, li, d);
+        });
+        // lane l holds the sum of value l >> 2; one lane of each four adds it and
+        // the other three add zero, as an LDS atomic with every lane active (no
+        // divergent branch in the op loop)
+        const T r = wave_transpose_reduce<T, 16>(d);
+        __hip_atomic_fetch_add(&acc[lane >> 2], (lane & 3) == 0 ? (double)r : 0.0, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    T gv[32];
+    load_gate_lds<T>(lgate, gv);
+    next_op();   // the next op's descriptor, under this op's FMAs
+    with_bit<R>(i, [&](auto I) {
+        apply_pair_g<T, R, decltype(I)::value>(pr, pi, gv);
+        apply_pair_g<T, R, decltype(I)::value>(lr, li, gv);
+    });
 }
 
-template <typename T, int R, int KT, int KMAX, int NT = FL_NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && NT == FL_NT ? 2 : 1))) void k_adjoint(typename CT<T>::c* __restrict__ psi,
-                                                   typename CT<T>::c* __restrict__ lam, const T* __restrict__ gates,
-                                                   int C, int W, uint32_t ntiles, fl_pass pd,
-                                                   double* __restrict__ Mpart, int nbonds) {
+// Chains of at most FL_KMAX_ONE sites: one workgroup, one quad of each state
+// per thread and op, as k_sweep_one.
+template <typename T>
+__global__ __launch_bounds__(FL_NT) void k_adjoint_one(typename CT<T>::c* __restrict__ psi,
+                                                       typename CT<T>::c* __restrict__ lam, const T* __restrict__ gates,
+                                                       int L, fl_adj_words pd, double* __restrict__ Mpart) {
     typedef typename CT<T>::c cplx;
-    __shared__ cplx lp[1 << KMAX];
-    __shared__ cplx ll[1 << KMAX];
-    __shared__ double wacc[NT / 64][FL_MAX_SLOTS][16];
-    const int K = KT > 0 ? KT : C + W;
-    const int h = pd.h;
+    constexpr int NW = FL_NT / 64;
+    __shared__ cplx lp[1 << FL_KMAX_ONE];
+    __shared__ cplx ll[1 << FL_KMAX_ONE];
+    __shared__ __attribute__((aligned(16))) T lg[FL_KMAX_ONE * 32];
+    __shared__ double wacc[NW][FL_MAX_SLOTS][16];
+    __shared__ uint32_t meta[FL_SWEEP_WORDS];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int t = threadIdx.x; t < (NT / 64) * FL_MAX_SLOTS * 16; t += NT) (&wacc[0][0][0])[t] = 0.0;
-    const uint32_t nsub = 1u << (K - R);   // <= NT
-    const bool active = threadIdx.x < nsub;
+    for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) {
+        lp[fl_swz(j)] = psi[j];
+        ll[fl_swz(j)] = lam[j];
+    }
+    for (int t = threadIdx.x; t < (L - 1) * 32; t += FL_NT) lg[t] = gates[t];
+    for (int t = threadIdx.x; t < pd.nwords; t += FL_NT) meta[t] = pd.w[t];
+    for (int t = threadIdx.x; t < NW * FL_MAX_SLOTS * 16; t += FL_NT) (&wacc[0][0][0])[t] = 0.0;
+    __syncthreads();
+    const bool active = threadIdx.x < (1u << (L - 2));
+    int pos = pd.ngroups;
+    for (int g = 0; g < pd.ngroups; ++g) {
+        const uint32_t head = __builtin_amdgcn_readfirstlane(meta[g]);
+        const int u0 = head & 255, nops = head >> 8;
+        const uint32_t b0 = fl_spread(active ? threadIdx.x : 0u, u0, 2);
+        T pr[4], pi[4], lr[4], li[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const uint32_t o = fl_swz(b0 | ((uint32_t)m << u0));
+            cplx a = lp[o], b = ll[o];
+            if (!active) a.x = a.y = b.x = b.y = 0;   // no part in the sums
+            pr[m] = a.x;
+            pi[m] = a.y;
+            lr[m] = b.x;
+            li[m] = b.y;
+        }
+        for (int q = 0; q < nops; ++q) {
+            const uint32_t w = __builtin_amdgcn_readfirstlane(meta[pos + q]);
+            adj_op<T, 2>(pr, pi, lr, li, 0, lg + 32 * (w >> 16), wacc[wave][(w >> 8) & 255], lane, [] {});
+        }
+        pos += nops;
+        if (active) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const uint32_t o = fl_swz(b0 | ((uint32_t)m << u0));
+                cplx a, b;
+                a.x = pr[m];
+                a.y = pi[m];
+                b.x = lr[m];
+                b.y = li[m];
+                lp[o] = a;
+                ll[o] = b;
+            }
+        }
+        __syncthreads();
+    }
+    for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) {
+        psi[j] = lp[fl_swz(j)];
+        lam[j] = ll[fl_swz(j)];
+    }
+    for (int t = threadIdx.x; t < pd.nslots * 16; t += FL_NT) {
+        const int sl = t >> 4, v = t & 15;
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s += wacc[w][sl][v];
+        Mpart[(size_t)pd.sbond[sl] * 16 + v] += s;
+    }
+}
+
+// Tiles of both states, persistent workgroups (the sums stay in LDS from tile
+// to tile).  Descriptors as in k_sweep_tiles.  The gates come from the
+// workgroup's LDS copy of G^dagger into vector registers, so that the FMAs of
+// two waves can issue together (two waves per SIMD on 12-bit tiles: two
+// workgroups' tiles fill the LDS).  Bound by the vector ALUs: 736 FMA-type
+// instructions per op and 16 amplitudes, and about 100 of the wave sums, which
+// do not pair.  complex64 L = 24, 50 periods: 26.1 ms (28.5 with the gates in
+// scalar registers); c128 L = 22: 13.7 ms (14.1).
+template <typename T, int R, int KT, int NT, int CL, int WPE, typename D>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void k_adjoint_tiles(
+    typename CT<T>::c* __restrict__ psi, typename CT<T>::c* __restrict__ lam, const T* __restrict__ gates, int W,
+    uint32_t ntiles, D pd, double* __restrict__ Mpart, int nbonds) {
+    typedef typename CT<T>::c cplx;
+    constexpr bool LM = std::is_same<D, fl_adj_words>::value;
+    constexpr int C = CL, K = KT, NW = NT / 64;
+    static_assert((1 << (K - R)) == NT, "one register group per thread");
+    constexpr int APL = sizeof(T) == 4 ? 2 : 1;
+    constexpr int ITER = (1 << K) / (APL * NT);
+    typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
+    __shared__ __attribute__((aligned(16))) cplx lp[1 << K];
+    __shared__ __attribute__((aligned(16))) cplx ll[1 << K];
+    __shared__ __attribute__((aligned(16))) T lg[FL_MAX_GATE_TABLE * 32];
+    __shared__ double wacc[NW][FL_MAX_SLOTS][16];
+    __shared__ uint32_t meta[LM ? FL_SWEEP_WORDS : 1];
+    const int h = pd.h, ng = pd.ngroups;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    char* const pb = reinterpret_cast<char*>(lp);
+    char* const lb = reinterpret_cast<char*>(ll);
+    static_assert((APL * NT) % (1 << C) == 0, "tile access stride");
+    // full-size tiles stream through; the states of short chains stay in cache
+    auto load = [](const cplx* p) {
+        const v16* q = reinterpret_cast<const v16*>(p);
+        return LM ? *q : __builtin_nontemporal_load(q);
+    };
+    auto store = [](const v16& x, cplx* p) {
+        v16* q = reinterpret_cast<v16*>(p);
+        if (LM) *q = x;
+        else __builtin_nontemporal_store(x, q);
+    };
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        // opaque per tile: addresses are formed anew, not kept across the ops
+        uint32_t tid = threadIdx.x;
+        __asm__ volatile("" : "+v"(tid));
         const uint64_t base = fl_tile_base(tile, C, W, h);
+        const uint64_t toff = fl_tile_offset(APL * tid, C, h);
+        const uint64_t tstride = (uint64_t)((APL * NT) >> C) << h;
+        const uint32_t l0 = fl_swz(APL * tid);
+        {
+            const cplx* sp = psi + base + toff;
+            const cplx* sl = lam + base + toff;
+            v16 a[ITER], b[ITER];
+#pragma unroll
+            for (int s = 0; s < ITER; ++s) a[s] = load(sp + s * tstride);
+#pragma unroll
+            for (int s = 0; s < ITER; ++s) b[s] = load(sl + s * tstride);
+            if (tile == blockIdx.x) {
+                const fl_f32x4* src = reinterpret_cast<const fl_f32x4*>(gates);
+                for (int t = threadIdx.x; t < nbonds * (int)(32 * sizeof(T) / 16); t += NT)
+                    reinterpret_cast<fl_f32x4*>(lg)[t] = src[t];
+                if constexpr (LM)
+                    for (int t = threadIdx.x; t < pd.nwords; t += NT) meta[t] = pd.w[t];
+                for (int t = threadIdx.x; t < NW * FL_MAX_SLOTS * 16; t += NT) (&wacc[0][0][0])[t] = 0.0;
+            } else {
+                __syncthreads();   // the previous tile's stores have read LDS
+            }
+#pragma unroll
+            for (int s = 0; s < ITER; ++s) {
+                const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
+                if constexpr (sizeof(T) == 4) {
+                    lp[l] = make_float2(a[s][0], a[s][1]);
+                    lp[l ^ 1] = make_float2(a[s][2], a[s][3]);
+                    ll[l] = make_float2(b[s][0], b[s][1]);
+                    ll[l ^ 1] = make_float2(b[s][2], b[s][3]);
+                } else {
+                    lp[l] = make_double2(a[s][0], a[s][1]);
+                    ll[l] = make_double2(b[s][0], b[s][1]);
+                }
+            }
+        }
         __syncthreads();
-        tile_load<T, KT, NT>(psi, base, K, C, h, lp);
-        tile_load<T, KT, NT>(lam, base, K, C, h, ll);
-        __syncthreads();
-        for (int g = 0; g < pd.ngroups; ++g) {
-            const int u0 = pass_u0(pd, g);
-            const int nops = pass_nops(pd, g);
-            const uint32_t b0 = fl_spread(active ? threadIdx.x : 0u, u0, R);
-            // byte offset of element b0 | m << u0: slot(b0) ^ slot(m << u0), the
-            // second part uniform (the swizzle is linear over XOR)
-            const uint32_t vb = fl_swz(b0) * (uint32_t)sizeof(cplx);
-            auto loff = [&](int m) { return vb ^ (fl_swz((uint32_t)m << u0) * (uint32_t)sizeof(cplx)); };
-            char* const pb = reinterpret_cast<char*>(lp);
-            char* const lb = reinterpret_cast<char*>(ll);
+        int pos = ng;
+        for (int g = 0; g < ng; ++g) {
+            int u0, nops;
+            if constexpr (LM) {
+                const uint32_t head = __builtin_amdgcn_readfirstlane(meta[g]);
+                u0 = head & 255;
+                nops = head >> 8;
+            } else {
+                u0 = pass_u0(pd, g);
+                nops = pass_nops(pd, g);
+            }
+            uint32_t bk[R];
+#pragma unroll
+            for (int k = 0; k < R; ++k) bk[k] = fl_swz(1u << (u0 + k)) * (uint32_t)sizeof(cplx);
+            const uint32_t vb = fl_swz(fl_spread(tid, u0, R)) * (uint32_t)sizeof(cplx);
+            auto loff = [&](int m) {
+                uint32_t r = vb;
+#pragma unroll
+                for (int k = 0; k < R; ++k)
+                    if ((m >> k) & 1) r ^= bk[k];
+                return r;
+            };
             T pr[1 << R], pi[1 << R], lr[1 << R], li[1 << R];
 #pragma unroll
             for (int m = 0; m < (1 << R); ++m) {
                 const uint32_t o = loff(m);
-                cplx a = *reinterpret_cast<const cplx*>(pb + o), b = *reinterpret_cast<const cplx*>(lb + o);
-                if (!active) { a.x = a.y = b.x = b.y = 0; }
+                const cplx a = *reinterpret_cast<const cplx*>(pb + o), b = *reinterpret_cast<const cplx*>(lb + o);
                 pr[m] = a.x;
                 pi[m] = a.y;
                 lr[m] = b.x;
                 li[m] = b.y;
             }
-            // Ops run two per iteration with the op metadata read as scalar
-            // words and the gate fetched into scalar registers one op ahead
-            // (the structure of the forward sweep's op loop).
-            auto fetch = [&](int q, int& i, int& slot, T (&gg)[32]) {
-                i = pass_bit(pd, g, q);
-                slot = pass_slot(pd, g, q);
-                const T* G = gates + 32 * pass_gate(pd, g, q);
-#pragma unroll
-                for (int k = 0; k < 32; ++k) gg[k] = G[k];
+            // op metadata one op ahead, as in the sweep
+            int bit, slot, idx;
+            auto fetch = [&](int q) {
+                if constexpr (LM) {
+                    const uint32_t w = __builtin_amdgcn_readfirstlane(meta[pos + q]);
+                    bit = w & 255;
+                    slot = (w >> 8) & 255;
+                    idx = w >> 16;
+                } else {
+                    bit = pass_bit(pd, g, q);
+                    slot = pass_slot(pd, g, q);
+                    idx = pass_gate(pd, g, q) - nbonds;
+                }
             };
-            auto run = [&](int i, int slot, const T (&gg)[32]) {
-                T d[16];
-#pragma unroll
-                for (int k = 0; k < 16; ++k) d[k] = 0;
-                with_bit<R>(i, [&](auto I) { adj_op<T, R, decltype(I)::value>(pr, pi, lr, li, gg, d); });
-                // lane l holds the sum of value l >> 2; one lane of each
-                // four adds it and the other three add zero, as an LDS atomic
-                // with every lane active (no divergent branch in the op loop)
-                const T r = wave_transpose_reduce<T, 16>(d);
-                __hip_atomic_fetch_add(&wacc[wave][slot][lane >> 2], (lane & 3) == 0 ? (double)r : 0.0,
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            fetch(0);
+            auto run = [&](int q) {
+                adj_op<T, R>(pr, pi, lr, li, bit, lg + 32 * idx, wacc[wave][slot], lane,
+                             [&] { fetch(q + 1 < nops ? q + 1 : q); });
             };
-            int i0, s0;
-            T gc[32];
-            fetch(0, i0, s0, gc);
             for (int q = 0; q < nops; q += 2) {
-                __builtin_amdgcn_s_waitcnt(FL_WAIT_LGKM0);
-                int i1, s1;
-                T gn[32];
-                fetch((q + 1 < nops) ? q + 1 : q, i1, s1, gn);
-                run(i0, s0, gc);
-                if (q + 1 < nops) {
-                    __builtin_amdgcn_s_waitcnt(FL_WAIT_LGKM0);
-                    fetch((q + 2 < nops) ? q + 2 : q + 1, i0, s0, gc);
-                    run(i1, s1, gn);
-                }
+                run(q);
+                if (q + 1 < nops) run(q + 1);
             }
-            if (active) {
+            pos += nops;
 #pragma unroll
-                for (int m = 0; m < (1 << R); ++m) {
-                    const uint32_t o = loff(m);
-                    cplx a, b;
-                    a.x = pr[m];
-                    a.y = pi[m];
-                    b.x = lr[m];
-                    b.y = li[m];
-                    *reinterpret_cast<cplx*>(pb + o) = a;
-                    *reinterpret_cast<cplx*>(lb + o) = b;
-                }
+            for (int m = 0; m < (1 << R); ++m) {
+                const uint32_t o = loff(m);
+                cplx a, b;
+                a.x = pr[m];
+                a.y = pi[m];
+                b.x = lr[m];
+                b.y = li[m];
+                *reinterpret_cast<cplx*>(pb + o) = a;
+                *reinterpret_cast<cplx*>(lb + o) = b;
             }
             __syncthreads();
         }
-        tile_store<T, KT, NT>(psi, base, K, C, h, lp);
-        tile_store<T, KT, NT>(lam, base, K, C, h, ll);
+        {
+            cplx* dp = psi + base + toff;
+            cplx* dl = lam + base + toff;
+#pragma unroll
+            for (int s = 0; s < ITER; ++s) {
+                const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
+                v16 a, b;
+                if constexpr (sizeof(T) == 4) {
+                    const float2 a0 = lp[l], a1 = lp[l ^ 1], b0 = ll[l], b1 = ll[l ^ 1];
+                    a = v16{a0.x, a0.y, a1.x, a1.y};
+                    b = v16{b0.x, b0.y, b1.x, b1.y};
+                } else {
+                    const double2 a0 = lp[l], b0 = ll[l];
+                    a = v16{a0.x, a0.y};
+                    b = v16{b0.x, b0.y};
+                }
+                store(a, dp + s * tstride);
+                store(b, dl + s * tstride);
+            }
+        }
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < pd.nslots * 16; t += NT) {
+    const int nslots = pd.nslots;
+    for (int t = threadIdx.x; t < nslots * 16; t += NT) {
         const int sl = t >> 4, v = t & 15;
         double s = 0.0;
 #pragma unroll
-        for (int w = 0; w < NT / 64; ++w) s += wacc[w][sl][v];
+        for (int w = 0; w < NW; ++w) s += wacc[w][sl][v];
         double* dst = Mpart + ((size_t)blockIdx.x * nbonds + pd.sbond[sl]) * 16 + v;
         *dst += s;
     }
@@ -2428,44 +2593,77 @@ hipError_t launch_apply_h_tiles(int dtype, const fl_geom& g, const void* psi, vo
     return hipGetLastError();
 }
 
-hipError_t launch_adjoint(int dtype, const fl_geom& g, void* psi, void* lam, const void* gates, const fl_pass& pd,
-                          double* Mpart, int grid, hipStream_t s) {
-    const uint32_t nt = ntiles_of(g);
+static bool adj_words(const fl_pass& pd, int gofs, fl_adj_words& w) {
+    int n = pd.ngroups;
+    for (int g = 0; g < pd.ngroups; ++g) n += pd.nops[g];
+    if (n + 1 > FL_SWEEP_WORDS) return false;
+    w.h = pd.h;
+    w.ngroups = pd.ngroups;
+    w.nslots = pd.nslots;
+    for (int k = 0; k < FL_MAX_SLOTS; ++k) w.sbond[k] = pd.sbond[k];
+    n = 0;
+    for (int g = 0; g < pd.ngroups; ++g) w.w[n++] = (uint32_t)pd.u0[g] | (uint32_t)pd.nops[g] << 8;
+    for (int g = 0; g < pd.ngroups; ++g)
+        for (int k = 0; k < pd.nops[g]; ++k)
+            w.w[n++] = (uint32_t)pd.opi[g][k] | (uint32_t)pd.ops[g][k] << 8 | (uint32_t)(pd.opg[g][k] - gofs) << 16;
+    w.w[n++] = 0;
+    w.nwords = n;
+    return true;
+}
+
+template <typename T, int R, int K, int C, int WPE, typename D>
+static hipError_t launch_adj_tiles(const fl_geom& g, void* psi, void* lam, const void* gates, const fl_pass& pd,
+                                   double* Mpart, int grid, hipStream_t s) {
+    typedef typename CT<T>::c cplx;
+    constexpr int NT = 1 << (K - R);
     const int nb = g.L - 1;
-    if (dtype == 0) {
-        float2* p = (float2*)psi;
-        float2* l = (float2*)lam;
-        const float* G = (const float*)gates;
-        if (g.K == FL_KMAX_ADJ && g.R == 4)
-            hipLaunchKernelGGL((k_adjoint<float, 4, FL_KMAX_ADJ, FL_KMAX_ADJ>), dim3(grid), dim3(FL_NT), 0, s, p, l, G,
-                               g.C, g.W, nt, pd, Mpart, nb);
-        else if (g.R == 4)
-            hipLaunchKernelGGL((k_adjoint<float, 4, 0, FL_KMAX_ADJ>), dim3(grid), dim3(FL_NT), 0, s, p, l, G, g.C, g.W,
-                               nt, pd, Mpart, nb);
-        else if (g.R == 3)
-            hipLaunchKernelGGL((k_adjoint<float, 3, 0, FL_KMAX_ADJ>), dim3(grid), dim3(FL_NT), 0, s, p, l, G, g.C, g.W,
-                               nt, pd, Mpart, nb);
-        else
-            hipLaunchKernelGGL((k_adjoint<float, 2, 0, FL_KMAX_ADJ>), dim3(grid), dim3(FL_NT), 0, s, p, l, G, g.C, g.W,
-                               nt, pd, Mpart, nb);
+    const T* G = (const T*)gates + 32 * nb;   // G^dagger
+    if constexpr (std::is_same<D, fl_adj_words>::value) {
+        fl_adj_words w;
+        if (!adj_words(pd, nb, w)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_adjoint_tiles<T, R, K, NT, C, WPE, D>), dim3(grid), dim3(NT), 0, s, (cplx*)psi, (cplx*)lam,
+                           G, g.W, ntiles_of(g), w, Mpart, nb);
     } else {
-        double2* p = (double2*)psi;
-        double2* l = (double2*)lam;
-        const double* G = (const double*)gates;
-        if (g.K == FL_KMAX_ADJ && g.R == 4)
-            hipLaunchKernelGGL((k_adjoint<double, 4, FL_KMAX_ADJ, FL_KMAX_ADJ>), dim3(grid), dim3(FL_NT), 0, s, p, l,
-                               G, g.C, g.W, nt, pd, Mpart, nb);
-        else if (g.R == 4)
-            hipLaunchKernelGGL((k_adjoint<double, 4, 0, FL_KMAX_ADJ>), dim3(grid), dim3(FL_NT), 0, s, p, l, G, g.C,
-                               g.W, nt, pd, Mpart, nb);
-        else if (g.R == 3)
-            hipLaunchKernelGGL((k_adjoint<double, 3, 0, FL_KMAX_ADJ>), dim3(grid), dim3(FL_NT), 0, s, p, l, G, g.C,
-                               g.W, nt, pd, Mpart, nb);
-        else
-            hipLaunchKernelGGL((k_adjoint<double, 2, 0, FL_KMAX_ADJ>), dim3(grid), dim3(FL_NT), 0, s, p, l, G, g.C,
-                               g.W, nt, pd, Mpart, nb);
+        hipLaunchKernelGGL((k_adjoint_tiles<T, R, K, NT, C, WPE, D>), dim3(grid), dim3(NT), 0, s, (cplx*)psi, (cplx*)lam,
+                           G, g.W, ntiles_of(g), pd, Mpart, nb);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_adjoint(int dtype, const fl_geom& g, void* psi, void* lam, const void* gates, const fl_pass& pd,
+                          double* Mpart, int grid, hipStream_t s) {
+    const int nb = g.L - 1;
+    if (nb > FL_MAX_GATE_TABLE || grid < 1 || pd.nslots > FL_MAX_SLOTS) return hipErrorInvalidValue;
+    for (int q = 0; q < pd.ngroups; ++q) {
+        if (pd.nops[q] < 1) return hipErrorInvalidValue;
+        for (int k = 0; k < pd.nops[q]; ++k)
+            if (pd.opg[q][k] < nb || pd.opg[q][k] >= 2 * nb || pd.ops[q][k] < 0 || pd.ops[q][k] >= pd.nslots)
+                return hipErrorInvalidValue;
+    }
+    if (g.W == 0) {
+        fl_adj_words w;
+        if (g.L < 2 || g.L > FL_KMAX_ONE || g.R != 2 || !adj_words(pd, nb, w)) return hipErrorInvalidValue;
+        if (dtype == 0)
+            hipLaunchKernelGGL(k_adjoint_one<float>, dim3(1), dim3(FL_NT), 0, s, (float2*)psi, (float2*)lam,
+                               (const float*)gates + 32 * nb, g.L, w, Mpart);
+        else
+            hipLaunchKernelGGL(k_adjoint_one<double>, dim3(1), dim3(FL_NT), 0, s, (double2*)psi, (double2*)lam,
+                               (const double*)gates + 32 * nb, g.L, w, Mpart);
+        return hipGetLastError();
+    }
+    // the geometries of adjoint_geom
+    const int key = (dtype << 12) | (g.K << 8) | (g.C << 4) | g.R;
+    auto code = [](int dt, int K, int C, int R) { return (dt << 12) | (K << 8) | (C << 4) | R; };
+    if (key == code(0, 12, 4, 4)) return launch_adj_tiles<float, 4, 12, 4, 2, fl_pass>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(0, 12, 4, 3)) return launch_adj_tiles<float, 3, 12, 4, 2, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(0, 11, 3, 3)) return launch_adj_tiles<float, 3, 11, 3, 2, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(0, 10, 3, 2)) return launch_adj_tiles<float, 2, 10, 3, 4, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(0, 9, 3, 2)) return launch_adj_tiles<float, 2, 9, 3, 4, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(1, 12, 4, 4)) return launch_adj_tiles<double, 4, 12, 4, 1, fl_pass>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(1, 11, 3, 3)) return launch_adj_tiles<double, 3, 11, 3, 1, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(1, 10, 3, 2)) return launch_adj_tiles<double, 2, 10, 3, 2, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(1, 9, 3, 2)) return launch_adj_tiles<double, 2, 9, 3, 2, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_adjoint_win4(const fl_geom& g, void* psi, void* lam, const void* mats, const fl_pass& pd,

@@ -109,3 +109,33 @@ def test_bond_density_matrices_in_windows(dtype, L):
                 want = (x[:, i] * x[:, j].conj()).sum().item()
                 assert abs(rho[b, i, j] - want) < 1e-13 * norm, (b, i, j)
                 assert rho[b, j, i] == np.conj(rho[b, i, j])
+
+
+# one workgroup, then each tile size of the reverse pass at its shortest and
+# longest chains, and the first chain on 12-bit tiles with 4-bit groups
+@pytest.mark.parametrize("dtype,L,n,K", [("c64", 3, 4, 2), ("c64", 10, 4, 2), ("c64", 11, 4, 0), ("c64", 17, 2, 1),
+                                         ("c64", 18, 2, 0), ("c64", 19, 2, 0), ("c64", 20, 2, 1), ("c64", 21, 2, 0),
+                                         ("c128", 2, 3, 1), ("c128", 10, 4, 2), ("c128", 11, 4, 0), ("c128", 17, 2, 1),
+                                         ("c128", 18, 2, 0), ("c128", 19, 2, 0), ("c128", 20, 2, 1)])
+def test_gradient_at_the_edges_of_its_tile_sizes(dtype, L, n, K):
+    """Every component against the oracle adjoint.  The replayed states are off
+    by at most n (L-1) units in the last place (as the sweep's), the gradient by
+    that times ||H0|| <= 4 (L-1) and the generators' norms, times two."""
+    say(f"case: grad {dtype} L={L} n={n} K={K}")
+    w = fin.xyz_workload(L, seed=800 + L)
+    hs = O.xyz_bond_hamiltonians(L, w["J"], w["fields"])
+    gens = O.xyz_coupling_generators(L)
+    ref, _ = O.adjoint_gradient(L, hs, gens, w["T"], O.product_state(w["spinors"]), n)
+    ctx = fl.fl_create(L, dtype)
+    fl.fl_set_bonds(ctx, hs, w["T"])
+    psi = fl.new_state(ctx)
+    fl.fl_init_state(ctx, psi, w["spinors"])
+    ck = []
+    for _ in range(n // K if K else 0):
+        ck.append(psi.clone())
+        fl.fl_apply_period(ctx, psi, K)
+    if not K:
+        fl.fl_apply_period(ctx, psi, n)
+    g = fl.fl_grad(ctx, psi, ck, n, K, gens, torch.empty_like(psi))
+    ulp = 6e-8 if dtype == "c64" else 1.2e-16
+    assert np.max(np.abs(g - ref)) < 2 * n * (L - 1) * ulp * 4 * (L - 1)
