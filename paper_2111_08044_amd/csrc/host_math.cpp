@@ -170,28 +170,31 @@ void mat_mul_n(const cd* A, const cd* B, cd* C, int n) {
     std::memcpy(C, t.data(), sizeof(cd) * n * n);
 }
 
-void embed_gate(const cd* G, int nbits, int i, cd* U) {
-    // U = I (x) G (x) I acting on window bits (i, i+1) of an nbits-bit window;
-    // window index w, local gate index 2*bit(i+1) + bit(i).
-    const int n = 1 << nbits;
-    for (int r = 0; r < n * n; ++r) U[r] = 0.0;
-    for (int w = 0; w < n; ++w) {
-        const int rest = w & ~(3 << i);
-        const int col_l = (w >> i) & 3;
-        for (int row_l = 0; row_l < 4; ++row_l) {
-            const int wr = rest | (row_l << i);
-            U[(size_t)wr * n + w] += G[4 * row_l + col_l];
-        }
-    }
-}
-
 void window_matrix_bits(const cd* const* gates, const int* pos, int nops, int nbits, cd* U) {
     const int n = 1 << nbits;
-    std::vector<cd> E((size_t)n * n);
     for (int r = 0; r < n * n; ++r) U[r] = (r % (n + 1) == 0) ? cd(1.0) : cd(0.0);
+    // U <- E(gate) U: the gate mixes the four rows that agree off its two bits
+    std::vector<cd> in((size_t)4 * n);
     for (int k = 0; k < nops; ++k) {
-        embed_gate(gates[k], nbits, pos[k], E.data());
-        mat_mul_n(E.data(), U, U, n);
+        const cd* G = gates[k];
+        const int i = pos[k];
+        for (int z = 0; z < n / 4; ++z) {
+            const int r0 = (z & ((1 << i) - 1)) | ((z >> i) << (i + 2));
+            for (int a = 0; a < 4; ++a)
+                for (int c = 0; c < n; ++c) in[(size_t)a * n + c] = U[(size_t)(r0 | (a << i)) * n + c];
+            for (int a = 0; a < 4; ++a) {
+                cd* row = U + (size_t)(r0 | (a << i)) * n;
+                for (int c = 0; c < n; ++c) {
+                    double re = 0.0, im = 0.0;
+                    for (int b = 0; b < 4; ++b) {
+                        const cd g = G[4 * a + b], u = in[(size_t)b * n + c];
+                        re += g.real() * u.real() - g.imag() * u.imag();
+                        im += g.real() * u.imag() + g.imag() * u.real();
+                    }
+                    row[c] = cd(re, im);
+                }
+            }
+        }
     }
 }
 
@@ -271,11 +274,15 @@ void window_fragments4(const cd* U, float* out) {
 }
 
 double bf16_rne(double a) {
-    if (a == 0.0 || !std::isfinite(a)) return a;
-    int e = 0;
-    std::frexp(a, &e);                        // a = f 2^e, 0.5 <= |f| < 1
-    const double scale = std::ldexp(1.0, e - 8);   // 8 significant bits
-    return std::nearbyint(a / scale) * scale;      // ties to even (default rounding mode)
+    if (!std::isfinite(a)) return a;
+    // 8 significant bits: drop 45 of the 52 mantissa bits, ties to even (a carry
+    // runs into the exponent as it should)
+    uint64_t u;
+    std::memcpy(&u, &a, 8);
+    u += ((uint64_t)1 << 44) - 1 + ((u >> 45) & 1);
+    u &= ~(((uint64_t)1 << 45) - 1);
+    std::memcpy(&a, &u, 8);
+    return a;
 }
 
 static uint16_t bf16_bits(double v) {

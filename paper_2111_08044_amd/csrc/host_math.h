@@ -22,11 +22,9 @@ void xyz_bond(const double* J3, const double* fl3, const double* fr3, std::compl
 void mat_mul_n(const std::complex<double>* A, const std::complex<double>* B,
                std::complex<double>* C, int n);
 
-// Embed a 4x4 gate on bits (i, i+1) of an nbits-bit window into a 2^nbits matrix.
-void embed_gate(const std::complex<double>* G, int nbits, int i, std::complex<double>* U);
-
 // U = E(op_{n-1}) ... E(op_0) on an nbits-bit window, E = gate gates[k]
-// embedded at window bits (pos[k], pos[k]+1).  U: 2^nbits x 2^nbits row-major.
+// embedded at window bits (pos[k], pos[k]+1), window index bit i = tile bit
+// u0 + i, gate local index 2 bit(pos+1) + bit(pos).  U: 2^nbits x 2^nbits row-major.
 void window_matrix_bits(const std::complex<double>* const* gates, const int* pos, int nops, int nbits,
                         std::complex<double>* U);
 // The 6-bit case (U: 64x64).

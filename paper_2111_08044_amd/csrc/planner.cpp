@@ -45,6 +45,10 @@ struct Gate {
     int slot;
 };
 
+// Progress of every bond.  In terms of the layer t_b = 2 cnt_b + a_b of a
+// bond's next application the rule above reads: b may run when t_b is below
+// both neighbours' layers, so neighbours' layers always differ by one and a
+// run raises a local minimum of the profile by two.
 struct Sched {
     int L, nb, n;
     std::vector<int> cnt, off;
@@ -64,23 +68,81 @@ bool bond_in_tile(const fl_geom& g, int h, int b) {
     return u >= 0 && u1 == u + 1;
 }
 
-// Apply rounds of ready gates inside tile window h; returns the bonds in order.
-std::vector<int> run_tile(const fl_geom& g, int h, Sched& s, int cap) {
+// The bonds inside a tile of window h, as runs of consecutive bonds (the low
+// bits' and the window's; one run where the window follows the low bits).
+struct Window {
+    int h = 0, nruns = 0;
+    int lo[2] = {0, 0}, hi[2] = {-1, -1};
+};
+
+Window tile_window(const fl_geom& g, int h) {
+    Window w;
+    w.h = h;
+    for (int b = 0; b < g.L - 1; ++b) {
+        if (!bond_in_tile(g, h, b)) continue;
+        if (w.nruns > 0 && w.hi[w.nruns - 1] == b - 1) {
+            w.hi[w.nruns - 1] = b;
+        } else {
+            w.lo[w.nruns] = w.hi[w.nruns] = b;
+            ++w.nruns;
+        }
+    }
+    return w;
+}
+
+// Apply rounds of ready gates inside tile window w; returns the bonds in order.
+std::vector<int> run_tile(const Window& w, Sched& s, int cap) {
     std::vector<int> out;
-    std::vector<int> round;
+    int round[64];
     while ((int)out.size() < cap) {
-        round.clear();
-        for (int b = 0; b < s.nb; ++b)
-            if (bond_in_tile(g, h, b) && s.ready(b)) round.push_back(b);
-        if (round.empty()) break;
-        for (int b : round) {
-            if ((int)out.size() >= cap) break;
-            s.cnt[b]++;
-            out.push_back(b);
+        int nr = 0;
+        for (int r = 0; r < w.nruns; ++r)
+            for (int b = w.lo[r]; b <= w.hi[r]; ++b)
+                if (s.ready(b)) round[nr++] = b;
+        if (nr == 0) break;
+        for (int k = 0; k < nr && (int)out.size() < cap; ++k) {
+            s.cnt[round[k]]++;
+            out.push_back(round[k]);
         }
     }
     return out;
 }
+
+// The layer profile of a schedule (t[b + 1] = t_b; the ends past the chain
+// never hold a bond back) and its last layer n per bond.
+struct Profile {
+    int nb = 0;
+    int t[66], last[66];
+    explicit Profile(const Sched& s) : nb(s.nb) {
+        t[0] = t[nb + 1] = 1 << 28;
+        for (int b = 0; b < nb; ++b) {
+            t[b + 1] = 2 * s.cnt[b] + s.off[b];
+            last[b + 1] = 2 * s.n + s.off[b];
+        }
+    }
+    // Where a tile's rounds end when none is cut short: every bond of a run goes
+    // as far as the fixed layers beside the run allow (they bound it by their own
+    // layer plus the distance) and no further than the circuit's end.
+    // Writes the new layers to out[1 ..] of the runs and returns the gate count.
+    int advance(const Window& w, int* out) const {
+        int gates = 0;
+        for (int r = 0; r < w.nruns; ++r) {
+            const int l = w.lo[r], h = w.hi[r];
+            int bound = t[l];   // the layer left of the run
+            for (int b = l; b <= h; ++b) {
+                bound = std::min(bound + 1, last[b + 1]);
+                out[b + 1] = bound;
+            }
+            bound = t[h + 2];
+            for (int b = h; b >= l; --b) {
+                bound = std::min(bound + 1, out[b + 1]);
+                out[b + 1] = bound;
+                gates += (bound - t[b + 1]) / 2;
+            }
+        }
+        return gates;
+    }
+};
 
 // Pack an ordered gate list into register groups.  A gate may join the
 // current group only if no earlier gate left for later shares one of its
@@ -89,39 +151,45 @@ std::vector<int> run_tile(const fl_geom& g, int h, Sched& s, int cap) {
 std::vector<Gate> pack_groups(const fl_geom& g, std::vector<Gate> rem, fl_pass& pd, int max_groups) {
     pd.ngroups = 0;
     while (!rem.empty() && pd.ngroups < max_groups) {
-        int best_u0 = -1;
-        std::vector<int> best;
+        const int nrem = (int)rem.size();
+        int best_u0 = -1, nbest = 0;
+        int best[FL_MAX_OPS], take[FL_MAX_OPS];
         for (int u0 = 0; u0 + g.R <= g.K; ++u0) {
             unsigned blocked = 0;
-            std::vector<int> take;
-            for (int i = 0; i < (int)rem.size(); ++i) {
+            const unsigned inside = ((1u << g.R) - 1u) << u0;   // once all of it is blocked no gate fits
+            int n = 0;
+            for (int i = 0; i < nrem && (blocked & inside) != inside; ++i) {
                 const unsigned m = 3u << rem[i].u;
                 const bool fits = rem[i].u >= u0 && rem[i].u + 1 < u0 + g.R;
-                if ((m & blocked) == 0 && fits && (int)take.size() < FL_MAX_OPS)
-                    take.push_back(i);
+                if ((m & blocked) == 0 && fits && n < FL_MAX_OPS)
+                    take[n++] = i;
                 else
                     blocked |= m;
             }
-            if ((int)take.size() > (int)best.size()) {
-                best = take;
+            if (n > nbest) {
+                nbest = n;
                 best_u0 = u0;
+                std::copy(take, take + n, best);
             }
         }
         const int gi = pd.ngroups++;
         pd.u0[gi] = (int8_t)best_u0;
-        pd.nops[gi] = (int8_t)best.size();
-        std::vector<char> used(rem.size(), 0);
-        for (int k = 0; k < (int)best.size(); ++k) {
+        pd.nops[gi] = (int8_t)nbest;
+        for (int k = 0; k < nbest; ++k) {
             const Gate& q = rem[best[k]];
             pd.opi[gi][k] = (int8_t)(q.u - best_u0);
             pd.opg[gi][k] = (int16_t)q.gidx;
             pd.ops[gi][k] = (int16_t)q.slot;
-            used[best[k]] = 1;
         }
-        std::vector<Gate> next;
-        for (int i = 0; i < (int)rem.size(); ++i)
-            if (!used[i]) next.push_back(rem[i]);
-        rem.swap(next);
+        // drop the taken gates (best is in increasing order)
+        int out = 0, k = 0;
+        for (int i = 0; i < nrem; ++i) {
+            if (k < nbest && best[k] == i)
+                ++k;
+            else
+                rem[out++] = rem[i];
+        }
+        rem.resize(out);
     }
     return rem;
 }
@@ -189,24 +257,40 @@ void balance_groups(const fl_geom& g, fl_pass& pd) {
 }
 
 // Passes the plain greedy rule (the window admitting the most gates) needs to
-// finish the circuit from state s.
-int greedy_passes(const fl_geom& g, const std::vector<int>& windows, Sched s, int cap) {
+// finish the circuit from state s; gives up once `most` are not enough.
+int greedy_passes(const std::vector<Window>& windows, const Sched& s0, int cap, int most) {
     long long left = 0;
-    for (int b = 0; b < s.nb; ++b) left += s.n - s.cnt[b];
+    for (int b = 0; b < s0.nb; ++b) left += s0.n - s0.cnt[b];
+    if (left == 0) return 0;
+    Profile p(s0);
+    Sched s;         // kept only once a tile's rounds are cut short by the cap
+    bool exact = true;
     int passes = 0;
+    int a[2][66];
     while (left > 0) {
-        int best = 0;
-        Sched best_s;
-        for (int h : windows) {
-            Sched t = s;
-            const int got = (int)run_tile(g, h, t, cap).size();
+        if (passes >= most) return most + 1;
+        int best = 0, best_w = -1, cur = 0;
+        for (int k = 0; k < (int)windows.size(); ++k) {
+            const int got = std::min(p.advance(windows[k], a[cur]), cap);
             if (got > best) {
                 best = got;
-                best_s = std::move(t);
+                best_w = k;
+                cur ^= 1;   // keep this window's layers
             }
         }
         if (best == 0) return 1 << 20;   // cannot happen for a valid circuit
-        s = std::move(best_s);
+        const Window& w = windows[best_w];
+        if (best == cap) {
+            // the rounds may end at the cap: run them one by one
+            if (exact) s = s0;
+            for (int b = 0; b < s0.nb; ++b) s.cnt[b] = (p.t[b + 1] - s0.off[b]) / 2;
+            exact = false;
+            run_tile(w, s, cap);
+            for (int b = 0; b < s0.nb; ++b) p.t[b + 1] = 2 * s.cnt[b] + s0.off[b];
+        } else {
+            for (int r = 0; r < w.nruns; ++r)
+                for (int b = w.lo[r]; b <= w.hi[r]; ++b) p.t[b + 1] = a[cur ^ 1][b + 1];
+        }
         left -= best;
         ++passes;
     }
@@ -230,28 +314,28 @@ std::vector<fl_pass> plan_sweep(const fl_geom& g, int n, bool dagger, bool with_
         const bool first = dagger ? (b % 2 == 0) : (b % 2 == 1);
         s.off[b] = first ? 0 : 1;
     }
-    std::vector<int> windows;
+    std::vector<Window> windows;
     if (g.W == 0)
-        windows.push_back(g.C);
+        windows.push_back(tile_window(g, g.C));
     else
-        for (int h = g.C; h + g.W <= L; ++h) windows.push_back(h);
+        for (int h = g.C; h + g.W <= L; ++h) windows.push_back(tile_window(g, h));
 
     long long total = (long long)n * nb, done = 0;
     while (done < total) {
         // One-step lookahead: take the window after which the greedy rule
         // finishes in the fewest passes; ties go to the window that applies
         // more gates now, then to the lower window.
-        int best_h = -1, best_cost = 1 << 30;
+        int best_h = -1, best_cost = 1 << 20;
         std::vector<int> best;
-        for (int h : windows) {
+        for (const Window& w : windows) {
             Sched t = s;
-            std::vector<int> got = run_tile(g, h, t, max_gates_per_pass);
+            std::vector<int> got = run_tile(w, t, max_gates_per_pass);
             if (got.empty()) continue;
-            const int cost = greedy_passes(g, windows, t, max_gates_per_pass);
+            const int cost = greedy_passes(windows, t, max_gates_per_pass, best_cost);
             if (cost < best_cost || (cost == best_cost && got.size() > best.size())) {
                 best_cost = cost;
-                best = got;
-                best_h = h;
+                best = std::move(got);
+                best_h = w.h;
             }
         }
         if (best.empty()) break;  // cannot happen for a valid circuit
