@@ -108,16 +108,16 @@ fl_geom adjoint_geom(int L, int dtype) {
 }
 
 // Geometry of the energy / density-matrix reduction: full tiles with 4 low
-// bits (a chain of exactly one full tile takes them as 4 low bits plus a
-// window too); shorter chains in one tile.
+// bits; from L = 10 (9 bonds: 4 windows) a chain in one tile takes them as 4 low
+// bits plus a window too, shorter ones the plain single tile.
 fl_geom rdm_geom(int L, int dtype) {
     const int kmax = kmax_of(dtype);
-    if (L < kmax) return fl::make_geom(L, FL_KMAX_RDM, 2);
+    if (L < 10) return fl::make_geom(L, FL_KMAX_RDM, 2);
     fl_geom g;
     g.L = L;
+    g.K = std::min(L, kmax);
     g.C = FL_RDM_LOWBITS;
-    g.W = kmax - FL_RDM_LOWBITS;
-    g.K = kmax;
+    g.W = g.K - FL_RDM_LOWBITS;
     g.R = 2;
     return g;
 }
@@ -174,8 +174,8 @@ struct fl_ctx {
     void* d_h = nullptr;       // H0 psi: the bond Hamiltonians, 32 reals each (single-tile chains), or the window tables
     double* d_h64 = nullptr;   // the same in FP64 (energy contraction on the device)
     double* d_part = nullptr;  // reduction partials [kReduceGrid][L][16]
-    double* d_red = nullptr;   // finalized reductions, 2 x L x 16
-    double* h_red = nullptr;   // pinned host copy
+    double* h_red = nullptr;   // finalized reductions, 2 x L x 16: pinned host memory that the kernels write
+    double* dh_red = nullptr;  // its device address
     void* d_tabs = nullptr;    // product-state factor tables
     double* d_mpart = nullptr; // gradient partials [kAdjGrid][L-1][16]
     // complex64 reverse pass with window overlaps on the matrix cores:
@@ -447,6 +447,20 @@ int launch_cover_rdm(fl_ctx* c, const void* psi, double* partials, int maxgrid, 
         if (e != hipSuccess) return fail_hip(e, "k_rdm launch");
     }
     *grid_out = grid;
+    return FL_OK;
+}
+
+// The finalized bond reductions of psi -> h_red[0 .. L*16) (there once the
+// stream has run).  The kernels write the pinned host memory themselves: a copy
+// would be one more launch behind them.  A single workgroup's partials are
+// the result.
+int reduce_bonds(fl_ctx* c, const void* psi) {
+    const bool one = ntiles(c->geom_rdm) == 1;
+    int grid = 0;
+    int rc = launch_cover_rdm(c, psi, one ? c->dh_red : c->d_part, kReduceGrid, &grid);
+    if (rc || one) return rc;
+    hipError_t e = fl::launch_finalize(c->d_part, grid, c->L * 16, c->dh_red, c->stream);
+    if (e != hipSuccess) return fail_hip(e, "k_finalize launch");
     return FL_OK;
 }
 
@@ -733,9 +747,8 @@ int apply_h0(fl_ctx* c, const void* psi, void* out, double* dots, int* grid_out)
 
 // The four overlap sums from their partial rows in d_part; synchronises.
 int read_overlap(fl_ctx* c, int grid, double out[4]) {
-    hipError_t e = fl::launch_finalize(c->d_part, grid, 4, c->d_red, c->stream);
+    hipError_t e = fl::launch_finalize(c->d_part, grid, 4, c->dh_red, c->stream);
     if (e != hipSuccess) return fail_hip(e, "k_finalize launch");
-    FL_HIP(hipMemcpyAsync(c->h_red, c->d_red, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     FL_HIP(hipStreamSynchronize(c->stream));
     for (int i = 0; i < 4; ++i) out[i] = c->h_red[i];
     return FL_OK;
@@ -828,8 +841,8 @@ int fl_create(fl_ctx** ctx, int L, int dtype, int variant, void* hip_stream) {
     if (e == hipSuccess) e = hipMalloc(&c->d_h, std::max((size_t)nb * 32, n_h_windows(c) * FL_HWIN_REALS) * rb);
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_h64, (size_t)nb * 32 * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_part, (size_t)kReduceGrid * L * 16 * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc((void**)&c->d_red, (size_t)2 * L * 16 * sizeof(double));
     if (e == hipSuccess) e = hipHostMalloc((void**)&c->h_red, (size_t)2 * L * 16 * sizeof(double), 0);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&c->dh_red, c->h_red, 0);
     if (e == hipSuccess) e = hipMalloc(&c->d_tabs, (size_t)3 * 4096 * 2 * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_mpart, (size_t)kAdjGrid * nb * 16 * sizeof(double));
     if (e == hipSuccess && use_win4_reverse(c))
@@ -859,7 +872,6 @@ int fl_destroy(fl_ctx* c) {
     if (c->d_h) (void)hipFree(c->d_h);
     if (c->d_h64) (void)hipFree(c->d_h64);
     if (c->d_part) (void)hipFree(c->d_part);
-    if (c->d_red) (void)hipFree(c->d_red);
     if (c->h_red) (void)hipHostFree(c->h_red);
     if (c->d_tabs) (void)hipFree(c->d_tabs);
     if (c->d_mpart) (void)hipFree(c->d_mpart);
@@ -1014,12 +1026,8 @@ int fl_expect_energy(fl_ctx* c, const void* psi, double out[2], double* rdm) {
     if (!out) return fail(FL_EINVAL, "out is NULL");
     if (!c->have_h) return fail(FL_ESTATE, "no bond Hamiltonians: call fl_set_bonds first");
     const int L = c->L;
-    int grid = 0;
-    rc = launch_cover_rdm(c, psi, c->d_part, kReduceGrid, &grid);
+    rc = reduce_bonds(c, psi);
     if (rc) return rc;
-    hipError_t e = fl::launch_finalize(c->d_part, grid, L * 16, c->d_red, c->stream);
-    if (e != hipSuccess) return fail_hip(e, "k_finalize launch");
-    FL_HIP(hipMemcpyAsync(c->h_red, c->d_red, (size_t)L * 16 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     FL_HIP(hipStreamSynchronize(c->stream));
     double E = 0.0;
     for (int b = 0; b < L - 1; ++b) {
@@ -1143,12 +1151,10 @@ int fl_grad(fl_ctx* c, void* psi_n, void* const* ckpts, int64_t n, int64_t K, co
     }
     if (P > 0 && !finite_all(gens, (size_t)nb * P * 32)) return fail(FL_EINVAL, "gens has non-finite entries");
     const size_t bytes = (size_t)(1ull << L) * amp_bytes(c->dtype);
-    // 1. bond density matrices of psi_n (explicit terms) -> d_red[0 .. L*16)
-    int grid = 0;
-    rc = launch_cover_rdm(c, psi_n, c->d_part, kReduceGrid, &grid);
+    // 1. bond density matrices of psi_n (explicit terms) -> h_red[0 .. L*16)
+    rc = reduce_bonds(c, psi_n);
     if (rc) return rc;
-    hipError_t e = fl::launch_finalize(c->d_part, grid, L * 16, c->d_red, c->stream);
-    if (e != hipSuccess) return fail_hip(e, "k_finalize launch");
+    hipError_t e = hipSuccess;
     // 2. lambda = H0 psi_n
     rc = apply_h0(c, psi_n, lam, nullptr, nullptr);
     if (rc) return rc;
@@ -1194,8 +1200,6 @@ int fl_grad(fl_ctx* c, void* psi_n, void* const* ckpts, int64_t n, int64_t K, co
             if (K > 0) FL_HIP(hipMemcpyAsync(psi_n, ckpts[s], bytes, hipMemcpyDeviceToDevice, c->stream));
         }
         std::vector<double> qsum(need);
-        FL_HIP(hipMemcpyAsync(c->h_red, c->d_red, (size_t)L * 16 * sizeof(double), hipMemcpyDeviceToHost,
-                              c->stream));
         FL_HIP(hipMemcpyAsync(qsum.data(), c->d_qsum, need * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         FL_HIP(hipStreamSynchronize(c->stream));
         Dmx.assign((size_t)nb * 16, 0.0);
@@ -1210,10 +1214,8 @@ int fl_grad(fl_ctx* c, void* psi_n, void* const* ckpts, int64_t n, int64_t K, co
             if (rc) return rc;
             if (K > 0) FL_HIP(hipMemcpyAsync(psi_n, ckpts[s], bytes, hipMemcpyDeviceToDevice, c->stream));
         }
-        e = fl::launch_finalize(c->d_mpart, agrid, nb * 16, c->d_red + (size_t)L * 16, c->stream);
+        e = fl::launch_finalize(c->d_mpart, agrid, nb * 16, c->dh_red + (size_t)L * 16, c->stream);
         if (e != hipSuccess) return fail_hip(e, "k_finalize launch");
-        FL_HIP(hipMemcpyAsync(c->h_red, c->d_red, (size_t)2 * L * 16 * sizeof(double), hipMemcpyDeviceToHost,
-                              c->stream));
         FL_HIP(hipStreamSynchronize(c->stream));
     }
     const double* Dsrc = Dmx.empty() ? c->h_red + (size_t)L * 16 : Dmx.data();

@@ -814,7 +814,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     constexpr int APL = sizeof(T) == 4 ? 2 : 1;
     constexpr int ITER = (1 << K) / (APL * NT);
     constexpr int UNITS = (1 << (K - 4)) / 64;   // wave-sized parts of a window's register groups
-    static_assert(NW % 4 == 0 && UNITS % NW == 0, "1, 2 or 4 windows share the waves evenly");
+    static_assert(NW == 4 && UNITS >= 1, "1, 2 or 4 windows share the waves evenly (4 below 12 tile bits)");
     constexpr bool PREF = sizeof(T) == 4;   // complex128 has no registers left for the next tile
     typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
     __shared__ __attribute__((aligned(16))) cplx lds[1 << K];
@@ -2486,20 +2486,30 @@ hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pas
     return hipGetLastError();
 }
 
+template <typename T, int K>
+static void launch_windows(const fl_geom& g, const void* psi, const rdm_desc& pd, double* partials, int grid, int nslot,
+                           hipStream_t s) {
+    hipLaunchKernelGGL((k_rdm_windows<T, K, FL_RDM_LOWBITS, 256>), dim3(grid), dim3(256), 0, s,
+                       (const typename CT<T>::c*)psi, g.W, ntiles_of(g), pd, partials, nslot);
+}
+
 hipError_t launch_rdm_windows(int dtype, const fl_geom& g, const void* psi, const rdm_desc& pd, double* partials,
                               int grid, int nslot, hipStream_t s) {
-    const int kmax = dtype == 0 ? FL_KMAX_C64 : FL_KMAX_C128;
-    if (g.K != kmax || g.C != FL_RDM_LOWBITS || (pd.nwin != 1 && pd.nwin != 2 && pd.nwin != 4) || grid < 1)
+    if (g.C != FL_RDM_LOWBITS || g.C + g.W != g.K || (pd.nwin != 1 && pd.nwin != 2 && pd.nwin != 4) || grid < 1)
         return hipErrorInvalidValue;
+    if (g.K < 12 && pd.nwin != 4) return hipErrorInvalidValue;   // fewer windows would leave waves without a part
     for (int w = 0; w < pd.nwin; ++w)
         if (pd.u0[w] < 0 || pd.u0[w] + 4 > g.K) return hipErrorInvalidValue;
-    const uint32_t nt = ntiles_of(g);
-    if (dtype == 0)
-        hipLaunchKernelGGL((k_rdm_windows<float, FL_KMAX_C64, FL_RDM_LOWBITS, 256>), dim3(grid), dim3(256), 0, s,
-                           (const float2*)psi, g.W, nt, pd, partials, nslot);
-    else
-        hipLaunchKernelGGL((k_rdm_windows<double, FL_KMAX_C128, FL_RDM_LOWBITS, 256>), dim3(grid), dim3(256), 0, s,
-                           (const double2*)psi, g.W, nt, pd, partials, nslot);
+    switch (g.K | dtype << 8) {
+        case 10: launch_windows<float, 10>(g, psi, pd, partials, grid, nslot, s); break;
+        case 11: launch_windows<float, 11>(g, psi, pd, partials, grid, nslot, s); break;
+        case 12: launch_windows<float, 12>(g, psi, pd, partials, grid, nslot, s); break;
+        case 13: launch_windows<float, 13>(g, psi, pd, partials, grid, nslot, s); break;
+        case 10 | 256: launch_windows<double, 10>(g, psi, pd, partials, grid, nslot, s); break;
+        case 11 | 256: launch_windows<double, 11>(g, psi, pd, partials, grid, nslot, s); break;
+        case 12 | 256: launch_windows<double, 12>(g, psi, pd, partials, grid, nslot, s); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -84,9 +84,10 @@ def test_sweep_at_the_edges_of_its_tile_sizes(dtype, L, n, dagger):
     assert np.linalg.norm(got - want) < n * (L - 1) * ulp * np.linalg.norm(want)
 
 
-# one full tile; 2 tiles; window shares of 1, 2 and 3 bonds, one and two bonds
+# one tile of each size; 2 tiles; window shares of 1, 2 and 3 bonds, one and two bonds
 # left for a last pass, more tiles than fit between two flushes of the sums
-@pytest.mark.parametrize("dtype,L", [("c64", 13), ("c64", 15), ("c64", 20), ("c64", 22), ("c64", 23), ("c64", 26),
+@pytest.mark.parametrize("dtype,L", [("c64", 10), ("c64", 11), ("c64", 12), ("c128", 10), ("c128", 11),
+                                     ("c64", 13), ("c64", 15), ("c64", 20), ("c64", 22), ("c64", 23), ("c64", 26),
                                      ("c128", 12), ("c128", 13), ("c128", 17), ("c128", 20), ("c128", 23)])
 def test_bond_density_matrices_in_windows(dtype, L):
     """Every bond density matrix and the norm of a random state, against plain
