@@ -73,9 +73,9 @@ fl_geom plain_geom(int L, int dtype) {
 //    share the work; a pass is then a serial chain of LDS round trips, and
 //    smaller register groups (2 or 3 bits) spread it over more waves.  Tiles
 //    below 10 (complex128: 9) bits need more passes than they save.  16
-//    periods, against full tiles (us): complex64 L = 14 123 / 201, 17 161 /
-//    257, 18 180 / 275, 19 220 / 299, 20 271 / 345; complex128 L = 13 121 /
-//    189, 17 179 / 292, 18 208 / 321, 19 253 / 362.
+//    periods, against full tiles (us): complex64 L = 14 105 / 201, 17 139 /
+//    257, 18 157 / 275, 19 220 / 299, 20 271 / 345; complex128 L = 13 108 /
+//    189, 17 160 / 292, 18 193 / 321, 19 253 / 362.
 //  - Longer chains: full tiles (complex64 L = 21: 365 on 13 bits, 407 on 12).
 //  - complex128 on 12-bit tiles takes 3 low bits (128-byte runs, a 9-bit
 //    window) for calls of 3 periods and more: 15 passes instead of 27 for 16

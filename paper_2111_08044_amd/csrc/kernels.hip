@@ -228,10 +228,118 @@ __device__ __forceinline__ void load_gate_lds(const T* src, T (&gv)[32]) {
     }
 }
 
+// apply_pair_g on one quad with the four outputs' chains side by side (the same
+// sums in the same order): a wave alone on its SIMD would wait for each FMA's
+// result on two chains.
+template <typename T>
+__device__ __forceinline__ void apply_quad(T (&vr)[4], T (&vi)[4], const T (&g)[32]) {
+    T sr[4], si[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        sr[i] = -g[10 * i + 1] * vi[i];
+        si[i] = g[10 * i + 1] * vr[i];
+    }
+#pragma unroll
+    for (int jj = 1; jj < 4; ++jj) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = (i + jj) & 3;
+            sr[i] = fma(g[8 * i + 2 * j], vr[j], sr[i]);
+            si[i] = fma(g[8 * i + 2 * j], vi[j], si[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = (i + jj) & 3;
+            sr[i] = fma(-g[8 * i + 2 * j + 1], vi[j], sr[i]);
+            si[i] = fma(g[8 * i + 2 * j + 1], vr[j], si[i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        vr[i] = fma(g[10 * i], vr[i], sr[i]);
+        vi[i] = fma(g[10 * i], vi[i], si[i]);
+    }
+}
+
+// Applies the pass's gates to a tile (or a whole short chain) in LDS, one quad
+// of amplitudes per thread and gate, a barrier between gates.  A serial chain:
+// only its latency matters, so the next gate's descriptor word, its address and
+// its entries (from lg) are fetched while the current one's FMAs run, and
+// between two barriers a thread only reads its quad, applies 64 FMAs and
+// writes it back.  meta holds a pass in words form with one op per group: first
+// bits, then gates << 8.  About 0.39 us a gate, 0.13 of them the FMAs of a
+// wave alone on its SIMD: 16 periods at L = 8 take 44 us (46 without the
+// fetches ahead), at L = 17 on 10-bit tiles 139 us (161; one barrier less per
+// pass but the gate read behind each barrier), complex128 L = 12 96 us (109).
+template <typename T>
+__device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, const uint32_t* meta, int nops,
+                                           bool active) {
+    typedef typename CT<T>::c cplx;
+    char* const lb = reinterpret_cast<char*>(lds);
+    // word k: head (first bit) and op of gate k
+    auto word = [&](int k) {
+        return (uint32_t)__builtin_amdgcn_readfirstlane(meta[k] & 255u) |
+               (uint32_t)__builtin_amdgcn_readfirstlane(meta[nops + k]) << 8;
+    };
+    auto addr = [&](uint32_t w, uint32_t (&la)[4]) {
+        const int u0 = w & 255;
+        const uint32_t s0 = fl_swz(1u << u0) * (uint32_t)sizeof(cplx), s1 = fl_swz(2u << u0) * (uint32_t)sizeof(cplx);
+        la[0] = fl_swz(fl_spread(threadIdx.x, u0, 2)) * (uint32_t)sizeof(cplx);
+        la[1] = la[0] ^ s0;
+        la[2] = la[0] ^ s1;
+        la[3] = la[1] ^ s1;
+    };
+    if (nops == 0) return;
+    T ga[32], gb[32];
+    uint32_t w = word(0), la[4];
+    load_gate_lds<T>(lg + 32 * (w >> 16), ga);
+    addr(w, la);
+    uint32_t wn = word(nops > 1 ? 1 : 0);
+    // one gate with its entries in g; the next one's go to gn
+    auto step = [&](int q, const T (&g)[32], T (&gn)[32]) {
+        T vr[4], vi[4];
+        if (active) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const cplx a = *reinterpret_cast<const cplx*>(lb + la[m]);
+                vr[m] = a.x;
+                vi[m] = a.y;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);   // the quad's reads lead the LDS queue
+        // the next gate: its word was read one gate ago
+        uint32_t ln[4];
+        addr(wn, ln);
+        load_gate_lds<T>(lg + 32 * (wn >> 16), gn);
+        const int k = q + 2 < nops ? q + 2 : nops - 1;
+        const uint32_t h2 = meta[k], o2 = meta[nops + k];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) __asm__ volatile("" : "+v"(ln[m]));
+        __builtin_amdgcn_sched_barrier(0);
+        if (active) {
+            apply_quad<T>(vr, vi, g);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                cplx a;
+                a.x = vr[m];
+                a.y = vi[m];
+                *reinterpret_cast<cplx*>(lb + la[m]) = a;
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) la[m] = ln[m];
+        wn = (uint32_t)__builtin_amdgcn_readfirstlane(h2 & 255u) | (uint32_t)__builtin_amdgcn_readfirstlane(o2) << 8;
+        __syncthreads();
+    };
+    for (int q = 0; q < nops; q += 2) {
+        step(q, ga, gb);
+        if (q + 1 < nops) step(q + 1, gb, ga);
+    }
+}
+
 // Chains of at most FL_KMAX_ONE sites: one workgroup holds the whole state in
-// LDS, one quad of amplitudes per thread and gate.  A serial chain of LDS
-// round trips: nothing but its latency matters, so the descriptor words and
-// the gates sit in LDS beside the state.
+// LDS.
 template <typename T>
 __global__ __launch_bounds__(FL_NT) void k_sweep_one(typename CT<T>::c* __restrict__ psi, const T* __restrict__ gates,
                                                      int L, fl_sweep_words pd) {
@@ -244,38 +352,59 @@ __global__ __launch_bounds__(FL_NT) void k_sweep_one(typename CT<T>::c* __restri
     for (int t = threadIdx.x; t < (L - 1) * 32; t += FL_NT) lg[t] = gates[t];
     for (int t = threadIdx.x; t < pd.nwords; t += FL_NT) meta[t] = pd.w[t];
     __syncthreads();
-    const bool active = threadIdx.x < (1u << (L - 2));
-    const int ng = pd.ngroups;
-    int pos = ng;
-    for (int g = 0; g < ng; ++g) {
-        const uint32_t head = meta[g];
-        const int u0 = head & 255, nops = head >> 8;
-        if (active) {
-            const uint32_t b0 = fl_spread(threadIdx.x, u0, 2);
-            T vr[4], vi[4];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const cplx a = lds[fl_swz(b0 | ((uint32_t)m << u0))];
-                vr[m] = a.x;
-                vi[m] = a.y;
-            }
-            for (int q = 0; q < nops; ++q) {
-                T gv[32];
-                load_gate_lds<T>(lg + 32 * (meta[pos + q] >> 8), gv);
-                apply_pair_g<T, 2, 0>(vr, vi, gv);
-            }
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                cplx a;
-                a.x = vr[m];
-                a.y = vi[m];
-                lds[fl_swz(b0 | ((uint32_t)m << u0))] = a;
-            }
-        }
-        pos += nops;
-        __syncthreads();
-    }
+    quad_chain<T>(lds, lg, meta, pd.ngroups, threadIdx.x < (1u << (L - 2)));
     for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) psi[j] = lds[fl_swz(j)];
+}
+
+// Tiles of 2^KT amplitudes (KT <= 10), one per workgroup.
+template <typename T, int KT, int CL>
+__global__ __launch_bounds__(1 << (KT - 2)) void k_sweep_quads(typename CT<T>::c* __restrict__ psi,
+                                                              const T* __restrict__ gates, int W, fl_sweep_words pd,
+                                                              int ngates) {
+    typedef typename CT<T>::c cplx;
+    constexpr int K = KT, C = CL, NT = 1 << (K - 2);
+    constexpr int APL = sizeof(T) == 4 ? 2 : 1;   // amplitudes per 16 bytes
+    constexpr int ITER = (1 << K) / (APL * NT);
+    static_assert((APL * NT) % (1 << C) == 0, "tile access stride");
+    typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
+    __shared__ __attribute__((aligned(16))) cplx lds[1 << K];
+    __shared__ __attribute__((aligned(16))) T lg[FL_MAX_GATE_TABLE * 32];
+    __shared__ uint32_t meta[FL_SWEEP_WORDS];
+    const int h = pd.h;
+    cplx* const src = psi + fl_tile_base(blockIdx.x, C, W, h) + fl_tile_offset(APL * threadIdx.x, C, h);
+    const uint64_t tstride = (uint64_t)((APL * NT) >> C) << h;
+    const uint32_t l0 = fl_swz(APL * threadIdx.x);
+    v16 a[ITER];
+#pragma unroll
+    for (int s = 0; s < ITER; ++s) a[s] = *reinterpret_cast<const v16*>(src + s * tstride);
+    const fl_f32x4* gsrc = reinterpret_cast<const fl_f32x4*>(gates);
+    for (int t = threadIdx.x; t < ngates * (int)(32 * sizeof(T) / 16); t += NT) reinterpret_cast<fl_f32x4*>(lg)[t] = gsrc[t];
+    for (int t = threadIdx.x; t < pd.nwords; t += NT) meta[t] = pd.w[t];
+#pragma unroll
+    for (int s = 0; s < ITER; ++s) {
+        const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
+        if constexpr (sizeof(T) == 4) {
+            lds[l] = make_float2(a[s][0], a[s][1]);
+            lds[l ^ 1] = make_float2(a[s][2], a[s][3]);
+        } else {
+            lds[l] = make_double2(a[s][0], a[s][1]);
+        }
+    }
+    __syncthreads();
+    quad_chain<T>(lds, lg, meta, pd.ngroups, true);
+#pragma unroll
+    for (int s = 0; s < ITER; ++s) {
+        const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
+        v16 x;
+        if constexpr (sizeof(T) == 4) {
+            const float2 p = lds[l], q = lds[l ^ 1];
+            x = v16{p.x, p.y, q.x, q.y};
+        } else {
+            const double2 p = lds[l];
+            x = v16{p.x, p.y};
+        }
+        *reinterpret_cast<v16*>(src + s * tstride) = x;
+    }
 }
 
 // Op q of group g as (gate-table index, register bit), read as aligned 32-bit
@@ -344,8 +473,8 @@ __device__ __forceinline__ void sweep_group_ops(T (&vr)[1 << R], T (&vi)[1 << R]
 // loads (many workgroups per CU: the loads hit the scalar cache and other
 // waves fill the wait), or fl_sweep_words, copied to LDS (short chains with at
 // most one workgroup per CU, where a scalar-cache miss per group or op would
-// add to a serial chain: 16 periods at L = 17 on 10-bit tiles take 170 us
-// against 192 with scalar loads).
+// add to a serial chain: 16 periods at L = 17 on 10-bit tiles with 3-bit groups
+// took 170 us against 192 with scalar loads).
 //
 // The first group is loaded straight from HBM into its register layout, and
 // the last group stored straight back, when the group's lowest bit u0 is at
@@ -2436,6 +2565,36 @@ static hipError_t launch_tiles(const fl_geom& g, void* psi, const void* gates, c
     return hipGetLastError();
 }
 
+// The words form with one op per group (2-bit groups): a bond's gates never
+// follow each other without its neighbours' between them, unless it has none.
+static bool quad_words(const fl_pass& pd, int gofs, fl_sweep_words& w) {
+    if (!sweep_words(pd, gofs, w)) return false;
+    int n = 0;
+    for (int g = 0; g < pd.ngroups; ++g) n += pd.nops[g];
+    if (2 * n + 1 > FL_SWEEP_WORDS) return false;
+    int k = 0;
+    for (int g = 0; g < pd.ngroups; ++g)
+        for (int q = 0; q < pd.nops[g]; ++q, ++k) {
+            w.w[k] = (uint32_t)pd.u0[g];
+            w.w[n + k] = (uint32_t)(pd.opg[g][q] - gofs) << 8;
+        }
+    w.w[2 * n] = 0;
+    w.ngroups = n;
+    w.nwords = 2 * n + 1;
+    return true;
+}
+
+template <typename T, int K, int C>
+static hipError_t launch_quads(const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int gofs,
+                               hipStream_t s) {
+    typedef typename CT<T>::c cplx;
+    fl_sweep_words w;
+    if (!quad_words(pd, gofs, w)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_sweep_quads<T, K, C>), dim3(ntiles_of(g)), dim3(1 << (K - 2)), 0, s, (cplx*)psi,
+                       (const T*)gates + 32 * gofs, g.W, w, g.L - 1);
+    return hipGetLastError();
+}
+
 hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd,
                         hipStream_t s) {
     // a pass applies gates of one direction: G_b (table entries 0 .. L-2) or G_b^dagger
@@ -2450,7 +2609,7 @@ hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gate
     if (g.W == 0) {
         if (g.L < 2 || g.L > FL_KMAX_ONE || g.R != 2) return hipErrorInvalidValue;
         fl_sweep_words w;
-        if (!sweep_words(pd, gofs, w)) return hipErrorInvalidValue;
+        if (!quad_words(pd, gofs, w)) return hipErrorInvalidValue;
         if (dtype == 0)
             hipLaunchKernelGGL(k_sweep_one<float>, dim3(1), dim3(FL_NT), 0, s, (float2*)psi,
                                (const float*)gates + 32 * gofs, g.L, w);
@@ -2465,12 +2624,12 @@ hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gate
     if (key == code(0, 13, 4, 4)) return launch_tiles<float, 4, 13, 4, 4, fl_pass>(g, psi, gates, pd, gofs, s);
     if (key == code(0, 12, 3, 3)) return launch_tiles<float, 3, 12, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
     if (key == code(0, 11, 3, 3)) return launch_tiles<float, 3, 11, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
-    if (key == code(0, 10, 3, 2)) return launch_tiles<float, 2, 10, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 10, 3, 2)) return launch_quads<float, 10, 3>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 12, 6, 4)) return launch_tiles<double, 4, 12, 6, 2, fl_pass>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 12, 3, 4)) return launch_tiles<double, 4, 12, 3, 2, fl_pass>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 11, 3, 3)) return launch_tiles<double, 3, 11, 3, 2, fl_sweep_words>(g, psi, gates, pd, gofs, s);
-    if (key == code(1, 10, 3, 2)) return launch_tiles<double, 2, 10, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
-    if (key == code(1, 9, 3, 2)) return launch_tiles<double, 2, 9, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 10, 3, 2)) return launch_quads<double, 10, 3>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 9, 3, 2)) return launch_quads<double, 9, 3>(g, psi, gates, pd, gofs, s);
     return hipErrorInvalidValue;
 }
 
