@@ -228,27 +228,28 @@ __device__ __forceinline__ void load_gate_lds(const T* src, T (&gv)[32]) {
     }
 }
 
-// apply_pair_g on one quad with the four outputs' chains side by side (the same
-// sums in the same order): a wave alone on its SIMD would wait for each FMA's
-// result on two chains.
-template <typename T>
-__device__ __forceinline__ void apply_quad(T (&vr)[4], T (&vi)[4], const T (&g)[32]) {
-    T sr[4], si[4];
+// The first NO outputs of a gate on one quad (v holds the quad, g the NO rows),
+// their chains side by side: a wave alone on its SIMD would wait for each FMA's
+// result on two chains.  Each output is the same sum in the same order as in
+// apply_pair_g: own imaginary term, the others in cyclic order, own real term.
+template <typename T, int NO>
+__device__ __forceinline__ void apply_rows(T (&vr)[4], T (&vi)[4], const T (&g)[8 * NO]) {
+    T sr[NO], si[NO];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NO; ++i) {
         sr[i] = -g[10 * i + 1] * vi[i];
         si[i] = g[10 * i + 1] * vr[i];
     }
 #pragma unroll
     for (int jj = 1; jj < 4; ++jj) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NO; ++i) {
             const int j = (i + jj) & 3;
             sr[i] = fma(g[8 * i + 2 * j], vr[j], sr[i]);
             si[i] = fma(g[8 * i + 2 * j], vi[j], si[i]);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NO; ++i) {
             const int j = (i + jj) & 3;
             sr[i] = fma(-g[8 * i + 2 * j + 1], vi[j], sr[i]);
             si[i] = fma(g[8 * i + 2 * j + 1], vr[j], si[i]);
@@ -256,48 +257,95 @@ __device__ __forceinline__ void apply_quad(T (&vr)[4], T (&vi)[4], const T (&g)[
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NO; ++i) {
         vr[i] = fma(g[10 * i], vr[i], sr[i]);
         vi[i] = fma(g[10 * i], vi[i], si[i]);
     }
 }
 
+// A thread's place in a quad chain with S threads per quad: the quad, and the
+// first of the 4 / S outputs that it computes.  The threads of a quad are lanes
+// of one wave, so all of them have read the quad before any writes to it.
+template <int S>
+struct fl_quad_lane {
+    static constexpr int QPW = 64 / S;   // quads per wave
+    uint32_t quad, rot;
+    __device__ __forceinline__ fl_quad_lane()
+        : quad((threadIdx.x >> 6) * QPW + (threadIdx.x & (QPW - 1))), rot(((threadIdx.x & 63) / QPW) * (4 / S)) {}
+};
+
 // Applies the pass's gates to a tile (or a whole short chain) in LDS, one quad
-// of amplitudes per thread and gate, a barrier between gates.  A serial chain:
-// only its latency matters, so the next gate's descriptor word, its address and
-// its entries (from lg) are fetched while the current one's FMAs run, and
-// between two barriers a thread only reads its quad, applies 64 FMAs and
-// writes it back.  meta holds a pass in words form with one op per group: first
-// bits, then gates << 8.  About 0.39 us a gate, 0.13 of them the FMAs of a
-// wave alone on its SIMD: 16 periods at L = 8 take 44 us (46 without the
-// fetches ahead), at L = 17 on 10-bit tiles 139 us (161; one barrier less per
-// pass but the gate read behind each barrier), complex128 L = 12 96 us (109).
-template <typename T>
+// of amplitudes per S threads and gate, a barrier between gates.  A serial
+// chain: only its latency matters, so the next gate's descriptor word, its
+// address and its entries (from lg) are fetched while the current one's FMAs
+// run, and between two barriers a thread only reads its quad, applies 64 / S
+// FMAs and writes its outputs back.  Each thread holds the quad and its gate
+// rows rotated, so that its first output stands first; the sums do not depend
+// on S.  About 0.33 us a gate (0.39 with one thread per quad, of which 0.13 are
+// the 64 FMAs of a wave alone on its SIMD).  meta holds a pass in words form with one op per group: first bits,
+// then gates << 8.
+template <typename T, int S>
 __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, const uint32_t* meta, int nops,
-                                           bool active) {
+                                           const fl_quad_lane<S>& me, bool active) {
     typedef typename CT<T>::c cplx;
+    constexpr int NO = 4 / S;
     char* const lb = reinterpret_cast<char*>(lds);
     // word k: head (first bit) and op of gate k
     auto word = [&](int k) {
         return (uint32_t)__builtin_amdgcn_readfirstlane(meta[k] & 255u) |
                (uint32_t)__builtin_amdgcn_readfirstlane(meta[nops + k]) << 8;
     };
+    // la[m]: amplitude (m + rot) & 3 of the quad
     auto addr = [&](uint32_t w, uint32_t (&la)[4]) {
         const int u0 = w & 255;
         const uint32_t s0 = fl_swz(1u << u0) * (uint32_t)sizeof(cplx), s1 = fl_swz(2u << u0) * (uint32_t)sizeof(cplx);
-        la[0] = fl_swz(fl_spread(threadIdx.x, u0, 2)) * (uint32_t)sizeof(cplx);
-        la[1] = la[0] ^ s0;
-        la[2] = la[0] ^ s1;
-        la[3] = la[1] ^ s1;
+        const uint32_t b = fl_swz(fl_spread(me.quad, u0, 2)) * (uint32_t)sizeof(cplx);
+        if constexpr (S == 4) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const uint32_t x = m + me.rot;
+                la[m] = b ^ ((x & 1) ? s0 : 0u) ^ ((x & 2) ? s1 : 0u);
+            }
+        } else {
+            la[0] = S == 2 ? b ^ (me.rot ? s1 : 0u) : b;
+            la[1] = la[0] ^ s0;
+            la[2] = la[0] ^ s1;
+            la[3] = la[1] ^ s1;
+        }
+    };
+    // rows rot .. rot + NO - 1 of gate k, the columns from rot on
+    auto load_rows = [&](uint32_t k, T (&g)[8 * NO]) {
+        const T* const src = lg + 32 * k + 8 * me.rot;
+        if constexpr (S == 1) {
+            load_gate_lds<T>(src, g);
+        } else if constexpr (S == 2 && sizeof(T) == 4) {
+#pragma unroll
+            for (int i = 0; i < NO; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const fl_f32x4 v = *reinterpret_cast<const fl_f32x4*>(src + 8 * i + ((4 * h) ^ (2 * me.rot)));
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) g[8 * i + 4 * h + x] = v[x];
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NO; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const cplx v = *reinterpret_cast<const cplx*>(src + 8 * i + 2 * ((j + me.rot) & 3));
+                    g[8 * i + 2 * j] = v.x;
+                    g[8 * i + 2 * j + 1] = v.y;
+                }
+        }
     };
     if (nops == 0) return;
-    T ga[32], gb[32];
+    T ga[8 * NO], gb[8 * NO];
     uint32_t w = word(0), la[4];
-    load_gate_lds<T>(lg + 32 * (w >> 16), ga);
+    load_rows(w >> 16, ga);
     addr(w, la);
     uint32_t wn = word(nops > 1 ? 1 : 0);
     // one gate with its entries in g; the next one's go to gn
-    auto step = [&](int q, const T (&g)[32], T (&gn)[32]) {
+    auto step = [&](int q, const T (&g)[8 * NO], T (&gn)[8 * NO]) {
         T vr[4], vi[4];
         if (active) {
 #pragma unroll
@@ -311,16 +359,16 @@ __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, 
         // the next gate: its word was read one gate ago
         uint32_t ln[4];
         addr(wn, ln);
-        load_gate_lds<T>(lg + 32 * (wn >> 16), gn);
+        load_rows(wn >> 16, gn);
         const int k = q + 2 < nops ? q + 2 : nops - 1;
         const uint32_t h2 = meta[k], o2 = meta[nops + k];
 #pragma unroll
         for (int m = 0; m < 4; ++m) __asm__ volatile("" : "+v"(ln[m]));
         __builtin_amdgcn_sched_barrier(0);
         if (active) {
-            apply_quad<T>(vr, vi, g);
+            apply_rows<T, NO>(vr, vi, g);
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
+            for (int m = 0; m < NO; ++m) {
                 cplx a;
                 a.x = vr[m];
                 a.y = vi[m];
@@ -340,31 +388,36 @@ __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, 
 
 // Chains of at most FL_KMAX_ONE sites: one workgroup holds the whole state in
 // LDS.
-template <typename T>
-__global__ __launch_bounds__(FL_NT) void k_sweep_one(typename CT<T>::c* __restrict__ psi, const T* __restrict__ gates,
-                                                     int L, fl_sweep_words pd) {
+template <typename T, int S, int NT>
+__global__ __launch_bounds__(NT) void k_sweep_one(typename CT<T>::c* __restrict__ psi, const T* __restrict__ gates,
+                                                  int L, fl_sweep_words pd) {
     typedef typename CT<T>::c cplx;
     __shared__ __attribute__((aligned(16))) T lg[FL_KMAX_ONE * 32];
     __shared__ uint32_t meta[FL_SWEEP_WORDS];
-    __shared__ cplx lds[1 << FL_KMAX_ONE];
-    static_assert((1 << FL_KMAX_ONE) / 4 <= FL_NT, "one quad per thread");
-    for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) lds[fl_swz(j)] = psi[j];
-    for (int t = threadIdx.x; t < (L - 1) * 32; t += FL_NT) lg[t] = gates[t];
-    for (int t = threadIdx.x; t < pd.nwords; t += FL_NT) meta[t] = pd.w[t];
+    __shared__ __attribute__((aligned(16))) cplx lds[1 << FL_KMAX_ONE];
+    for (uint32_t j = threadIdx.x; j < (1u << L); j += NT) lds[fl_swz(j)] = psi[j];
+    for (int t = threadIdx.x; t < (L - 1) * 32; t += NT) lg[t] = gates[t];
+    for (int t = threadIdx.x; t < pd.nwords; t += NT) meta[t] = pd.w[t];
     __syncthreads();
-    quad_chain<T>(lds, lg, meta, pd.ngroups, threadIdx.x < (1u << (L - 2)));
-    for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) psi[j] = lds[fl_swz(j)];
+    const fl_quad_lane<S> me;
+    quad_chain<T, S>(lds, lg, meta, pd.ngroups, me, me.quad < (1u << (L - 2)));
+    for (uint32_t j = threadIdx.x; j < (1u << L); j += NT) psi[j] = lds[fl_swz(j)];
 }
 
-// Tiles of 2^KT amplitudes (KT <= 10), one per workgroup.
-template <typename T, int KT, int CL>
-__global__ __launch_bounds__(1 << (KT - 2)) void k_sweep_quads(typename CT<T>::c* __restrict__ psi,
+// Tiles of 2^KT amplitudes (KT <= 11), one per workgroup, S threads per quad:
+// two on 9- and 10-bit tiles, which then have four and eight waves (16 periods,
+// against one per quad (us): complex64 L = 12 73.1 / 81.8, 17 127 / 139;
+// complex128 L = 12 91.8 / 96.3, 18 181 / 193), one on 11 bits (192.7 with two
+// at L = 19, 190.4 with one: all SIMDs have two waves already).
+template <typename T, int KT, int CL, int S>
+__global__ __launch_bounds__(S << (KT - 2)) void k_sweep_quads(typename CT<T>::c* __restrict__ psi,
                                                               const T* __restrict__ gates, int W, fl_sweep_words pd,
                                                               int ngates) {
     typedef typename CT<T>::c cplx;
-    constexpr int K = KT, C = CL, NT = 1 << (K - 2);
+    constexpr int K = KT, C = CL, NT = S << (K - 2);
     constexpr int APL = sizeof(T) == 4 ? 2 : 1;   // amplitudes per 16 bytes
     constexpr int ITER = (1 << K) / (APL * NT);
+    static_assert(ITER >= 1, "a whole access per thread");
     static_assert((APL * NT) % (1 << C) == 0, "tile access stride");
     typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
     __shared__ __attribute__((aligned(16))) cplx lds[1 << K];
@@ -391,7 +444,7 @@ __global__ __launch_bounds__(1 << (KT - 2)) void k_sweep_quads(typename CT<T>::c
         }
     }
     __syncthreads();
-    quad_chain<T>(lds, lg, meta, pd.ngroups, true);
+    quad_chain<T, S>(lds, lg, meta, pd.ngroups, fl_quad_lane<S>(), true);
 #pragma unroll
     for (int s = 0; s < ITER; ++s) {
         const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
@@ -2584,15 +2637,38 @@ static bool quad_words(const fl_pass& pd, int gofs, fl_sweep_words& w) {
     return true;
 }
 
-template <typename T, int K, int C>
+template <typename T, int K, int C, int S>
 static hipError_t launch_quads(const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int gofs,
                                hipStream_t s) {
     typedef typename CT<T>::c cplx;
     fl_sweep_words w;
     if (!quad_words(pd, gofs, w)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_sweep_quads<T, K, C>), dim3(ntiles_of(g)), dim3(1 << (K - 2)), 0, s, (cplx*)psi,
+    hipLaunchKernelGGL((k_sweep_quads<T, K, C, S>), dim3(ntiles_of(g)), dim3(S << (K - 2)), 0, s, (cplx*)psi,
                        (const T*)gates + 32 * gofs, g.W, w, g.L - 1);
     return hipGetLastError();
+}
+
+template <typename T, int S, int NT>
+static hipError_t launch_one_s(int L, void* psi, const void* gates, const fl_sweep_words& w, int gofs, hipStream_t s) {
+    typedef typename CT<T>::c cplx;
+    hipLaunchKernelGGL((k_sweep_one<T, S, NT>), dim3(1), dim3(NT), 0, s, (cplx*)psi, (const T*)gates + 32 * gofs, L, w);
+    return hipGetLastError();
+}
+
+// Threads per quad: as many as give every SIMD a wave (L = 8: 64 quads in four
+// waves instead of one), two at most where the quads alone do; up to L = 6 one
+// wave holds all and no barrier waits for another.  16 periods, with one thread
+// per quad in 256-thread workgroups before (us): complex64 L = 4 20.1 -> 14.0,
+// 8 44.0 -> 36.2, 9 54.3 -> 42.5, 10 62.9 -> 54.3; complex128 L = 6 34.8 -> 20.9,
+// 8 50.2 -> 40.0, 10 77.2 -> 72.1.  Four per quad are slower at L = 9 (45.8) and
+// 10 (66.3): each reads the whole quad.  L = 2 has nothing to share.
+template <typename T>
+static hipError_t launch_one(int L, void* psi, const void* gates, const fl_sweep_words& w, int gofs, hipStream_t s) {
+    if (L == 2) return launch_one_s<T, 1, 64>(L, psi, gates, w, gofs, s);
+    if (L <= 6) return launch_one_s<T, 4, 64>(L, psi, gates, w, gofs, s);
+    if (L <= 8) return launch_one_s<T, 4, 256>(L, psi, gates, w, gofs, s);
+    if (L == 9) return launch_one_s<T, 2, 256>(L, psi, gates, w, gofs, s);
+    return launch_one_s<T, 2, 512>(L, psi, gates, w, gofs, s);
 }
 
 hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd,
@@ -2610,26 +2686,20 @@ hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gate
         if (g.L < 2 || g.L > FL_KMAX_ONE || g.R != 2) return hipErrorInvalidValue;
         fl_sweep_words w;
         if (!quad_words(pd, gofs, w)) return hipErrorInvalidValue;
-        if (dtype == 0)
-            hipLaunchKernelGGL(k_sweep_one<float>, dim3(1), dim3(FL_NT), 0, s, (float2*)psi,
-                               (const float*)gates + 32 * gofs, g.L, w);
-        else
-            hipLaunchKernelGGL(k_sweep_one<double>, dim3(1), dim3(FL_NT), 0, s, (double2*)psi,
-                               (const double*)gates + 32 * gofs, g.L, w);
-        return hipGetLastError();
+        return dtype == 0 ? launch_one<float>(g.L, psi, gates, w, gofs, s) : launch_one<double>(g.L, psi, gates, w, gofs, s);
     }
     // the geometries of sweep_geom
     const int key = (dtype << 12) | (g.K << 8) | (g.C << 4) | g.R;
     auto code = [](int dt, int K, int C, int R) { return (dt << 12) | (K << 8) | (C << 4) | R; };
     if (key == code(0, 13, 4, 4)) return launch_tiles<float, 4, 13, 4, 4, fl_pass>(g, psi, gates, pd, gofs, s);
-    if (key == code(0, 12, 3, 3)) return launch_tiles<float, 3, 12, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
-    if (key == code(0, 11, 3, 3)) return launch_tiles<float, 3, 11, 3, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
-    if (key == code(0, 10, 3, 2)) return launch_quads<float, 10, 3>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 12, 4, 3)) return launch_tiles<float, 3, 12, 4, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 11, 3, 2)) return launch_quads<float, 11, 3, 1>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 10, 3, 2)) return launch_quads<float, 10, 3, 2>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 12, 6, 4)) return launch_tiles<double, 4, 12, 6, 2, fl_pass>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 12, 3, 4)) return launch_tiles<double, 4, 12, 3, 2, fl_pass>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 11, 3, 3)) return launch_tiles<double, 3, 11, 3, 2, fl_sweep_words>(g, psi, gates, pd, gofs, s);
-    if (key == code(1, 10, 3, 2)) return launch_quads<double, 10, 3>(g, psi, gates, pd, gofs, s);
-    if (key == code(1, 9, 3, 2)) return launch_quads<double, 9, 3>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 10, 3, 2)) return launch_quads<double, 10, 3, 2>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 9, 3, 2)) return launch_quads<double, 9, 3, 2>(g, psi, gates, pd, gofs, s);
     return hipErrorInvalidValue;
 }
 

@@ -84,6 +84,18 @@ def test_sweep_at_the_edges_of_its_tile_sizes(dtype, L, n, dagger):
     assert np.linalg.norm(got - want) < n * (L - 1) * ulp * np.linalg.norm(want)
 
 
+# one workgroup: a lone quad, then each number of threads per quad (4 in one
+# wave, 4, 2) at its shortest and longest chain; two threads per quad on 9- and
+# 10-bit tiles between the chains above, with a remainder after a block
+@pytest.mark.parametrize("dagger", [False, True])
+@pytest.mark.parametrize("dtype,L,n", [(d, L, n) for d in ("c64", "c128") for L, n in
+                                       ((2, 5), (3, 19), (4, 5), (6, 5), (7, 5), (8, 19), (9, 5), (10, 17),
+                                        (12, 17), (14, 3))])
+def test_sweep_with_several_threads_per_quad(dtype, L, n, dagger):
+    """As test_sweep_at_the_edges_of_its_tile_sizes, with its tolerance."""
+    test_sweep_at_the_edges_of_its_tile_sizes(dtype, L, n, dagger)
+
+
 # one tile of each size; 2 tiles; window shares of 1, 2 and 3 bonds, one and two bonds
 # left for a last pass, more tiles than fit between two flushes of the sums
 @pytest.mark.parametrize("dtype,L", [("c64", 10), ("c64", 11), ("c64", 12), ("c128", 10), ("c128", 11),
