@@ -98,13 +98,13 @@ fl_geom sweep_geom(int L, int dtype, int64_t n) {
 // one workgroup up to L = 10, then tiles of L - 8 bits (256 workgroups) of at
 // least 9 bits, up to the 12 bits whose two tiles leave room for two workgroups
 // per CU.  fl_grad over 50 periods, against 12-bit tiles with 4-bit groups
-// (us): complex64 L = 12 827 / 1263, 14 985 / 1684, 18 1472 / 2268, 19 1838 /
-// 2450, 20 2328 / 2661 (L = 21: 4317 / 3542); complex128 L = 14 1076 / 2070,
-// 18 1679 / 2817, 19 2123 / 3058.
+// (us): complex64 L = 12 657 / 1263, 14 794 / 1684, 18 1228 / 2268, 19 1765 /
+// 2450 (1865 with 3-bit groups on 11-bit tiles), 20 2364 / 2661 (L = 21: 4317 /
+// 3542); complex128 L = 14 882 / 2070, 18 1608 / 2817, 19 2158 / 3058.
 fl_geom adjoint_geom(int L, int dtype) {
     if (L <= FL_KMAX_ONE) return fl::make_geom(L, FL_KMAX_ONE, 2, 3);
     const int k = std::max(L - 8, 9);
-    if (k <= 10) return fl::make_geom(L, k, 2, 3);
+    if (k <= 10 || (k == 11 && dtype == FL_C64)) return fl::make_geom(L, k, 2, 3);
     if (k == 11) return fl::make_geom(L, k, 3, 3);
     if (k == 12 && dtype == FL_C64) return fl::make_geom(L, FL_KMAX_ADJ, 3, kAdjLowBits);
     return fl::make_geom(L, FL_KMAX_ADJ, 4, kAdjLowBits);

@@ -274,6 +274,56 @@ struct fl_quad_lane {
         : quad((threadIdx.x >> 6) * QPW + (threadIdx.x & (QPW - 1))), rot(((threadIdx.x & 63) / QPW) * (4 / S)) {}
 };
 
+// LDS byte offsets of the thread's quad on tile bits (u0, u0 + 1): la[m] is
+// amplitude (m + rot) & 3.
+template <typename T, int S>
+__device__ __forceinline__ void quad_addr(const fl_quad_lane<S>& me, int u0, uint32_t (&la)[4]) {
+    constexpr uint32_t SZ = sizeof(typename CT<T>::c);
+    const uint32_t s0 = fl_swz(1u << u0) * SZ, s1 = fl_swz(2u << u0) * SZ;
+    const uint32_t b = fl_swz(fl_spread(me.quad, u0, 2)) * SZ;
+    if constexpr (S == 4) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const uint32_t x = m + me.rot;
+            la[m] = b ^ ((x & 1) ? s0 : 0u) ^ ((x & 2) ? s1 : 0u);
+        }
+    } else {
+        la[0] = S == 2 ? b ^ (me.rot ? s1 : 0u) : b;
+        la[1] = la[0] ^ s0;
+        la[2] = la[0] ^ s1;
+        la[3] = la[1] ^ s1;
+    }
+}
+
+// Rows rot .. rot + 4 / S - 1 of the gate at src, their columns from rot on.
+template <typename T, int S>
+__device__ __forceinline__ void load_gate_rows(const fl_quad_lane<S>& me, const T* src, T (&g)[32 / S]) {
+    typedef typename CT<T>::c cplx;
+    constexpr int NO = 4 / S;
+    src += 8 * me.rot;
+    if constexpr (S == 1) {
+        load_gate_lds<T>(src, g);
+    } else if constexpr (S == 2 && sizeof(T) == 4) {
+#pragma unroll
+        for (int i = 0; i < NO; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const fl_f32x4 v = *reinterpret_cast<const fl_f32x4*>(src + 8 * i + ((4 * h) ^ (2 * me.rot)));
+#pragma unroll
+                for (int x = 0; x < 4; ++x) g[8 * i + 4 * h + x] = v[x];
+            }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NO; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const cplx v = *reinterpret_cast<const cplx*>(src + 8 * i + 2 * ((j + me.rot) & 3));
+                g[8 * i + 2 * j] = v.x;
+                g[8 * i + 2 * j + 1] = v.y;
+            }
+    }
+}
+
 // Applies the pass's gates to a tile (or a whole short chain) in LDS, one quad
 // of amplitudes per S threads and gate, a barrier between gates.  A serial
 // chain: only its latency matters, so the next gate's descriptor word, its
@@ -295,54 +345,11 @@ __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, 
         return (uint32_t)__builtin_amdgcn_readfirstlane(meta[k] & 255u) |
                (uint32_t)__builtin_amdgcn_readfirstlane(meta[nops + k]) << 8;
     };
-    // la[m]: amplitude (m + rot) & 3 of the quad
-    auto addr = [&](uint32_t w, uint32_t (&la)[4]) {
-        const int u0 = w & 255;
-        const uint32_t s0 = fl_swz(1u << u0) * (uint32_t)sizeof(cplx), s1 = fl_swz(2u << u0) * (uint32_t)sizeof(cplx);
-        const uint32_t b = fl_swz(fl_spread(me.quad, u0, 2)) * (uint32_t)sizeof(cplx);
-        if constexpr (S == 4) {
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const uint32_t x = m + me.rot;
-                la[m] = b ^ ((x & 1) ? s0 : 0u) ^ ((x & 2) ? s1 : 0u);
-            }
-        } else {
-            la[0] = S == 2 ? b ^ (me.rot ? s1 : 0u) : b;
-            la[1] = la[0] ^ s0;
-            la[2] = la[0] ^ s1;
-            la[3] = la[1] ^ s1;
-        }
-    };
-    // rows rot .. rot + NO - 1 of gate k, the columns from rot on
-    auto load_rows = [&](uint32_t k, T (&g)[8 * NO]) {
-        const T* const src = lg + 32 * k + 8 * me.rot;
-        if constexpr (S == 1) {
-            load_gate_lds<T>(src, g);
-        } else if constexpr (S == 2 && sizeof(T) == 4) {
-#pragma unroll
-            for (int i = 0; i < NO; ++i)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const fl_f32x4 v = *reinterpret_cast<const fl_f32x4*>(src + 8 * i + ((4 * h) ^ (2 * me.rot)));
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) g[8 * i + 4 * h + x] = v[x];
-                }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NO; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const cplx v = *reinterpret_cast<const cplx*>(src + 8 * i + 2 * ((j + me.rot) & 3));
-                    g[8 * i + 2 * j] = v.x;
-                    g[8 * i + 2 * j + 1] = v.y;
-                }
-        }
-    };
     if (nops == 0) return;
     T ga[8 * NO], gb[8 * NO];
     uint32_t w = word(0), la[4];
-    load_rows(w >> 16, ga);
-    addr(w, la);
+    load_gate_rows<T, S>(me, lg + 32 * (w >> 16), ga);
+    quad_addr<T, S>(me, w & 255, la);
     uint32_t wn = word(nops > 1 ? 1 : 0);
     // one gate with its entries in g; the next one's go to gn
     auto step = [&](int q, const T (&g)[8 * NO], T (&gn)[8 * NO]) {
@@ -358,8 +365,8 @@ __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, 
         __builtin_amdgcn_sched_barrier(0);   // the quad's reads lead the LDS queue
         // the next gate: its word was read one gate ago
         uint32_t ln[4];
-        addr(wn, ln);
-        load_rows(wn >> 16, gn);
+        quad_addr<T, S>(me, wn & 255, ln);
+        load_gate_rows<T, S>(me, lg + 32 * (wn >> 16), gn);
         const int k = q + 2 < nops ? q + 2 : nops - 1;
         const uint32_t h2 = meta[k], o2 = meta[nops + k];
 #pragma unroll
@@ -1634,76 +1641,239 @@ __device__ __forceinline__ void adj_op(T (&pr)[1 << R], T (&pi)[1 << R], T (&lr)
     });
 }
 
-// Chains of at most FL_KMAX_ONE sites: one workgroup, one quad of each state
-// per thread and op, as k_sweep_one.
+// Sums a and b over the lanes l and l ^ 32: a's sum in the lower half of the
+// wave, b's in the upper half.
 template <typename T>
-__global__ __launch_bounds__(FL_NT) void k_adjoint_one(typename CT<T>::c* __restrict__ psi,
-                                                       typename CT<T>::c* __restrict__ lam, const T* __restrict__ gates,
-                                                       int L, fl_adj_words pd, double* __restrict__ Mpart) {
-    typedef typename CT<T>::c cplx;
-    constexpr int NW = FL_NT / 64;
-    __shared__ cplx lp[1 << FL_KMAX_ONE];
-    __shared__ cplx ll[1 << FL_KMAX_ONE];
-    __shared__ __attribute__((aligned(16))) T lg[FL_KMAX_ONE * 32];
-    __shared__ double wacc[NW][FL_MAX_SLOTS][16];
-    __shared__ uint32_t meta[FL_SWEEP_WORDS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) {
-        lp[fl_swz(j)] = psi[j];
-        ll[fl_swz(j)] = lam[j];
+__device__ __forceinline__ T fold32(T a, T b) {
+    if constexpr (sizeof(T) == 4) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+        const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+        const auto rl = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto rh = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+        return __longlong_as_double((long long)(((uint64_t)rh[0] << 32) | rl[0])) +
+               __longlong_as_double((long long)(((uint64_t)rh[1] << 32) | rl[1]));
     }
-    for (int t = threadIdx.x; t < (L - 1) * 32; t += FL_NT) lg[t] = gates[t];
-    for (int t = threadIdx.x; t < pd.nwords; t += FL_NT) meta[t] = pd.w[t];
-    for (int t = threadIdx.x; t < NW * FL_MAX_SLOTS * 16; t += FL_NT) (&wacc[0][0][0])[t] = 0.0;
-    __syncthreads();
-    const bool active = threadIdx.x < (1u << (L - 2));
-    int pos = pd.ngroups;
-    for (int g = 0; g < pd.ngroups; ++g) {
-        const uint32_t head = __builtin_amdgcn_readfirstlane(meta[g]);
-        const int u0 = head & 255, nops = head >> 8;
-        const uint32_t b0 = fl_spread(active ? threadIdx.x : 0u, u0, 2);
+}
+
+// The reverse pass's quad chain: as quad_chain with two threads per quad, on
+// both states, the overlap terms of the op's slot taken before its gate.  The
+// thread with rot = 0 (lower half of the wave) and the one with rot = 2 (upper
+// half) run the same instructions on the quad as they hold it, v_m = amplitude
+// (m + rot) & 3: the terms of D_00, D_11, D_01, D_12 become those of D_22,
+// D_33, D_23 and D_30 = -conj(D_03), and each has one half of D_02 and D_13
+// (the other half with the amplitudes exchanged, real parts negated).  So the
+// first of the wave sum's steps is done for 12 of the 16 values.  The quads'
+// reads and the next gate's stand first, the wave sum after the write-back.
+// meta: first bits, then slot << 8 | gate << 16.  A serial chain like the
+// sweep's.  fl_grad over 50 periods, against one thread per quad with the gate
+// read behind the sums (us): complex64 L = 12 657 / 812, 14 794 / 977, 17 1054 /
+// 1280, 18 1228 / 1463; complex128 L = 14 882 / 1058, 18 1608 / 1694.
+template <typename T>
+__device__ __forceinline__ void adj_quad_chain(typename CT<T>::c* lp, typename CT<T>::c* ll, const T* lg,
+                                               const uint32_t* meta, int nops, double (*acc)[16],
+                                               const fl_quad_lane<2>& me, bool active) {
+    typedef typename CT<T>::c cplx;
+    char* const pb = reinterpret_cast<char*>(lp);
+    char* const lb = reinterpret_cast<char*>(ll);
+    const int lane = threadIdx.x & 63;
+    const T sg = me.rot ? T(-1) : T(1);
+    // after the sum lane l holds value (l >> 2) & 7 of its half's list
+    const int vi8 = (lane >> 2) & 7;
+    const int at = me.rot ? (vi8 < 2 ? vi8 + 2 : vi8 < 4 ? vi8 + 12 : vi8 < 6 ? vi8 + 4 : vi8 + 6)
+                          : (vi8 < 2 ? vi8 : vi8 < 4 ? vi8 + 2 : vi8 < 6 ? vi8 + 6 : vi8);
+    const bool adds = (lane & 3) == 0;
+    auto uni = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane(x); };
+    if (nops == 0) return;
+    T ga[16], gb[16];
+    uint32_t u = uni(meta[0]), w = uni(meta[nops]), la[4];
+    load_gate_rows<T, 2>(me, lg + 32 * (w >> 16), ga);
+    quad_addr<T, 2>(me, u, la);
+    const int k1 = nops > 1 ? 1 : 0;
+    uint32_t un = uni(meta[k1]), wn = uni(meta[nops + k1]);
+    auto step = [&](int q, const T (&g)[16], T (&gn)[16]) {
         T pr[4], pi[4], lr[4], li[4];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
-            const uint32_t o = fl_swz(b0 | ((uint32_t)m << u0));
-            cplx a = lp[o], b = ll[o];
-            if (!active) a.x = a.y = b.x = b.y = 0;   // no part in the sums
-            pr[m] = a.x;
-            pi[m] = a.y;
-            lr[m] = b.x;
-            li[m] = b.y;
+            pr[m] = pi[m] = lr[m] = li[m] = 0;   // an idle thread has no part in the sums
+            if (active) {
+                const cplx a = *reinterpret_cast<const cplx*>(pb + la[m]), b = *reinterpret_cast<const cplx*>(lb + la[m]);
+                pr[m] = a.x;
+                pi[m] = a.y;
+                lr[m] = b.x;
+                li[m] = b.y;
+            }
         }
-        for (int q = 0; q < nops; ++q) {
-            const uint32_t w = __builtin_amdgcn_readfirstlane(meta[pos + q]);
-            adj_op<T, 2>(pr, pi, lr, li, 0, lg + 32 * (w >> 16), wacc[wave][(w >> 8) & 255], lane, [] {});
-        }
-        pos += nops;
+        __builtin_amdgcn_sched_barrier(0);   // the quads' reads lead the LDS queue
+        uint32_t ln[4];
+        quad_addr<T, 2>(me, un, ln);
+        load_gate_rows<T, 2>(me, lg + 32 * (wn >> 16), gn);
+        const int k = q + 2 < nops ? q + 2 : nops - 1;
+        const uint32_t u2 = meta[k], w2 = meta[nops + k];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) __asm__ volatile("" : "+v"(ln[m]));
+        __builtin_amdgcn_sched_barrier(0);
+        // first halves of conj(lambda_x) psi_y - conj(psi_x) lambda_y, then the second
+        auto half = [&](int x, int y, T& re, T& im) {
+            re = fma(lr[x], pr[y], li[x] * pi[y]);
+            im = fma(lr[x], pi[y], -li[x] * pr[y]);
+        };
+        auto whole = [&](int x, int y, T& re, T& im) {
+            half(x, y, re, im);
+            re = fma(-pr[x], lr[y], re);
+            re = fma(-pi[x], li[y], re);
+            im = fma(-pr[x], li[y], im);
+            im = fma(pi[x], lr[y], im);
+        };
+        T v[8], r02, i02, r13, i13;
+        v[0] = fma(lr[0], pi[0], -li[0] * pr[0]);
+        v[1] = fma(lr[1], pi[1], -li[1] * pr[1]);
+        whole(0, 1, v[2], v[3]);
+        whole(1, 2, v[4], v[5]);
+        half(0, 2, r02, i02);
+        half(1, 3, r13, i13);
+        v[4] *= sg;
+        apply_rows<T, 2>(pr, pi, g);
+        apply_rows<T, 2>(lr, li, g);
         if (active) {
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const uint32_t o = fl_swz(b0 | ((uint32_t)m << u0));
+            for (int m = 0; m < 2; ++m) {
                 cplx a, b;
                 a.x = pr[m];
                 a.y = pi[m];
                 b.x = lr[m];
                 b.y = li[m];
-                lp[o] = a;
-                ll[o] = b;
+                *reinterpret_cast<cplx*>(pb + la[m]) = a;
+                *reinterpret_cast<cplx*>(lb + la[m]) = b;
             }
         }
+        v[6] = fold32<T>(r02 * sg, r13 * sg);
+        v[7] = fold32<T>(i02, i13);
+        T r;
+        if constexpr (sizeof(T) == 4) tr_steps_f32<8, 16>(v, lane);
+        else tr_steps_f64<8, 16>(v, lane);
+        r = v[0];
+        __hip_atomic_fetch_add(&acc[(w >> 8) & 255][at], adds ? (double)r : 0.0, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) la[m] = ln[m];
+        w = wn;
+        un = uni(u2);
+        wn = uni(w2);
         __syncthreads();
+    };
+    for (int q = 0; q < nops; q += 2) {
+        step(q, ga, gb);
+        if (q + 1 < nops) step(q + 1, gb, ga);
     }
-    for (uint32_t j = threadIdx.x; j < (1u << L); j += FL_NT) {
-        psi[j] = lp[fl_swz(j)];
-        lam[j] = ll[fl_swz(j)];
-    }
-    for (int t = threadIdx.x; t < pd.nslots * 16; t += FL_NT) {
+}
+
+// The workgroup's sums of every slot, added to its row of Mpart.
+template <int NT>
+__device__ __forceinline__ void adj_flush(const double (*wacc)[FL_MAX_SLOTS][16], const fl_adj_words& pd, double* row) {
+    for (int t = threadIdx.x; t < pd.nslots * 16; t += NT) {
         const int sl = t >> 4, v = t & 15;
         double s = 0.0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) s += wacc[w][sl][v];
-        Mpart[(size_t)pd.sbond[sl] * 16 + v] += s;
+        for (int w = 0; w < NT / 64; ++w) s += wacc[w][sl][v];
+        row[(size_t)pd.sbond[sl] * 16 + v] += s;
     }
+}
+
+// Chains of at most FL_KMAX_ONE sites: one workgroup, as k_sweep_one.
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void k_adjoint_one(typename CT<T>::c* __restrict__ psi,
+                                                    typename CT<T>::c* __restrict__ lam, const T* __restrict__ gates,
+                                                    int L, fl_adj_words pd, double* __restrict__ Mpart) {
+    typedef typename CT<T>::c cplx;
+    constexpr int NW = NT / 64;
+    __shared__ __attribute__((aligned(16))) cplx lp[1 << FL_KMAX_ONE];
+    __shared__ __attribute__((aligned(16))) cplx ll[1 << FL_KMAX_ONE];
+    __shared__ __attribute__((aligned(16))) T lg[FL_KMAX_ONE * 32];
+    __shared__ double wacc[NW][FL_MAX_SLOTS][16];
+    __shared__ uint32_t meta[FL_SWEEP_WORDS];
+    for (uint32_t j = threadIdx.x; j < (1u << L); j += NT) {
+        lp[fl_swz(j)] = psi[j];
+        ll[fl_swz(j)] = lam[j];
+    }
+    for (int t = threadIdx.x; t < (L - 1) * 32; t += NT) lg[t] = gates[t];
+    for (int t = threadIdx.x; t < pd.nwords; t += NT) meta[t] = pd.w[t];
+    for (int t = threadIdx.x; t < NW * FL_MAX_SLOTS * 16; t += NT) (&wacc[0][0][0])[t] = 0.0;
+    __syncthreads();
+    const fl_quad_lane<2> me;
+    adj_quad_chain<T>(lp, ll, lg, meta, pd.ngroups, wacc[threadIdx.x >> 6], me, me.quad < (1u << (L - 2)));
+    for (uint32_t j = threadIdx.x; j < (1u << L); j += NT) {
+        psi[j] = lp[fl_swz(j)];
+        lam[j] = ll[fl_swz(j)];
+    }
+    adj_flush<NT>(wacc, pd, Mpart);
+}
+
+// Tiles of 2^KT amplitudes (KT <= 11) of both states, one per workgroup, as
+// k_sweep_quads.
+template <typename T, int KT, int CL>
+__global__ __launch_bounds__(2 << (KT - 2)) void k_adjoint_quads(typename CT<T>::c* __restrict__ psi,
+                                                                typename CT<T>::c* __restrict__ lam,
+                                                                const T* __restrict__ gates, int W, fl_adj_words pd,
+                                                                double* __restrict__ Mpart, int nbonds) {
+    typedef typename CT<T>::c cplx;
+    constexpr int K = KT, C = CL, NT = 2 << (K - 2), NW = NT / 64;
+    constexpr int APL = sizeof(T) == 4 ? 2 : 1;   // amplitudes per 16 bytes
+    constexpr int ITER = (1 << K) / (APL * NT);
+    static_assert(ITER >= 1, "a whole access per thread");
+    static_assert((APL * NT) % (1 << C) == 0, "tile access stride");
+    typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
+    __shared__ __attribute__((aligned(16))) cplx lp[1 << K];
+    __shared__ __attribute__((aligned(16))) cplx ll[1 << K];
+    __shared__ __attribute__((aligned(16))) T lg[FL_MAX_GATE_TABLE * 32];
+    __shared__ double wacc[NW][FL_MAX_SLOTS][16];
+    __shared__ uint32_t meta[FL_SWEEP_WORDS];
+    const uint64_t at = fl_tile_base(blockIdx.x, C, W, pd.h) + fl_tile_offset(APL * threadIdx.x, C, pd.h);
+    const uint64_t tstride = (uint64_t)((APL * NT) >> C) << pd.h;
+    const uint32_t l0 = fl_swz(APL * threadIdx.x);
+    v16 a[ITER], b[ITER];
+#pragma unroll
+    for (int s = 0; s < ITER; ++s) {
+        a[s] = *reinterpret_cast<const v16*>(psi + at + s * tstride);
+        b[s] = *reinterpret_cast<const v16*>(lam + at + s * tstride);
+    }
+    const fl_f32x4* gsrc = reinterpret_cast<const fl_f32x4*>(gates);
+    for (int t = threadIdx.x; t < nbonds * (int)(32 * sizeof(T) / 16); t += NT) reinterpret_cast<fl_f32x4*>(lg)[t] = gsrc[t];
+    for (int t = threadIdx.x; t < pd.nwords; t += NT) meta[t] = pd.w[t];
+    for (int t = threadIdx.x; t < NW * FL_MAX_SLOTS * 16; t += NT) (&wacc[0][0][0])[t] = 0.0;
+#pragma unroll
+    for (int s = 0; s < ITER; ++s) {
+        const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
+        if constexpr (sizeof(T) == 4) {
+            lp[l] = make_float2(a[s][0], a[s][1]);
+            lp[l ^ 1] = make_float2(a[s][2], a[s][3]);
+            ll[l] = make_float2(b[s][0], b[s][1]);
+            ll[l ^ 1] = make_float2(b[s][2], b[s][3]);
+        } else {
+            lp[l] = make_double2(a[s][0], a[s][1]);
+            ll[l] = make_double2(b[s][0], b[s][1]);
+        }
+    }
+    __syncthreads();
+    adj_quad_chain<T>(lp, ll, lg, meta, pd.ngroups, wacc[threadIdx.x >> 6], fl_quad_lane<2>(), true);
+#pragma unroll
+    for (int s = 0; s < ITER; ++s) {
+        const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
+        v16 x, y;
+        if constexpr (sizeof(T) == 4) {
+            const float2 p0 = lp[l], p1 = lp[l ^ 1], q0 = ll[l], q1 = ll[l ^ 1];
+            x = v16{p0.x, p0.y, p1.x, p1.y};
+            y = v16{q0.x, q0.y, q1.x, q1.y};
+        } else {
+            const double2 p0 = lp[l], q0 = ll[l];
+            x = v16{p0.x, p0.y};
+            y = v16{q0.x, q0.y};
+        }
+        *reinterpret_cast<v16*>(psi + at + s * tstride) = x;
+        *reinterpret_cast<v16*>(lam + at + s * tstride) = y;
+    }
+    adj_flush<NT>(wacc, pd, Mpart + (size_t)blockIdx.x * nbonds * 16);
 }
 
 // Tiles of both states, persistent workgroups (the sums stay in LDS from tile
@@ -2850,6 +3020,44 @@ static bool adj_words(const fl_pass& pd, int gofs, fl_adj_words& w) {
     return true;
 }
 
+// The words form with one op per group, as quad_words.
+static bool adj_quad_words(const fl_pass& pd, int gofs, fl_adj_words& w) {
+    if (!adj_words(pd, gofs, w)) return false;
+    int n = 0;
+    for (int g = 0; g < pd.ngroups; ++g) n += pd.nops[g];
+    if (2 * n > FL_SWEEP_WORDS) return false;
+    int k = 0;
+    for (int g = 0; g < pd.ngroups; ++g)
+        for (int q = 0; q < pd.nops[g]; ++q, ++k) {
+            w.w[k] = (uint32_t)pd.u0[g];
+            w.w[n + k] = (uint32_t)pd.ops[g][q] << 8 | (uint32_t)(pd.opg[g][q] - gofs) << 16;
+        }
+    w.ngroups = n;
+    w.nwords = 2 * n;
+    return true;
+}
+
+template <typename T, int K, int C>
+static hipError_t launch_adj_quads(const fl_geom& g, void* psi, void* lam, const void* gates, const fl_pass& pd,
+                                   double* Mpart, int grid, hipStream_t s) {
+    typedef typename CT<T>::c cplx;
+    const int nb = g.L - 1;
+    fl_adj_words w;
+    if ((uint32_t)grid != ntiles_of(g) || !adj_quad_words(pd, nb, w)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_adjoint_quads<T, K, C>), dim3(grid), dim3(2 << (K - 2)), 0, s, (cplx*)psi, (cplx*)lam,
+                       (const T*)gates + 32 * nb, g.W, w, Mpart, nb);
+    return hipGetLastError();
+}
+
+template <typename T, int NT>
+static hipError_t launch_adj_one(int L, void* psi, void* lam, const void* gates, const fl_adj_words& w, double* Mpart,
+                                 hipStream_t s) {
+    typedef typename CT<T>::c cplx;
+    hipLaunchKernelGGL((k_adjoint_one<T, NT>), dim3(1), dim3(NT), 0, s, (cplx*)psi, (cplx*)lam,
+                       (const T*)gates + 32 * (L - 1), L, w, Mpart);
+    return hipGetLastError();
+}
+
 template <typename T, int R, int K, int C, int WPE, typename D>
 static hipError_t launch_adj_tiles(const fl_geom& g, void* psi, void* lam, const void* gates, const fl_pass& pd,
                                    double* Mpart, int grid, hipStream_t s) {
@@ -2881,27 +3089,27 @@ hipError_t launch_adjoint(int dtype, const fl_geom& g, void* psi, void* lam, con
     }
     if (g.W == 0) {
         fl_adj_words w;
-        if (g.L < 2 || g.L > FL_KMAX_ONE || g.R != 2 || !adj_words(pd, nb, w)) return hipErrorInvalidValue;
+        if (g.L < 2 || g.L > FL_KMAX_ONE || g.R != 2 || !adj_quad_words(pd, nb, w)) return hipErrorInvalidValue;
         if (dtype == 0)
-            hipLaunchKernelGGL(k_adjoint_one<float>, dim3(1), dim3(FL_NT), 0, s, (float2*)psi, (float2*)lam,
-                               (const float*)gates + 32 * nb, g.L, w, Mpart);
-        else
-            hipLaunchKernelGGL(k_adjoint_one<double>, dim3(1), dim3(FL_NT), 0, s, (double2*)psi, (double2*)lam,
-                               (const double*)gates + 32 * nb, g.L, w, Mpart);
-        return hipGetLastError();
+            return g.L <= 7   ? launch_adj_one<float, 64>(g.L, psi, lam, gates, w, Mpart, s)
+                   : g.L <= 9 ? launch_adj_one<float, 256>(g.L, psi, lam, gates, w, Mpart, s)
+                              : launch_adj_one<float, 512>(g.L, psi, lam, gates, w, Mpart, s);
+        return g.L <= 7   ? launch_adj_one<double, 64>(g.L, psi, lam, gates, w, Mpart, s)
+               : g.L <= 9 ? launch_adj_one<double, 256>(g.L, psi, lam, gates, w, Mpart, s)
+                          : launch_adj_one<double, 512>(g.L, psi, lam, gates, w, Mpart, s);
     }
     // the geometries of adjoint_geom
     const int key = (dtype << 12) | (g.K << 8) | (g.C << 4) | g.R;
     auto code = [](int dt, int K, int C, int R) { return (dt << 12) | (K << 8) | (C << 4) | R; };
     if (key == code(0, 12, 4, 4)) return launch_adj_tiles<float, 4, 12, 4, 2, fl_pass>(g, psi, lam, gates, pd, Mpart, grid, s);
     if (key == code(0, 12, 4, 3)) return launch_adj_tiles<float, 3, 12, 4, 2, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
-    if (key == code(0, 11, 3, 3)) return launch_adj_tiles<float, 3, 11, 3, 2, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
-    if (key == code(0, 10, 3, 2)) return launch_adj_tiles<float, 2, 10, 3, 4, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
-    if (key == code(0, 9, 3, 2)) return launch_adj_tiles<float, 2, 9, 3, 4, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(0, 11, 3, 2)) return launch_adj_quads<float, 11, 3>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(0, 10, 3, 2)) return launch_adj_quads<float, 10, 3>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(0, 9, 3, 2)) return launch_adj_quads<float, 9, 3>(g, psi, lam, gates, pd, Mpart, grid, s);
     if (key == code(1, 12, 4, 4)) return launch_adj_tiles<double, 4, 12, 4, 1, fl_pass>(g, psi, lam, gates, pd, Mpart, grid, s);
     if (key == code(1, 11, 3, 3)) return launch_adj_tiles<double, 3, 11, 3, 1, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
-    if (key == code(1, 10, 3, 2)) return launch_adj_tiles<double, 2, 10, 3, 2, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
-    if (key == code(1, 9, 3, 2)) return launch_adj_tiles<double, 2, 9, 3, 2, fl_adj_words>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(1, 10, 3, 2)) return launch_adj_quads<double, 10, 3>(g, psi, lam, gates, pd, Mpart, grid, s);
+    if (key == code(1, 9, 3, 2)) return launch_adj_quads<double, 9, 3>(g, psi, lam, gates, pd, Mpart, grid, s);
     return hipErrorInvalidValue;
 }
 

@@ -152,3 +152,12 @@ def test_gradient_at_the_edges_of_its_tile_sizes(dtype, L, n, K):
     g = fl.fl_grad(ctx, psi, ck, n, K, gens, torch.empty_like(psi))
     ulp = 6e-8 if dtype == "c64" else 1.2e-16
     assert np.max(np.abs(g - ref)) < 2 * n * (L - 1) * ulp * 4 * (L - 1)
+
+
+# the reverse pass in one workgroup of one wave, of four with idle lanes and
+# with none; tiles between the chains above
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("L,n,K", [(2, 5, 0), (4, 3, 0), (7, 18, 0), (8, 4, 2), (9, 18, 9), (12, 17, 0), (14, 4, 2)])
+def test_gradient_with_two_threads_per_quad(dtype, L, n, K):
+    """As test_gradient_at_the_edges_of_its_tile_sizes, with its tolerance."""
+    test_gradient_at_the_edges_of_its_tile_sizes(dtype, L, n, K)
