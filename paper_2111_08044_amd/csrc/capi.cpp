@@ -46,6 +46,7 @@ int fail_hip(hipError_t e, const char* what) {
     } while (0)
 
 constexpr int kPlanBlock = 16;        // periods per planned block
+constexpr int kPeriodsPerLaunch = 256;  // periods of one launch of a one-workgroup chain: below 1 ms
 constexpr int kMaxGatesPerPass = 96;  // cap on gates the planner puts in one pass
 constexpr int kReduceGrid = 2048;     // most workgroups of the reduction kernels (rows of the partials)
 constexpr int kRdmGrid = 512;          // workgroups of the bond reductions: two per CU, persistent
@@ -560,16 +561,30 @@ int run_dense(fl_ctx* c, void* psi, int64_t n, bool dagger) {
     return FL_OK;
 }
 
+// Chains of one workgroup: a period's gates (9 at most) are one pass, which a
+// launch repeats with the state kept in LDS.  The plan of 16 periods took up to
+// four launches of up to 40 gates, each with the state's way in and out.
+// Before and after (us): 16 periods at L = 4 14.0 / 12.2, 8 36.0 / 31.6, 10 54.1 /
+// 48.2, complex128 71.8 / 65.8; 100 periods at L = 8 225 / 185, 10 338 / 289.
+bool one_workgroup(const fl_ctx* c) { return c->L <= FL_KMAX_ONE; }
+
 int run_periods(fl_ctx* c, void* psi, int64_t n, bool dagger) {
     if (is_dense(c)) return run_dense(c, psi, n, dagger);
     const int64_t q = n / kPlanBlock, r = n % kPlanBlock;
-    auto go = [&](const fl_ctx::SweepPlan& plan) -> int {
+    auto go = [&](const fl_ctx::SweepPlan& plan, int reps = 1) -> int {
         for (const fl_pass& p : plan.passes) {
-            hipError_t e = fl::launch_sweep(c->dtype, plan.g, psi, c->d_gates, p, c->stream);
+            hipError_t e = fl::launch_sweep(c->dtype, plan.g, psi, c->d_gates, p, reps, c->stream);
             if (e != hipSuccess) return fail_hip(e, "sweep kernel launch");
         }
         return FL_OK;
     };
+    if (one_workgroup(c)) {
+        for (int64_t k = 0; k < n; k += kPeriodsPerLaunch) {
+            int rc = go(get_plan(c, 1, n, dagger), (int)std::min<int64_t>(n - k, kPeriodsPerLaunch));
+            if (rc) return rc;
+        }
+        return FL_OK;
+    }
     for (int64_t i = 0; i < q; ++i) {
         int rc = go(get_plan(c, kPlanBlock, n, dagger));
         if (rc) return rc;
@@ -581,14 +596,21 @@ int run_periods(fl_ctx* c, void* psi, int64_t n, bool dagger) {
 int run_reverse(fl_ctx* c, void* psi, void* lam, int64_t n) {
     const int grid = (int)std::min<uint32_t>(ntiles(c->geom_adj), kAdjGrid);
     const int64_t q = n / kPlanBlock, r = n % kPlanBlock;
-    auto go = [&](const std::vector<fl_pass>& plan) -> int {
+    auto go = [&](const std::vector<fl_pass>& plan, int reps = 1) -> int {
         for (const fl_pass& p : plan) {
-            hipError_t e = fl::launch_adjoint(c->dtype, c->geom_adj, psi, lam, c->d_gates, p, c->d_mpart, grid,
+            hipError_t e = fl::launch_adjoint(c->dtype, c->geom_adj, psi, lam, c->d_gates, p, reps, c->d_mpart, grid,
                                               c->stream);
             if (e != hipSuccess) return fail_hip(e, "k_adjoint launch");
         }
         return FL_OK;
     };
+    if (one_workgroup(c)) {
+        for (int64_t k = 0; k < n; k += kPeriodsPerLaunch) {
+            int rc = go(get_adj_plan(c, 1), (int)std::min<int64_t>(n - k, kPeriodsPerLaunch));
+            if (rc) return rc;
+        }
+        return FL_OK;
+    }
     for (int64_t i = 0; i < q; ++i) {
         int rc = go(get_adj_plan(c, kPlanBlock));
         if (rc) return rc;

@@ -7,7 +7,10 @@
 
 namespace fl {
 
-hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, hipStream_t s);
+// pd's gates; chains in one workgroup (g.W = 0) apply them reps times in one
+// launch, others take reps = 1 (also launch_adjoint)
+hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int reps,
+                        hipStream_t s);
 // single-tile chains shorter than a full tile
 hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,
                       int nslot, hipStream_t s);
@@ -43,7 +46,7 @@ struct apply_h_desc {
 hipError_t launch_apply_h_tiles(int dtype, const fl_geom& g, const void* psi, void* lam, const void* tab,
                                 const apply_h_desc& pd, double* dots, int grid, hipStream_t s);
 hipError_t launch_adjoint(int dtype, const fl_geom& g, void* psi, void* lam, const void* gates, const fl_pass& pd,
-                          double* Mpart, int grid, hipStream_t s);
+                          int reps, double* Mpart, int grid, hipStream_t s);
 // reverse pass of the 4-qubit-window form (complex64, full 13-bit tiles) on
 // the matrix cores: mats = the pass's window fragments (4 KiB per group, the
 // transposes of the forward's), Qpart [grid][FL_WIN4_MAX_GROUPS][512]

@@ -331,11 +331,11 @@ __device__ __forceinline__ void load_gate_rows(const fl_quad_lane<S>& me, const 
 // run, and between two barriers a thread only reads its quad, applies 64 / S
 // FMAs and writes its outputs back.  Each thread holds the quad and its gate
 // rows rotated, so that its first output stands first; the sums do not depend
-// on S.  About 0.33 us a gate (0.39 with one thread per quad, of which 0.13 are
+// on S.  The nops gates run over and over, total gates in all.  About 0.33 us a gate (0.39 with one thread per quad, of which 0.13 are
 // the 64 FMAs of a wave alone on its SIMD).  meta holds a pass in words form with one op per group: first bits,
 // then gates << 8.
 template <typename T, int S>
-__device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, const uint32_t* meta, int nops,
+__device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, const uint32_t* meta, int nops, int total,
                                            const fl_quad_lane<S>& me, bool active) {
     typedef typename CT<T>::c cplx;
     constexpr int NO = 4 / S;
@@ -350,9 +350,11 @@ __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, 
     uint32_t w = word(0), la[4];
     load_gate_rows<T, S>(me, lg + 32 * (w >> 16), ga);
     quad_addr<T, S>(me, w & 255, la);
-    uint32_t wn = word(nops > 1 ? 1 : 0);
+    auto after = [&](int k) { return k + 1 < nops ? k + 1 : 0; };
+    int kn = after(0);   // the gate after the current one
+    uint32_t wn = word(kn);
     // one gate with its entries in g; the next one's go to gn
-    auto step = [&](int q, const T (&g)[8 * NO], T (&gn)[8 * NO]) {
+    auto step = [&](const T (&g)[8 * NO], T (&gn)[8 * NO]) {
         T vr[4], vi[4];
         if (active) {
 #pragma unroll
@@ -367,8 +369,8 @@ __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, 
         uint32_t ln[4];
         quad_addr<T, S>(me, wn & 255, ln);
         load_gate_rows<T, S>(me, lg + 32 * (wn >> 16), gn);
-        const int k = q + 2 < nops ? q + 2 : nops - 1;
-        const uint32_t h2 = meta[k], o2 = meta[nops + k];
+        kn = after(kn);
+        const uint32_t h2 = meta[kn], o2 = meta[nops + kn];
 #pragma unroll
         for (int m = 0; m < 4; ++m) __asm__ volatile("" : "+v"(ln[m]));
         __builtin_amdgcn_sched_barrier(0);
@@ -387,17 +389,17 @@ __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, 
         wn = (uint32_t)__builtin_amdgcn_readfirstlane(h2 & 255u) | (uint32_t)__builtin_amdgcn_readfirstlane(o2) << 8;
         __syncthreads();
     };
-    for (int q = 0; q < nops; q += 2) {
-        step(q, ga, gb);
-        if (q + 1 < nops) step(q + 1, gb, ga);
+    for (int q = 0; q < total; q += 2) {
+        step(ga, gb);
+        if (q + 1 < total) step(gb, ga);
     }
 }
 
 // Chains of at most FL_KMAX_ONE sites: one workgroup holds the whole state in
-// LDS.
+// LDS for reps runs of the pass.
 template <typename T, int S, int NT>
 __global__ __launch_bounds__(NT) void k_sweep_one(typename CT<T>::c* __restrict__ psi, const T* __restrict__ gates,
-                                                  int L, fl_sweep_words pd) {
+                                                  int L, fl_sweep_words pd, int reps) {
     typedef typename CT<T>::c cplx;
     __shared__ __attribute__((aligned(16))) T lg[FL_KMAX_ONE * 32];
     __shared__ uint32_t meta[FL_SWEEP_WORDS];
@@ -407,7 +409,7 @@ __global__ __launch_bounds__(NT) void k_sweep_one(typename CT<T>::c* __restrict_
     for (int t = threadIdx.x; t < pd.nwords; t += NT) meta[t] = pd.w[t];
     __syncthreads();
     const fl_quad_lane<S> me;
-    quad_chain<T, S>(lds, lg, meta, pd.ngroups, me, me.quad < (1u << (L - 2)));
+    quad_chain<T, S>(lds, lg, meta, pd.ngroups, pd.ngroups * reps, me, me.quad < (1u << (L - 2)));
     for (uint32_t j = threadIdx.x; j < (1u << L); j += NT) psi[j] = lds[fl_swz(j)];
 }
 
@@ -451,7 +453,7 @@ __global__ __launch_bounds__(S << (KT - 2)) void k_sweep_quads(typename CT<T>::c
         }
     }
     __syncthreads();
-    quad_chain<T, S>(lds, lg, meta, pd.ngroups, fl_quad_lane<S>(), true);
+    quad_chain<T, S>(lds, lg, meta, pd.ngroups, pd.ngroups, fl_quad_lane<S>(), true);
 #pragma unroll
     for (int s = 0; s < ITER; ++s) {
         const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
@@ -1672,7 +1674,7 @@ __device__ __forceinline__ T fold32(T a, T b) {
 // 1280, 18 1228 / 1463; complex128 L = 14 882 / 1058, 18 1608 / 1694.
 template <typename T>
 __device__ __forceinline__ void adj_quad_chain(typename CT<T>::c* lp, typename CT<T>::c* ll, const T* lg,
-                                               const uint32_t* meta, int nops, double (*acc)[16],
+                                               const uint32_t* meta, int nops, int total, double (*acc)[16],
                                                const fl_quad_lane<2>& me, bool active) {
     typedef typename CT<T>::c cplx;
     char* const pb = reinterpret_cast<char*>(lp);
@@ -1690,9 +1692,10 @@ __device__ __forceinline__ void adj_quad_chain(typename CT<T>::c* lp, typename C
     uint32_t u = uni(meta[0]), w = uni(meta[nops]), la[4];
     load_gate_rows<T, 2>(me, lg + 32 * (w >> 16), ga);
     quad_addr<T, 2>(me, u, la);
-    const int k1 = nops > 1 ? 1 : 0;
-    uint32_t un = uni(meta[k1]), wn = uni(meta[nops + k1]);
-    auto step = [&](int q, const T (&g)[16], T (&gn)[16]) {
+    auto after = [&](int k) { return k + 1 < nops ? k + 1 : 0; };
+    int kn = after(0);
+    uint32_t un = uni(meta[kn]), wn = uni(meta[nops + kn]);
+    auto step = [&](const T (&g)[16], T (&gn)[16]) {
         T pr[4], pi[4], lr[4], li[4];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
@@ -1709,8 +1712,8 @@ __device__ __forceinline__ void adj_quad_chain(typename CT<T>::c* lp, typename C
         uint32_t ln[4];
         quad_addr<T, 2>(me, un, ln);
         load_gate_rows<T, 2>(me, lg + 32 * (wn >> 16), gn);
-        const int k = q + 2 < nops ? q + 2 : nops - 1;
-        const uint32_t u2 = meta[k], w2 = meta[nops + k];
+        kn = after(kn);
+        const uint32_t u2 = meta[kn], w2 = meta[nops + kn];
 #pragma unroll
         for (int m = 0; m < 4; ++m) __asm__ volatile("" : "+v"(ln[m]));
         __builtin_amdgcn_sched_barrier(0);
@@ -1763,9 +1766,9 @@ __device__ __forceinline__ void adj_quad_chain(typename CT<T>::c* lp, typename C
         wn = uni(w2);
         __syncthreads();
     };
-    for (int q = 0; q < nops; q += 2) {
-        step(q, ga, gb);
-        if (q + 1 < nops) step(q + 1, gb, ga);
+    for (int q = 0; q < total; q += 2) {
+        step(ga, gb);
+        if (q + 1 < total) step(gb, ga);
     }
 }
 
@@ -1785,7 +1788,7 @@ __device__ __forceinline__ void adj_flush(const double (*wacc)[FL_MAX_SLOTS][16]
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void k_adjoint_one(typename CT<T>::c* __restrict__ psi,
                                                     typename CT<T>::c* __restrict__ lam, const T* __restrict__ gates,
-                                                    int L, fl_adj_words pd, double* __restrict__ Mpart) {
+                                                    int L, fl_adj_words pd, int reps, double* __restrict__ Mpart) {
     typedef typename CT<T>::c cplx;
     constexpr int NW = NT / 64;
     __shared__ __attribute__((aligned(16))) cplx lp[1 << FL_KMAX_ONE];
@@ -1802,7 +1805,8 @@ __global__ __launch_bounds__(NT) void k_adjoint_one(typename CT<T>::c* __restric
     for (int t = threadIdx.x; t < NW * FL_MAX_SLOTS * 16; t += NT) (&wacc[0][0][0])[t] = 0.0;
     __syncthreads();
     const fl_quad_lane<2> me;
-    adj_quad_chain<T>(lp, ll, lg, meta, pd.ngroups, wacc[threadIdx.x >> 6], me, me.quad < (1u << (L - 2)));
+    adj_quad_chain<T>(lp, ll, lg, meta, pd.ngroups, pd.ngroups * reps, wacc[threadIdx.x >> 6], me,
+                      me.quad < (1u << (L - 2)));
     for (uint32_t j = threadIdx.x; j < (1u << L); j += NT) {
         psi[j] = lp[fl_swz(j)];
         lam[j] = ll[fl_swz(j)];
@@ -1856,7 +1860,7 @@ __global__ __launch_bounds__(2 << (KT - 2)) void k_adjoint_quads(typename CT<T>:
         }
     }
     __syncthreads();
-    adj_quad_chain<T>(lp, ll, lg, meta, pd.ngroups, wacc[threadIdx.x >> 6], fl_quad_lane<2>(), true);
+    adj_quad_chain<T>(lp, ll, lg, meta, pd.ngroups, pd.ngroups, wacc[threadIdx.x >> 6], fl_quad_lane<2>(), true);
 #pragma unroll
     for (int s = 0; s < ITER; ++s) {
         const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
@@ -2819,30 +2823,34 @@ static hipError_t launch_quads(const fl_geom& g, void* psi, const void* gates, c
 }
 
 template <typename T, int S, int NT>
-static hipError_t launch_one_s(int L, void* psi, const void* gates, const fl_sweep_words& w, int gofs, hipStream_t s) {
+static hipError_t launch_one_s(int L, void* psi, const void* gates, const fl_sweep_words& w, int gofs, int reps,
+                               hipStream_t s) {
     typedef typename CT<T>::c cplx;
-    hipLaunchKernelGGL((k_sweep_one<T, S, NT>), dim3(1), dim3(NT), 0, s, (cplx*)psi, (const T*)gates + 32 * gofs, L, w);
+    hipLaunchKernelGGL((k_sweep_one<T, S, NT>), dim3(1), dim3(NT), 0, s, (cplx*)psi, (const T*)gates + 32 * gofs, L, w,
+                       reps);
     return hipGetLastError();
 }
 
 // Threads per quad: as many as give every SIMD a wave (L = 8: 64 quads in four
 // waves instead of one), two at most where the quads alone do; up to L = 6 one
 // wave holds all and no barrier waits for another.  16 periods, with one thread
-// per quad in 256-thread workgroups before (us): complex64 L = 4 20.1 -> 14.0,
-// 8 44.0 -> 36.2, 9 54.3 -> 42.5, 10 62.9 -> 54.3; complex128 L = 6 34.8 -> 20.9,
-// 8 50.2 -> 40.0, 10 77.2 -> 72.1.  Four per quad are slower at L = 9 (45.8) and
-// 10 (66.3): each reads the whole quad.  L = 2 has nothing to share.
+// per quad in 256-thread workgroups before, on plans of 16 periods (us):
+// complex64 L = 4 20.1 -> 14.0, 8 44.0 -> 36.2, 9 54.3 -> 42.5, 10 62.9 -> 54.3;
+// complex128 L = 6 34.8 -> 20.9, 8 50.2 -> 40.0, 10 77.2 -> 72.1.  Four per quad
+// are slower at L = 9 (45.8) and 10 (66.3): each reads the whole quad.  L = 2 has nothing to share.
 template <typename T>
-static hipError_t launch_one(int L, void* psi, const void* gates, const fl_sweep_words& w, int gofs, hipStream_t s) {
-    if (L == 2) return launch_one_s<T, 1, 64>(L, psi, gates, w, gofs, s);
-    if (L <= 6) return launch_one_s<T, 4, 64>(L, psi, gates, w, gofs, s);
-    if (L <= 8) return launch_one_s<T, 4, 256>(L, psi, gates, w, gofs, s);
-    if (L == 9) return launch_one_s<T, 2, 256>(L, psi, gates, w, gofs, s);
-    return launch_one_s<T, 2, 512>(L, psi, gates, w, gofs, s);
+static hipError_t launch_one(int L, void* psi, const void* gates, const fl_sweep_words& w, int gofs, int reps,
+                             hipStream_t s) {
+    if (L == 2) return launch_one_s<T, 1, 64>(L, psi, gates, w, gofs, reps, s);
+    if (L <= 6) return launch_one_s<T, 4, 64>(L, psi, gates, w, gofs, reps, s);
+    if (L <= 8) return launch_one_s<T, 4, 256>(L, psi, gates, w, gofs, reps, s);
+    if (L == 9) return launch_one_s<T, 2, 256>(L, psi, gates, w, gofs, reps, s);
+    return launch_one_s<T, 2, 512>(L, psi, gates, w, gofs, reps, s);
 }
 
-hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd,
+hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int reps,
                         hipStream_t s) {
+    if (reps < 1 || (reps > 1 && g.W != 0)) return hipErrorInvalidValue;
     // a pass applies gates of one direction: G_b (table entries 0 .. L-2) or G_b^dagger
     const int nb = g.L - 1;
     if (nb > FL_MAX_GATE_TABLE) return hipErrorInvalidValue;
@@ -2856,7 +2864,8 @@ hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gate
         if (g.L < 2 || g.L > FL_KMAX_ONE || g.R != 2) return hipErrorInvalidValue;
         fl_sweep_words w;
         if (!quad_words(pd, gofs, w)) return hipErrorInvalidValue;
-        return dtype == 0 ? launch_one<float>(g.L, psi, gates, w, gofs, s) : launch_one<double>(g.L, psi, gates, w, gofs, s);
+        return dtype == 0 ? launch_one<float>(g.L, psi, gates, w, gofs, reps, s)
+                          : launch_one<double>(g.L, psi, gates, w, gofs, reps, s);
     }
     // the geometries of sweep_geom
     const int key = (dtype << 12) | (g.K << 8) | (g.C << 4) | g.R;
@@ -3050,11 +3059,11 @@ static hipError_t launch_adj_quads(const fl_geom& g, void* psi, void* lam, const
 }
 
 template <typename T, int NT>
-static hipError_t launch_adj_one(int L, void* psi, void* lam, const void* gates, const fl_adj_words& w, double* Mpart,
-                                 hipStream_t s) {
+static hipError_t launch_adj_one(int L, void* psi, void* lam, const void* gates, const fl_adj_words& w, int reps,
+                                 double* Mpart, hipStream_t s) {
     typedef typename CT<T>::c cplx;
     hipLaunchKernelGGL((k_adjoint_one<T, NT>), dim3(1), dim3(NT), 0, s, (cplx*)psi, (cplx*)lam,
-                       (const T*)gates + 32 * (L - 1), L, w, Mpart);
+                       (const T*)gates + 32 * (L - 1), L, w, reps, Mpart);
     return hipGetLastError();
 }
 
@@ -3078,8 +3087,9 @@ static hipError_t launch_adj_tiles(const fl_geom& g, void* psi, void* lam, const
 }
 
 hipError_t launch_adjoint(int dtype, const fl_geom& g, void* psi, void* lam, const void* gates, const fl_pass& pd,
-                          double* Mpart, int grid, hipStream_t s) {
+                          int reps, double* Mpart, int grid, hipStream_t s) {
     const int nb = g.L - 1;
+    if (reps < 1 || (reps > 1 && g.W != 0)) return hipErrorInvalidValue;
     if (nb > FL_MAX_GATE_TABLE || grid < 1 || pd.nslots > FL_MAX_SLOTS) return hipErrorInvalidValue;
     for (int q = 0; q < pd.ngroups; ++q) {
         if (pd.nops[q] < 1) return hipErrorInvalidValue;
@@ -3091,12 +3101,12 @@ hipError_t launch_adjoint(int dtype, const fl_geom& g, void* psi, void* lam, con
         fl_adj_words w;
         if (g.L < 2 || g.L > FL_KMAX_ONE || g.R != 2 || !adj_quad_words(pd, nb, w)) return hipErrorInvalidValue;
         if (dtype == 0)
-            return g.L <= 7   ? launch_adj_one<float, 64>(g.L, psi, lam, gates, w, Mpart, s)
-                   : g.L <= 9 ? launch_adj_one<float, 256>(g.L, psi, lam, gates, w, Mpart, s)
-                              : launch_adj_one<float, 512>(g.L, psi, lam, gates, w, Mpart, s);
-        return g.L <= 7   ? launch_adj_one<double, 64>(g.L, psi, lam, gates, w, Mpart, s)
-               : g.L <= 9 ? launch_adj_one<double, 256>(g.L, psi, lam, gates, w, Mpart, s)
-                          : launch_adj_one<double, 512>(g.L, psi, lam, gates, w, Mpart, s);
+            return g.L <= 7   ? launch_adj_one<float, 64>(g.L, psi, lam, gates, w, reps, Mpart, s)
+                   : g.L <= 9 ? launch_adj_one<float, 256>(g.L, psi, lam, gates, w, reps, Mpart, s)
+                              : launch_adj_one<float, 512>(g.L, psi, lam, gates, w, reps, Mpart, s);
+        return g.L <= 7   ? launch_adj_one<double, 64>(g.L, psi, lam, gates, w, reps, Mpart, s)
+               : g.L <= 9 ? launch_adj_one<double, 256>(g.L, psi, lam, gates, w, reps, Mpart, s)
+                          : launch_adj_one<double, 512>(g.L, psi, lam, gates, w, reps, Mpart, s);
     }
     // the geometries of adjoint_geom
     const int key = (dtype << 12) | (g.K << 8) | (g.C << 4) | g.R;

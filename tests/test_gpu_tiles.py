@@ -161,3 +161,18 @@ def test_gradient_at_the_edges_of_its_tile_sizes(dtype, L, n, K):
 def test_gradient_with_two_threads_per_quad(dtype, L, n, K):
     """As test_gradient_at_the_edges_of_its_tile_sizes, with its tolerance."""
     test_gradient_at_the_edges_of_its_tile_sizes(dtype, L, n, K)
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("L", [2, 4, 8])
+def test_more_periods_than_one_launch_of_a_short_chain(dtype, L):
+    """300 periods in one workgroup are two launches, of 256 and 44: the sweep
+    against the oracle (tolerance as above), and the gradient's replay back to
+    the initial state, off by the forward's and its own n (L-1) units."""
+    n = 300
+    test_sweep_at_the_edges_of_its_tile_sizes(dtype, L, n, False)
+    ctx, hs, psi, ref = _random_context(L, dtype, 90 + L)
+    fl.fl_apply_period(ctx, psi, n)
+    fl.fl_grad(ctx, psi, [], n, 0, O.xyz_coupling_generators(L), torch.empty_like(psi))
+    ulp = 6e-8 if dtype == "c64" else 1.2e-16
+    assert np.linalg.norm(psi.cpu().numpy() - ref) < 2 * n * (L - 1) * ulp * np.linalg.norm(ref)
