@@ -1,14 +1,16 @@
 // HIP kernels of the Floquet brickwork engine (gfx950, wave64).
 //
-//  k_sweep_tiles / k_sweep
+//  k_sweep_tiles / k_sweep_quads / k_sweep_one
 //             fused gate sweep: one HBM read + write of the state applies
 //             every gate of a pass (Sec. II Eq. (2), fused as in Sec. II).
 //  k_rdm_windows / k_rdm
 //             two-site reduced density matrices of the bonds of a pass (plus
 //             the norm): exact products of the stored amplitudes, FP64 sums
 //             (Sec. II Eq. (1); Sec. IV Eq. (10)).
-//  k_apply_h  lambda = H0 psi, out of place (Sec. IV Eq. (11), Sec. V).
-//  k_adjoint  reverse replay with G^dagger and the overlap terms of the
+//  k_apply_h_tiles / k_apply_h
+//             lambda = H0 psi, out of place (Sec. IV Eq. (11), Sec. V).
+//  k_adjoint_tiles / k_adjoint_quads / k_adjoint_one / k_adjoint_win4
+//             reverse replay with G^dagger and the overlap terms of the
 //             gradient of <H0>.
 //  k_dense6 / k_dense4
 //             pre-multiplied 6-qubit (FP32 or split BF16x3) and 4-qubit (FP32)
