@@ -72,13 +72,15 @@ fl_geom plain_geom(int L, int dtype) {
 //  - L <= 10: one workgroup holds the state, one quad per gate and one, two or
 //    four threads.
 //  - Short chains: tiles of L - 8 bits, so that 256 workgroups, one per CU,
-//    share the work; a pass is then a serial chain of LDS round trips, and
-//    smaller register groups (2 bits up to 10- or, in complex64, 11-bit tiles,
-//    then 3) spread it over more waves.  Tiles below 10 (complex128: 9) bits
-//    need more passes than they save.  16 periods, against full tiles (us):
-//    complex64 L = 14 95 / 201, 17 127 / 257, 18 145 / 275, 19 190 / 297 (223
+//    share the work; a pass is then a serial chain, which more waves shorten:
+//    one amplitude per thread up to 10-bit tiles, quads on 11 bits in
+//    complex64, 3-bit register groups above.  Tiles below 10 (complex128: 9) bits
+//    need more passes than they save (complex64 on 9 bits: ten periods and an
+//    energy at L = 12 in 9 launches instead of 6, 74.5 us against 68; 16 periods
+//    at L = 14 91 / 92, at 18 160 / 140).  16 periods, against full tiles (us):
+//    complex64 L = 14 92 / 201, 17 123 / 257, 18 140 / 275, 19 190 / 297 (223
 //    with 3-bit groups), 20 253 / 342 (273 with 3 low bits: two passes more);
-//    complex128 L = 13 103 / 189, 17 155 / 292, 18 181 / 321, 19 253 / 362.
+//    complex128 L = 13 90 / 189, 17 138 / 292, 18 169 / 321, 19 253 / 362.
 //  - Longer chains: full tiles (complex64 L = 21: 362 on 13 bits, 412 on 12).
 //  - complex128 on 12-bit tiles takes 3 low bits (128-byte runs, a 9-bit
 //    window) for calls of 3 periods and more: 15 passes instead of 27 for 16
@@ -89,8 +91,8 @@ fl_geom sweep_geom(int L, int dtype, int64_t n) {
     if (L <= FL_KMAX_ONE) return fl::make_geom(L, FL_KMAX_ONE, 2, 3);
     const bool c64 = dtype == FL_C64;
     const int k = std::max(L - 8, c64 ? 10 : 9);
-    if (k <= 10 || (k == 11 && c64)) return fl::make_geom(L, k, 2, 3);
-    if (k == 11) return fl::make_geom(L, k, 3, 3);
+    if (k <= 10) return fl::make_geom(L, k, 4, 3);
+    if (k == 11) return fl::make_geom(L, k, c64 ? 2 : 3, 3);
     if (k == 12 && c64) return fl::make_geom(L, k, 3, 4);
     if (!c64 && n >= 3) return fl::make_geom(L, FL_KMAX_C128, 4, 3);
     return plain_geom(L, dtype);

@@ -415,17 +415,14 @@ __global__ __launch_bounds__(NT) void k_sweep_one(typename CT<T>::c* __restrict_
     for (uint32_t j = threadIdx.x; j < (1u << L); j += NT) psi[j] = lds[fl_swz(j)];
 }
 
-// Tiles of 2^KT amplitudes (KT <= 11), one per workgroup, S threads per quad:
-// two on 9- and 10-bit tiles, which then have four and eight waves (16 periods,
-// against one per quad (us): complex64 L = 12 73.1 / 81.8, 17 127 / 139;
-// complex128 L = 12 91.8 / 96.3, 18 181 / 193), one on 11 bits (192.7 with two
-// at L = 19, 190.4 with one: all SIMDs have two waves already).
-template <typename T, int KT, int CL, int S>
-__global__ __launch_bounds__(S << (KT - 2)) void k_sweep_quads(typename CT<T>::c* __restrict__ psi,
+// Tiles of 2^KT amplitudes (KT = 11), one per workgroup: eight waves of one
+// thread per quad (16 periods at L = 19: 190 us, 193 with two per quad).
+template <typename T, int KT, int CL>
+__global__ __launch_bounds__(1 << (KT - 2)) void k_sweep_quads(typename CT<T>::c* __restrict__ psi,
                                                               const T* __restrict__ gates, int W, fl_sweep_words pd,
                                                               int ngates) {
     typedef typename CT<T>::c cplx;
-    constexpr int K = KT, C = CL, NT = S << (K - 2);
+    constexpr int K = KT, C = CL, NT = 1 << (K - 2);
     constexpr int APL = sizeof(T) == 4 ? 2 : 1;   // amplitudes per 16 bytes
     constexpr int ITER = (1 << K) / (APL * NT);
     static_assert(ITER >= 1, "a whole access per thread");
@@ -455,7 +452,7 @@ __global__ __launch_bounds__(S << (KT - 2)) void k_sweep_quads(typename CT<T>::c
         }
     }
     __syncthreads();
-    quad_chain<T, S>(lds, lg, meta, pd.ngroups, pd.ngroups, fl_quad_lane<S>(), true);
+    quad_chain<T, 1>(lds, lg, meta, pd.ngroups, pd.ngroups, fl_quad_lane<1>(), true);
 #pragma unroll
     for (int s = 0; s < ITER; ++s) {
         const uint32_t l = l0 ^ fl_swz((uint32_t)(s * APL * NT));
@@ -860,6 +857,151 @@ __device__ __forceinline__ T wave_transpose_reduce(T (&v)[NV]) {
     else
         tr_steps_f64<NV, 32>(v, threadIdx.x & 63);
     return v[0];
+}
+
+// ---------------------------------------------------------------------------
+// short chains: gates between the lanes of a wave
+// ---------------------------------------------------------------------------
+// lane ^ X of x for the distances of the quads on 4 lane bits
+template <int X>
+__device__ __forceinline__ float lane_xor(float x) {
+    if constexpr (X == 1) return fl_dpp_f<0xB1>(x);                      // quad_perm(1,0,3,2)
+    else if constexpr (X == 2) return fl_dpp_f<0x4E>(x);                 // quad_perm(2,3,0,1)
+    else if constexpr (X == 3) return fl_dpp_f<0x1B>(x);                 // quad_perm(3,2,1,0)
+    else if constexpr (X == 8) return fl_dpp_f<0x128>(x);                // row_ror:8
+    else if constexpr (X == 4) return fl_dpp_f<0x141>(lane_xor<3>(x));   // row_half_mirror: ^ 7
+    else if constexpr (X == 6) return fl_dpp_f<0x141>(lane_xor<1>(x));
+    else {
+        static_assert(X == 12, "distance");
+        return fl_dpp_f<0x140>(lane_xor<3>(x));                          // row_mirror: ^ 15
+    }
+}
+template <int X>
+__device__ __forceinline__ double lane_xor(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = __float_as_uint(lane_xor<X>(__uint_as_float((uint32_t)u)));
+    const uint32_t hi = __float_as_uint(lane_xor<X>(__uint_as_float((uint32_t)(u >> 32))));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// A gate on lane bits (I, I + 1), one amplitude per lane: c holds the lane's
+// row, entry d for the amplitude of the lane whose two bits differ by d.  The
+// own real term comes last, as in apply_pair_g.
+template <typename T, int I>
+__device__ __forceinline__ void apply_lanes(T& vr, T& vi, const T (&c)[8]) {
+    const T ar = lane_xor<(1 << I)>(vr), ai = lane_xor<(1 << I)>(vi);
+    const T br = lane_xor<(2 << I)>(vr), bi = lane_xor<(2 << I)>(vi);
+    const T dr = lane_xor<(3 << I)>(vr), di = lane_xor<(3 << I)>(vi);
+    T sr = -c[1] * vi, si = c[1] * vr;
+    sr = fma(c[2], ar, sr);
+    si = fma(c[2], ai, si);
+    sr = fma(-c[3], ai, sr);
+    si = fma(c[3], ar, si);
+    sr = fma(c[4], br, sr);
+    si = fma(c[4], bi, si);
+    sr = fma(-c[5], bi, sr);
+    si = fma(c[5], br, si);
+    sr = fma(c[6], dr, sr);
+    si = fma(c[6], di, si);
+    sr = fma(-c[7], di, sr);
+    si = fma(c[7], dr, si);
+    vr = fma(c[0], vr, sr);
+    vi = fma(c[0], vi, si);
+}
+
+// The gate table as k_sweep_lanes reads it: entry d of row i is column i ^ d.
+template <typename T>
+__device__ __forceinline__ void lane_table(typename CT<T>::c* lg, const T* gates, int ngates, int nt) {
+    const typename CT<T>::c* const src = reinterpret_cast<const typename CT<T>::c*>(gates);
+    for (int t = threadIdx.x; t < ngates * 16; t += nt) lg[t] = src[(t & ~3) | ((t ^ (t >> 2)) & 3)];
+}
+
+// Tiles of 2^KT amplitudes (KT <= 10), one per workgroup and one amplitude per
+// thread.  A register group's 4 tile bits are the low 4 lane bits: its gates
+// exchange amplitudes between lanes of a row of 16 (DPP), with no LDS round
+// trip and no barrier between them; only a change of group goes through LDS.
+// The next gate's row, and the word of the one after, are fetched under the
+// current one's FMAs.  Against the quad chain with two threads per quad (a
+// barrier per gate), 16 periods (us): complex128 on 9 bits L = 12 80 / 92, 17
+// 138 / 153, on 10 bits 18 169 / 181; complex64 on 10 bits L = 11 61 / 65, 12 70 /
+// 73, 17 123 / 126, 18 140 / 144.  Bound by latency: of 0.3 us a gate the 16 FMAs,
+// 6 to 8 lane moves and the waits between them, and a third of an LDS exchange.
+// Two amplitudes per thread (half the waves) are slower: complex64 L = 12 72,
+// complex128 L = 12 85.  In one workgroup (L <= 10) this form is within 5% of the
+// quads, either way.
+template <typename T, int KT, int CL>
+__global__ __launch_bounds__(1 << KT) void k_sweep_lanes(typename CT<T>::c* __restrict__ psi,
+                                                        const T* __restrict__ gates, int W, fl_sweep_words pd,
+                                                        int ngates) {
+    typedef typename CT<T>::c cplx;
+    typedef typename std::conditional<sizeof(T) == 4, fl_f32x4, fl_f64x2>::type v16;
+    constexpr int NT = 1 << KT, PER = 16 / sizeof(T);
+    __shared__ __attribute__((aligned(16))) cplx lds[NT];
+    __shared__ __attribute__((aligned(16))) cplx lgt[FL_MAX_GATE_TABLE * 16];
+    __shared__ uint32_t meta[FL_SWEEP_WORDS];
+    cplx* const p = psi + fl_tile_base(blockIdx.x, CL, W, pd.h) + fl_tile_offset(threadIdx.x, CL, pd.h);
+    const cplx first = *p;
+    lane_table<T>(lgt, gates, ngates, NT);
+    for (int t = threadIdx.x; t < pd.nwords; t += NT) meta[t] = pd.w[t];
+    lds[fl_swz(threadIdx.x)] = first;
+    __syncthreads();
+    const T* const lg = reinterpret_cast<const T*>(lgt);
+    char* const lb = reinterpret_cast<char*>(lds);
+    const int ng = pd.ngroups, nt = pd.nwords - 1 - ng;   // groups, gates
+    const uint32_t m = threadIdx.x & 15;
+    auto uni = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane(x); };
+    auto addr = [&](uint32_t head) {
+        const int u0 = head & 255;
+        return fl_swz(fl_spread(threadIdx.x >> 4, u0, 4) | (m << u0)) * (uint32_t)sizeof(cplx);
+    };
+    auto row = [&](uint32_t w, T (&c)[8]) {
+        const T* const src = lg + 32 * (w >> 8) + 8 * ((m >> (w & 255)) & 3);
+#pragma unroll
+        for (int k = 0; k < 8 / PER; ++k) {
+            const v16 v = reinterpret_cast<const v16*>(src)[k];
+#pragma unroll
+            for (int e = 0; e < PER; ++e) c[PER * k + e] = v[e];
+        }
+    };
+    if (nt > 0) {
+        T ca[8], cb[8], vr, vi;
+        uint32_t w = uni(meta[ng]), head = uni(meta[0]);
+        row(w, ca);
+        int pos = nt > 1 ? 1 : 0;
+        uint32_t wn = uni(meta[ng + pos]);
+        auto op = [&](const T (&c)[8], T (&cn)[8]) {
+            row(wn, cn);
+            if (pos + 1 < nt) ++pos;
+            const uint32_t w2 = meta[ng + pos];
+            with_bit<4>(w & 255, [&](auto I) { apply_lanes<T, decltype(I)::value>(vr, vi, c); });
+            w = wn;
+            wn = uni(w2);
+        };
+        for (int g = 0; g < ng; ++g) {
+            const int nops = head >> 8;
+            cplx* const at = reinterpret_cast<cplx*>(lb + addr(head));
+            const cplx a = *at;
+            vr = a.x;
+            vi = a.y;
+            const uint32_t next = meta[g + 1];   // past the last group: the first gate's word, unused
+            for (int q = 0; q < nops; q += 2) {
+                op(ca, cb);
+                if (q + 1 < nops) {
+                    op(cb, ca);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) ca[k] = cb[k];
+                }
+            }
+            cplx b;
+            b.x = vr;
+            b.y = vi;
+            *at = b;
+            head = uni(next);
+            __syncthreads();
+        }
+    }
+    *p = lds[fl_swz(threadIdx.x)];
 }
 
 // ---------------------------------------------------------------------------
@@ -2813,13 +2955,24 @@ static bool quad_words(const fl_pass& pd, int gofs, fl_sweep_words& w) {
     return true;
 }
 
-template <typename T, int K, int C, int S>
+template <typename T, int K, int C>
 static hipError_t launch_quads(const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int gofs,
                                hipStream_t s) {
     typedef typename CT<T>::c cplx;
     fl_sweep_words w;
     if (!quad_words(pd, gofs, w)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_sweep_quads<T, K, C, S>), dim3(ntiles_of(g)), dim3(S << (K - 2)), 0, s, (cplx*)psi,
+    hipLaunchKernelGGL((k_sweep_quads<T, K, C>), dim3(ntiles_of(g)), dim3(1 << (K - 2)), 0, s, (cplx*)psi,
+                       (const T*)gates + 32 * gofs, g.W, w, g.L - 1);
+    return hipGetLastError();
+}
+
+template <typename T, int K, int C>
+static hipError_t launch_lanes(const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int gofs,
+                               hipStream_t s) {
+    typedef typename CT<T>::c cplx;
+    fl_sweep_words w;
+    if (!sweep_words(pd, gofs, w)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_sweep_lanes<T, K, C>), dim3(ntiles_of(g)), dim3(1 << K), 0, s, (cplx*)psi,
                        (const T*)gates + 32 * gofs, g.W, w, g.L - 1);
     return hipGetLastError();
 }
@@ -2874,13 +3027,13 @@ hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gate
     auto code = [](int dt, int K, int C, int R) { return (dt << 12) | (K << 8) | (C << 4) | R; };
     if (key == code(0, 13, 4, 4)) return launch_tiles<float, 4, 13, 4, 4, fl_pass>(g, psi, gates, pd, gofs, s);
     if (key == code(0, 12, 4, 3)) return launch_tiles<float, 3, 12, 4, 4, fl_sweep_words>(g, psi, gates, pd, gofs, s);
-    if (key == code(0, 11, 3, 2)) return launch_quads<float, 11, 3, 1>(g, psi, gates, pd, gofs, s);
-    if (key == code(0, 10, 3, 2)) return launch_quads<float, 10, 3, 2>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 11, 3, 2)) return launch_quads<float, 11, 3>(g, psi, gates, pd, gofs, s);
+    if (key == code(0, 10, 3, 4)) return launch_lanes<float, 10, 3>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 12, 6, 4)) return launch_tiles<double, 4, 12, 6, 2, fl_pass>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 12, 3, 4)) return launch_tiles<double, 4, 12, 3, 2, fl_pass>(g, psi, gates, pd, gofs, s);
     if (key == code(1, 11, 3, 3)) return launch_tiles<double, 3, 11, 3, 2, fl_sweep_words>(g, psi, gates, pd, gofs, s);
-    if (key == code(1, 10, 3, 2)) return launch_quads<double, 10, 3, 2>(g, psi, gates, pd, gofs, s);
-    if (key == code(1, 9, 3, 2)) return launch_quads<double, 9, 3, 2>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 10, 3, 4)) return launch_lanes<double, 10, 3>(g, psi, gates, pd, gofs, s);
+    if (key == code(1, 9, 3, 4)) return launch_lanes<double, 9, 3>(g, psi, gates, pd, gofs, s);
     return hipErrorInvalidValue;
 }
 
