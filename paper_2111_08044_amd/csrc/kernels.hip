@@ -1,6 +1,6 @@
 // HIP kernels of the Floquet brickwork engine (gfx950, wave64).
 //
-//  k_sweep_tiles / k_sweep_quads / k_sweep_one
+//  k_sweep_tiles / k_sweep_lanes / k_sweep_quads / k_sweep_one
 //             fused gate sweep: one HBM read + write of the state applies
 //             every gate of a pass (Sec. II Eq. (2), fused as in Sec. II).
 //  k_rdm_windows / k_rdm
@@ -333,9 +333,10 @@ __device__ __forceinline__ void load_gate_rows(const fl_quad_lane<S>& me, const 
 // run, and between two barriers a thread only reads its quad, applies 64 / S
 // FMAs and writes its outputs back.  Each thread holds the quad and its gate
 // rows rotated, so that its first output stands first; the sums do not depend
-// on S.  The nops gates run over and over, total gates in all.  About 0.33 us a gate (0.39 with one thread per quad, of which 0.13 are
-// the 64 FMAs of a wave alone on its SIMD).  meta holds a pass in words form with one op per group: first bits,
-// then gates << 8.
+// on S.  The nops gates run over and over, total gates in all.  About 0.33 us a
+// gate (0.39 with one thread per quad, of which 0.13 are the 64 FMAs of a wave
+// alone on its SIMD).  meta holds a pass in words form with one op per group:
+// first bits, then gates << 8.
 template <typename T, int S>
 __device__ __forceinline__ void quad_chain(typename CT<T>::c* lds, const T* lg, const uint32_t* meta, int nops, int total,
                                            const fl_quad_lane<S>& me, bool active) {
