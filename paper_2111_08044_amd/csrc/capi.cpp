@@ -177,7 +177,7 @@ struct fl_ctx {
     double T = 0.0;
     std::vector<cd> h, G;  // FP64, (L-1) x 16
     void* d_gates = nullptr;   // 2 (L-1) gates, 32 reals each, context precision
-    void* d_h = nullptr;       // H0 psi: the bond Hamiltonians, 32 reals each (single-tile chains), or the window tables
+    void* d_h = nullptr;       // H0 psi: the window tables (h_windows), or the bond Hamiltonians, 32 reals each
     double* d_h64 = nullptr;   // the same in FP64 (energy contraction on the device)
     double* d_part = nullptr;  // reduction partials [kReduceGrid][L][16]
     double* h_red = nullptr;   // finalized reductions, 2 x L x 16: pinned host memory that the kernels write
@@ -219,9 +219,10 @@ struct fl_ctx {
     };
     std::map<std::pair<int, int>, DensePlan> dense_plans;
     std::vector<std::vector<unsigned char>> dense_host;  // host fragments: sources of in-flight uploads
-    std::vector<fl_pass> cover;       // bond cover of the sweep geometry (H0 psi of single-tile chains)
-    fl_geom geom_h{};                 // the same tiles with 4-bit windows (longer chains):
+    std::vector<fl_pass> cover;       // bond cover of the sweep geometry (H0 psi, bond by bond)
+    fl_geom geom_h{};                 // the same tiles with 4-bit windows (chains longer than one tile):
     std::vector<fl_pass> cover_h;     // the cover's bonds packed into windows
+    bool h_windows = false;           // H0 psi runs by windows (set with the bond terms)
     std::vector<fl_pass> cover_rdm;   // bond cover of the reductions of chains shorter than a full tile
     std::vector<fl::rdm_desc> cover_win;   // the cover of longer chains, in windows (geom_rdm: full tiles)
 };
@@ -325,6 +326,27 @@ size_t n_h_windows(const fl_ctx* c) {
     return n;
 }
 
+// Whether H0 psi may run by windows: on chains longer than one tile, and for
+// terms that are Hermitian to the rounding of the context's precision.  The
+// window tables hold an entry for each pair of conjugate ones; fl_set_bonds
+// accepts pairs that differ by up to 1e-12 of max(1, |h|), which is more than
+// rounding in complex128, and all of h where h itself is that small.
+bool h_fits_windows(const fl_ctx* c) {
+    if (c->cover_h.empty()) return false;
+    const double eps = c->dtype == FL_C64 ? 1.2e-7 : 2.3e-16;
+    for (int b = 0; b < c->L - 1; ++b) {
+        const cd* h = &c->h[(size_t)b * 16];
+        double scale = 0.0, asym = 0.0;
+        for (int i = 0; i < 4; ++i)
+            for (int j = 0; j < 4; ++j) {
+                scale = std::max(scale, std::abs(h[4 * i + j]));
+                asym = std::max(asym, std::abs(h[4 * i + j] - std::conj(h[4 * j + i])));
+            }
+        if (asym > 2.0 * eps * scale) return false;
+    }
+    return true;
+}
+
 // The summed Hamiltonian of every window of the H0 psi cover (FP64 sums,
 // rounded once), in the order apply_h_window reads: 16 diagonal reals, the
 // flips of bit k (rows with bit k clear) by its neighbours' values, the
@@ -416,10 +438,11 @@ int install_gates(fl_ctx* c) {
     const int rb = c->dtype == FL_C64 ? 4 : 8;
     stage_mats(st, c->d_gates, both, (size_t)2 * nb, rb);
     if (c->have_h) {
-        if (c->cover_h.empty())
-            stage_mats(st, c->d_h, c->h, nb, rb);
-        else
+        c->h_windows = h_fits_windows(c);
+        if (c->h_windows)
             stage_h_windows(st, c);
+        else
+            stage_mats(st, c->d_h, c->h, nb, rb);
         stage_mats(st, c->d_h64, c->h, nb, 8);
     }
     return stage_commit(c, st);
@@ -740,10 +763,10 @@ void overlap_terms_win4(const fl_ctx* c, const fl_ctx::AdjWin4& aw, const double
     }
 }
 
-// out <- H0 psi.  With dots (chains longer than one tile) the last pass also
-// leaves the per-workgroup sums of k_apply_h_tiles there, *grid_out rows.
+// out <- H0 psi.  With dots (by windows only) the last pass also leaves the
+// per-workgroup sums of k_apply_h_tiles there, *grid_out rows.
 int apply_h0(fl_ctx* c, const void* psi, void* out, double* dots, int* grid_out) {
-    if (c->cover_h.empty()) {
+    if (!c->h_windows) {
         bool first = true;
         for (const fl_pass& p : c->cover) {
             hipError_t e = fl::launch_apply_h(c->dtype, c->geom, psi, out, c->d_h, p, first ? 1 : 0, c->stream);
@@ -849,12 +872,11 @@ int fl_create(fl_ctx** ctx, int L, int dtype, int variant, void* hip_stream) {
               : (variant == FL_DENSE4_FP32) ? fl::make_geom(L, FL_KMAX_C64, 4, FL_DENSE4_LOWBITS)
                                             : fl::make_geom(L, FL_KMAX_C64, 6, kDense6LowBits);
     c->geom_adj = adjoint_geom(L, dtype);
+    c->cover = fl::plan_cover(c->geom);
     if (c->geom.W > 0) {
         c->geom_h = c->geom;
         c->geom_h.R = 4;
         c->cover_h = fl::plan_cover_groups(c->geom_h);
-    } else {
-        c->cover = fl::plan_cover(c->geom);
     }
     c->geom_rdm = rdm_geom(L, dtype);
     if (c->geom_rdm.W > 0)
@@ -1135,7 +1157,7 @@ int fl_energy_spread(fl_ctx* c, const void* psi, void* ws, double out[3]) {
     if (ws == psi) return fail(FL_EINVAL, "ws must not alias psi");
     if (!out) return fail(FL_EINVAL, "out is NULL");
     if (!c->have_h) return fail(FL_ESTATE, "no bond Hamiltonians: call fl_set_bonds first");
-    const bool fused = !c->cover_h.empty();   // the sums come with the last pass
+    const bool fused = c->h_windows;   // the sums come with the last pass
     int grid = 0;
     rc = apply_h0(c, psi, ws, fused ? c->d_part : nullptr, &grid);
     if (rc) return rc;

@@ -31,7 +31,8 @@ hipError_t launch_energy_contract(const double* red, const double* h64, int L, d
 hipError_t launch_init(int dtype, void* psi, int L, const void* tabs, int a, int b, hipStream_t s);
 hipError_t launch_overlap(int dta, const void* a, int dtb, const void* b, uint64_t n, double* partials, int grid,
                           hipStream_t s);
-// H0 psi of single-tile chains
+// one cover pass of H0 psi bond by bond, every entry of the terms as given:
+// single-tile chains, and terms that are not Hermitian to rounding
 hipError_t launch_apply_h(int dtype, const fl_geom& g, const void* psi, void* lam, const void* hmat, const fl_pass& pd,
                           int first, hipStream_t s);
 // one cover pass of H0 psi on full tiles: `first` writes lambda, the others add to it

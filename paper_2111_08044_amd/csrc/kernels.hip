@@ -1449,6 +1449,8 @@ __global__ __launch_bounds__(64) void k_energy_contract(const double* __restrict
 // lambda = H0 psi, out of place (the Hamiltonian application of Sec. V)
 // ---------------------------------------------------------------------------
 // One cover pass per launch; the first pass writes lambda, later passes add.
+// Bond by bond, with all 16 entries of each term as given: chains of one tile,
+// and longer ones whose terms are not Hermitian to rounding.
 
 template <typename T, int KT, int KMAX>
 __global__ __launch_bounds__(FL_NT) void k_apply_h(const typename CT<T>::c* __restrict__ psi,
@@ -1503,7 +1505,7 @@ __global__ __launch_bounds__(FL_NT) void k_apply_h(const typename CT<T>::c* __re
     tile_store<T, KT>(lam, base, K, C, h, ll);
 }
 
-// Full tiles (W > 0).  The bonds of a pass come packed into windows of 4
+// Full tiles (W > 0), Hermitian terms.  The bonds of a pass come packed into windows of 4
 // consecutive tile bits (up to 3 bonds each), and every thread applies a
 // window's summed Hamiltonian to 2^4 amplitudes at once.  A row of that sum
 // has one real diagonal entry, one entry per flipped bit (the bonds on both

@@ -176,3 +176,32 @@ def test_more_periods_than_one_launch_of_a_short_chain(dtype, L):
     fl.fl_grad(ctx, psi, [], n, 0, O.xyz_coupling_generators(L), torch.empty_like(psi))
     ulp = 6e-8 if dtype == "c64" else 1.2e-16
     assert np.linalg.norm(psi.cpu().numpy() - ref) < 2 * n * (L - 1) * ulp * np.linalg.norm(ref)
+
+
+# both sides of the window tables: terms Hermitian to rounding, and terms that
+# are Hermitian only within what fl_set_bonds accepts (1e-12 of max(1, |h|))
+@pytest.mark.parametrize("dtype,L", [("c64", 12), ("c64", 14), ("c64", 22), ("c128", 12), ("c128", 13), ("c128", 19)])
+@pytest.mark.parametrize("size,asym", [(1.0, 0.0), (1.0, 2e-16), (1.0, 5e-13), (3e-13, 3e-13)])
+def test_h0_psi_takes_every_entry_of_its_terms(dtype, L, size, asym):
+    """H0 psi applies the matrices as given, with the tolerance of
+    test_h0_psi_and_its_sums."""
+    say(f"case: H0 psi {dtype} L={L} size={size} asym={asym}")
+    rng = np.random.default_rng(40 + L)
+    hs = size * fin.gue_bond_sample(L, seed=40 + L)
+    hs = hs + asym * (rng.uniform(-0.5, 0.5, hs.shape) + 0.5j * rng.uniform(-0.5, 0.5, hs.shape))
+    ctx = fl.fl_create(L, dtype)
+    ulp = 6e-8 if dtype == "c64" else 1.2e-16
+    # Hermitian terms before and after them: the two forms follow each other on one context
+    for h in (2.0 * fin.gue_bond_sample(L, seed=L), hs, 2.0 * fin.gue_bond_sample(L, seed=L + 1)):
+        fl.fl_set_bonds(ctx, h, 0.7)
+        psi = fl.new_state(ctx)
+        psi.copy_(torch.from_numpy(fin.random_state(L, L)).to(psi.dtype))
+        ref = psi.cpu().numpy().astype(np.complex128)
+        ws = torch.full_like(psi, float("nan"))
+        E, E2, N = fl.fl_energy_spread(ctx, psi, ws)
+        want = O.apply_h0(ref, L, h)
+        got = ws.cpu().numpy().astype(np.complex128)
+        assert np.linalg.norm(got - want) < 10 * ulp * np.linalg.norm(want)
+        assert abs(E - np.vdot(ref, got).real) < 1e-12 * np.linalg.norm(ref) * np.linalg.norm(got)
+        assert abs(E2 - np.vdot(got, got).real) < 1e-12 * E2
+        assert abs(N - np.vdot(ref, ref).real) < 1e-12 * N
