@@ -257,8 +257,9 @@ int fl_host_window_matrix(const double *G, const int *pos, int nops, int mode, d
 int fl_host_window_overlaps(const double *Q, const double *G, const int *pos, int nops, double *out);
 
 /* The plan fl_apply_period would run for n periods (kind 0 = sweep,
- * 1 = reverse sweep of the gradient (chains of at most 10 sites run the
- * one-period plans of these two n times), 2 = energy / density-matrix cover (the
+ * 1 = reverse sweep of the gradient (both in blocks of 16 periods and a
+ * remainder; chains of at most 10 sites in blocks of one period, up to 256 of
+ * them in one launch), 2 = energy / density-matrix cover (the
  * bonds of each pass; full tiles with 4 low bits from L = 13 complex64, 12
  * complex128), 3 = cover used for H0 psi by a plain-sweep context, 4 = dense
  * 6-qubit-window sweep, 5 = dense 4-qubit-window sweep, 6 = a cover of

@@ -1448,20 +1448,15 @@ int fl_plan_query(int L, int dtype, int kind, int64_t n, int dagger, int32_t* bu
     if (!needed) return fail(FL_EINVAL, "needed is NULL");
     std::vector<fl_pass> plan;
     fl_geom g;
-    if (kind == 0) {
-        g = sweep_geom(L, dtype, n);
-        const int64_t q = n / kPlanBlock, r = n % kPlanBlock;
+    if (kind == 0 || kind == 1) {
+        g = kind == 0 ? sweep_geom(L, dtype, n) : adjoint_geom(L, dtype);
+        const bool dag = kind == 1 || dagger != 0;
+        // as run_periods and run_reverse: blocks of kPlanBlock periods, or of one
+        const int block = L <= FL_KMAX_ONE ? 1 : kPlanBlock;
+        const int64_t q = n / block, r = n % block;
         std::vector<fl_pass> pb, pr;
-        if (q > 0) pb = fl::plan_sweep(g, kPlanBlock, dagger != 0, false, kMaxGatesPerPass);
-        if (r > 0) pr = fl::plan_sweep(g, (int)r, dagger != 0, false, kMaxGatesPerPass);
-        for (int64_t i = 0; i < q; ++i) plan.insert(plan.end(), pb.begin(), pb.end());
-        plan.insert(plan.end(), pr.begin(), pr.end());
-    } else if (kind == 1) {
-        g = adjoint_geom(L, dtype);
-        const int64_t q = n / kPlanBlock, r = n % kPlanBlock;
-        std::vector<fl_pass> pb, pr;
-        if (q > 0) pb = fl::plan_sweep(g, kPlanBlock, true, true, kMaxGatesPerPass);
-        if (r > 0) pr = fl::plan_sweep(g, (int)r, true, true, kMaxGatesPerPass);
+        if (q > 0) pb = fl::plan_sweep(g, block, dag, kind == 1, kMaxGatesPerPass);
+        if (r > 0) pr = fl::plan_sweep(g, (int)r, dag, kind == 1, kMaxGatesPerPass);
         for (int64_t i = 0; i < q; ++i) plan.insert(plan.end(), pb.begin(), pb.end());
         plan.insert(plan.end(), pr.begin(), pr.end());
     } else if (kind == 2) {

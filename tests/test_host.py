@@ -220,6 +220,20 @@ def test_reverse_gradient_plan(L, n):
 
 
 @pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("kind,dagger", [(0, False), (0, True), (1, True)])
+@pytest.mark.parametrize("L", [2, 5, 10])
+def test_one_workgroup_chains_repeat_the_plan_of_one_period(dtype, kind, dagger, L):
+    """Chains of at most 10 sites run one period's passes over and over; from
+    11 sites on a block of 16 periods is planned as a whole."""
+    one = pt.parse_plan(fl.fl_plan_query(L, dtype, kind, 1, dagger))
+    for n in (2, 16, 35):
+        many = pt.parse_plan(fl.fl_plan_query(L, dtype, kind, n, dagger))
+        assert many == (*one[:3], one[3] * n)
+    longer = [pt.parse_plan(fl.fl_plan_query(11, dtype, kind, n, dagger))[3] for n in (1, 16, 19, 3)]
+    assert longer[1] != longer[0] * 16 and longer[2] == longer[1] + longer[3]
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
 @pytest.mark.parametrize("L", [2, 3, 12, 13, 14, 21, 30, 34])
 def test_energy_cover_visits_every_bond_once(dtype, L):
     if dtype == "c128" and L == 34:
