@@ -261,7 +261,9 @@ int fl_host_window_overlaps(const double *Q, const double *G, const int *pos, in
  * remainder; chains of at most 10 sites in blocks of one period, up to 256 of
  * them in one launch), 2 = energy / density-matrix cover (the
  * bonds of each pass; full tiles with 4 low bits from L = 13 complex64, 12
- * complex128), 3 = cover used for H0 psi by a plain-sweep context, 4 = dense
+ * complex128), 3 = cover used for H0 psi by a plain-sweep context
+ * (Hermitian terms; bonds packed into 4-bit windows on chains longer than one
+ * tile), 4 = dense
  * 6-qubit-window sweep, 5 = dense 4-qubit-window sweep, 6 = a cover of
  * complex64 states with L >= 14 on 13-bit tiles with 6 low bits, bonds packed
  * into 5-bit register groups), flattened as int32:

@@ -1476,7 +1476,8 @@ int fl_plan_query(int L, int dtype, int kind, int64_t n, int dagger, int32_t* bu
         plan.insert(plan.end(), pr.begin(), pr.end());
     } else if (kind == 3) {
         g = plain_geom(L, dtype);
-        plan = fl::plan_cover(g);
+        if (g.W > 0) g.R = 4;   // the windows of geom_h
+        plan = g.W > 0 ? fl::plan_cover_groups(g) : fl::plan_cover(g);
     } else if (kind == 6) {
         if (dtype != FL_C64 || L <= FL_KMAX_C64) return fail(FL_EINVAL, "the grouped cover needs complex64 and L >= 14");
         g = fl::make_geom(L, FL_KMAX_C64, 5);

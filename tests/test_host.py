@@ -278,6 +278,35 @@ def test_grouped_energy_cover_visits_every_bond_once(L):
         assert len(passes) == 4 and sum(len(o) for _, o in passes[0][2]) == 12
 
 
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("L", range(2, 35))
+def test_h0_cover_visits_every_bond_once(dtype, L):
+    """H0 psi: one bond per op on one tile; on longer chains windows of 4 tile
+    bits with up to 3 bonds each, which the kernel takes in order: at most 8 a
+    pass, the last one above the low 4 bits (its elements are loaded and stored
+    straight in that window's layout)."""
+    if dtype == "c128" and L == 34:
+        pytest.skip("L = 34 is complex64 only")
+    C, W, R, passes = pt.parse_plan(fl.fl_plan_query(L, dtype, 3, 0, False))
+    tile = 13 if dtype == "c64" else 12
+    assert (C, W) == ((L, 0) if L <= tile else (4, 9) if dtype == "c64" else (6, 6))
+    assert R == min(4, L)
+    seen = []
+    for h, _, windows in passes:
+        assert W == 0 or C <= h <= L - W
+        for u0, ops in windows:
+            assert 1 <= len(ops) <= (1 if W == 0 else 3)
+            assert u0 >= 0 and u0 + (2 if W == 0 else 4) <= C + W
+            for i, g, bond in ops:
+                assert g == -1 and 0 <= i <= (0 if W == 0 else 2)
+                p, p1 = pt.phys_bit(u0 + i, C, h), pt.phys_bit(u0 + i + 1, C, h)
+                assert p1 == p + 1 and bond == L - 2 - p
+                seen.append(bond)
+        if W > 0:
+            assert 1 <= len(windows) <= 8 and windows[-1][0] >= 4
+    assert sorted(seen) == list(range(L - 1))
+
+
 def test_grouped_energy_cover_needs_complex64_and_long_chains():
     with pytest.raises(fl.FloquetError):
         fl.fl_plan_query(13, "c64", 6, 0, False)
