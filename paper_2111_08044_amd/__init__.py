@@ -27,7 +27,7 @@ __all__ = [
     "fl_expect_energy", "fl_expect_energy_noalloc", "fl_energy_spread", "fl_overlap", "fl_grad_workspace_bytes", "fl_grad",
     "fl_last_error", "fl_xyz_bonds", "fl_xyz_generators", "fl_host_gates", "fl_host_gate_derivative",
     "fl_host_ground_states",
-    "fl_plan_query", "fl_tile_map", "fl_host_window_matrix", "fl_host_window_overlaps", "Context", "new_state", "FloquetEngine", "FloquetEnergy",
+    "fl_plan_query", "fl_readout_windows", "fl_tile_map", "fl_host_window_matrix", "fl_host_window_overlaps", "Context", "new_state", "FloquetEngine", "FloquetEnergy",
     "thermalization_rate", "fit_exponential_rate",
 ]
 
@@ -300,6 +300,15 @@ def fl_plan_query(L: int, dtype="c64", kind: int = 0, n: int = 1, dagger: bool =
     buf = np.zeros(need.value, dtype=np.int32)
     check(lib().fl_plan_query(int(L), dt, int(kind), int(n), 1 if dagger else 0,
                               buf.ctypes.data_as(C.POINTER(C.c_int32)), need.value, C.byref(need)))
+    return buf
+
+
+def fl_readout_windows(L: int, dtype="c64") -> np.ndarray:
+    dt = _DTYPES[dtype] if isinstance(dtype, str) else int(dtype)
+    need = C.c_int64()
+    check(lib().fl_readout_windows(int(L), dt, None, 0, C.byref(need)))
+    buf = np.zeros(need.value, dtype=np.int32)
+    check(lib().fl_readout_windows(int(L), dt, buf.ctypes.data_as(C.POINTER(C.c_int32)), need.value, C.byref(need)))
     return buf
 
 

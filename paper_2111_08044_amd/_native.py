@@ -49,6 +49,7 @@ SIGNATURES = {
     "fl_host_window_overlaps": (C.c_int, [dp, dp, C.POINTER(C.c_int), C.c_int, dp]),
     "fl_plan_query": (C.c_int, [C.c_int, C.c_int, C.c_int, i64, C.c_int, C.POINTER(C.c_int32), i64,
                                 C.POINTER(i64)]),
+    "fl_readout_windows": (C.c_int, [C.c_int, C.c_int, C.POINTER(C.c_int32), i64, C.POINTER(i64)]),
 }
 
 

@@ -115,10 +115,10 @@ fl_geom adjoint_geom(int L, int dtype) {
 
 // Geometry of the energy / density-matrix reduction: full tiles with 4 low
 // bits; from L = 10 (9 bonds: 4 windows) a chain in one tile takes them as 4 low
-// bits plus a window too, shorter ones the plain single tile.
+// bits plus a window too, shorter ones the plain single tile, bond by bond.
 fl_geom rdm_geom(int L, int dtype) {
     const int kmax = kmax_of(dtype);
-    if (L < 10) return fl::make_geom(L, FL_KMAX_RDM, 2);
+    if (L < FL_RDM_MIN_WINDOWS) return fl::make_geom(L, FL_KMAX_RDM, 2);
     fl_geom g;
     g.L = L;
     g.K = std::min(L, kmax);
@@ -128,43 +128,6 @@ fl_geom rdm_geom(int L, int dtype) {
     return g;
 }
 
-// The bond cover of g with each pass's bonds in 1, 2 or 4 windows of 4 tile
-// bits (the kernel shares its waves among the windows evenly): as few as hold
-// the bonds at three each, and the bonds spread over them evenly (8 bonds: 4
-// windows of 2, not 3, 3, 2 and an idle quarter).
-std::vector<fl::rdm_desc> cover_windows(const fl_geom& g) {
-    std::vector<fl::rdm_desc> out;
-    for (const fl_pass& p : fl::plan_cover(g)) {
-        std::vector<std::pair<int, int>> bonds;   // (tile bit, bond)
-        for (int k = 0; k < p.ngroups; ++k) bonds.emplace_back((int)p.u0[k], (int)p.ops[k][0]);
-        std::sort(bonds.begin(), bonds.end());
-        size_t done = 0;
-        bool first = true;
-        while (done < bonds.size()) {
-            const size_t left = std::min<size_t>(bonds.size() - done, 12);
-            fl::rdm_desc d;
-            std::memset(&d, 0, sizeof(d));
-            d.h = p.h;
-            d.flags = first ? p.flags : 0;
-            d.nwin = left <= 3 ? 1 : left <= 6 ? 2 : 4;
-            const size_t end = done + left;
-            for (int w = 0; w < d.nwin; ++w) {
-                const size_t share = (end - done + (size_t)(d.nwin - w) - 1) / (size_t)(d.nwin - w);
-                if (share == 0) continue;   // an empty window: mask 0
-                d.u0[w] = std::min(bonds[done].first, g.K - 4);
-                for (size_t k = 0; k < share && bonds[done].first + 1 < d.u0[w] + 4; ++k) {
-                    const int j = bonds[done].first - d.u0[w];
-                    d.mask[w] |= 1 << j;
-                    d.bond[w][j] = bonds[done].second;
-                    if (++done == end) break;
-                }
-            }
-            first = false;
-            out.push_back(d);   // bonds that no window reached come in another pass
-        }
-    }
-    return out;
-}
 size_t amp_bytes(int dtype) { return dtype == FL_C64 ? 8 : 16; }
 
 }  // namespace
@@ -223,8 +186,8 @@ struct fl_ctx {
     fl_geom geom_h{};                 // the same tiles with 4-bit windows (chains longer than one tile):
     std::vector<fl_pass> cover_h;     // the cover's bonds packed into windows
     bool h_windows = false;           // H0 psi runs by windows (set with the bond terms)
-    std::vector<fl_pass> cover_rdm;   // bond cover of the reductions of chains shorter than a full tile
-    std::vector<fl::rdm_desc> cover_win;   // the cover of longer chains, in windows (geom_rdm: full tiles)
+    std::vector<fl_pass> cover_rdm;   // bond cover of the reductions of chains below FL_RDM_MIN_WINDOWS sites
+    std::vector<fl::rdm_desc> cover_win;   // the cover of longer chains, in windows of geom_rdm's tiles
 };
 
 namespace {
@@ -831,6 +794,16 @@ int upload_tables_and_init(fl_ctx* c, void* psi, const std::vector<cd>& tlo, con
     return FL_OK;
 }
 
+// At most cap words to buf (may be NULL), the count to *needed.
+int copy_words(const std::vector<int>& words, int32_t* buf, int64_t cap, int64_t* needed) {
+    *needed = (int64_t)words.size();
+    if (buf) {
+        const int64_t m = std::min<int64_t>(cap, (int64_t)words.size());
+        for (int64_t i = 0; i < m; ++i) buf[i] = words[i];
+    }
+    return FL_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -880,7 +853,7 @@ int fl_create(fl_ctx** ctx, int L, int dtype, int variant, void* hip_stream) {
     }
     c->geom_rdm = rdm_geom(L, dtype);
     if (c->geom_rdm.W > 0)
-        c->cover_win = cover_windows(c->geom_rdm);
+        c->cover_win = fl::cover_windows(c->geom_rdm);
     else
         c->cover_rdm = fl::plan_cover(c->geom_rdm);
     const int nb = L - 1;
@@ -1487,12 +1460,22 @@ int fl_plan_query(int L, int dtype, int kind, int64_t n, int dagger, int32_t* bu
     }
     std::vector<int> words;
     fl::serialize_plan(g, plan, words);
-    *needed = (int64_t)words.size();
-    if (buf) {
-        const int64_t m = std::min<int64_t>(cap, (int64_t)words.size());
-        for (int64_t i = 0; i < m; ++i) buf[i] = words[i];
+    return copy_words(words, buf, cap, needed);
+}
+
+int fl_readout_windows(int L, int dtype, int32_t* buf, int64_t cap, int64_t* needed) {
+    if (dtype != FL_C64 && dtype != FL_C128) return fail(FL_EINVAL, "bad dtype");
+    if (L < FL_RDM_MIN_WINDOWS || L > (dtype == FL_C64 ? 34 : 33)) return fail(FL_EINVAL, "L out of range");
+    if (!needed) return fail(FL_EINVAL, "needed is NULL");
+    const fl_geom g = rdm_geom(L, dtype);
+    const std::vector<fl::rdm_desc> passes = fl::cover_windows(g);
+    std::vector<int> words = {g.C, g.W, (int)passes.size()};
+    for (const fl::rdm_desc& d : passes) {
+        words.insert(words.end(), {d.h, d.flags, d.nwin});
+        for (int w = 0; w < d.nwin; ++w)
+            words.insert(words.end(), {d.u0[w], d.mask[w], d.bond[w][0], d.bond[w][1], d.bond[w][2]});
     }
-    return FL_OK;
+    return copy_words(words, buf, cap, needed);
 }
 
 }  // extern "C"

@@ -37,7 +37,8 @@
 #define FL_KMAX_ADJ 12       // tile bits of the two-state adjoint pass (complex64)
 #define FL_WIN4_MAX_GROUPS 14  // register groups per pass of a 4-qubit-window plan (the reverse pass keeps one window-overlap sum per group)
 #define FL_WIN4_NT 512         // threads of the 4-qubit-window reverse pass (13-bit tiles of two states)
-#define FL_KMAX_RDM 12       // tile bits of the reduction of chains shorter than a full tile
+#define FL_KMAX_RDM 12       // tile bits of the bond-by-bond reduction of the shortest chains
+#define FL_RDM_MIN_WINDOWS 10  // shortest chain whose bonds are reduced in windows
 #define FL_MAX_SLOTS 16      // distinct reduction slots per pass
 #define FL_KMAX_ONE 10       // longest chain whose sweep runs in one workgroup
 #define FL_SWEEP_WORDS 144   // words of a sweep pass's descriptor in words form: groups + ops + 1
@@ -71,6 +72,19 @@ struct fl_pass {
     int16_t opg[FL_MAX_GROUPS][FL_MAX_OPS];  // gate-table index, -1 = no gate
     int16_t ops[FL_MAX_GROUPS][FL_MAX_OPS];  // reduction slot (index into sbond), -1 = none
 };
+
+// A pass of the bond reductions: the bonds of a tile in 1, 2 or 4 windows of 4
+// tile bits, a bond on window bits (j, j + 1) where mask bit j is set; flags & 1:
+// also the norm.
+#ifdef __cplusplus
+namespace fl {
+struct rdm_desc {
+    int32_t h, flags, nwin;
+    int32_t u0[4], mask[4];
+    int32_t bond[4][3];
+};
+}  // namespace fl
+#endif
 
 // A sweep pass as a kernel that keeps its descriptor in LDS takes it.
 struct fl_sweep_words {

@@ -11,17 +11,10 @@ namespace fl {
 // launch, others take reps = 1 (also launch_adjoint)
 hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int reps,
                         hipStream_t s);
-// single-tile chains shorter than a full tile
+// bond reductions of shorter chains, one tile
 hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,
                       int nslot, hipStream_t s);
-// bond reductions over full tiles (13 bits complex64, 12 bits complex128): a
-// pass's bonds in 1, 2 or 4 windows of 4 tile bits, a bond on window bits
-// (j, j + 1) where mask bit j is set; flags & 1: also the norm
-struct rdm_desc {
-    int32_t h, flags, nwin;
-    int32_t u0[4], mask[4];
-    int32_t bond[4][3];
-};
+// one pass of the bond reductions of chains from FL_RDM_MIN_WINDOWS sites on
 hipError_t launch_rdm_windows(int dtype, const fl_geom& g, const void* psi, const rdm_desc& pd, double* partials,
                               int grid, int nslot, hipStream_t s);
 hipError_t launch_finalize(const double* partials, int nblocks, int nvals, double* out, hipStream_t s);

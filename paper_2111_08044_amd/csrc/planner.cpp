@@ -459,6 +459,40 @@ std::vector<fl_pass> plan_cover_groups(const fl_geom& g) {
     return plan;
 }
 
+std::vector<rdm_desc> cover_windows(const fl_geom& g) {
+    std::vector<rdm_desc> out;
+    for (const fl_pass& p : plan_cover(g)) {
+        std::vector<std::pair<int, int>> bonds;   // (tile bit, bond)
+        for (int k = 0; k < p.ngroups; ++k) bonds.emplace_back((int)p.u0[k], (int)p.ops[k][0]);
+        std::sort(bonds.begin(), bonds.end());
+        size_t done = 0;
+        bool first = true;
+        while (done < bonds.size()) {
+            const size_t left = std::min<size_t>(bonds.size() - done, 12);
+            rdm_desc d;
+            std::memset(&d, 0, sizeof(d));
+            d.h = p.h;
+            d.flags = first ? p.flags : 0;
+            d.nwin = left <= 3 ? 1 : left <= 6 ? 2 : 4;
+            const size_t end = done + left;
+            for (int w = 0; w < d.nwin; ++w) {
+                const size_t share = (end - done + (size_t)(d.nwin - w) - 1) / (size_t)(d.nwin - w);
+                if (share == 0) continue;   // an empty window: mask 0
+                d.u0[w] = std::min(bonds[done].first, g.K - 4);
+                for (size_t k = 0; k < share && bonds[done].first + 1 < d.u0[w] + 4; ++k) {
+                    const int j = bonds[done].first - d.u0[w];
+                    d.mask[w] |= 1 << j;
+                    d.bond[w][j] = bonds[done].second;
+                    if (++done == end) break;
+                }
+            }
+            first = false;
+            out.push_back(d);   // bonds that no window reached come in another pass
+        }
+    }
+    return out;
+}
+
 void serialize_plan(const fl_geom& g, const std::vector<fl_pass>& plan, std::vector<int>& out) {
     out.clear();
     out.push_back(g.C);

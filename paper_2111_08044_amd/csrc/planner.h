@@ -41,6 +41,12 @@ std::vector<fl_pass> plan_cover(const fl_geom& g);
 // (u0 + i, u0 + i + 1), i = 0 .. R-2 (op bit i, op slot = bond, no gate).
 std::vector<fl_pass> plan_cover_groups(const fl_geom& g);
 
+// The bond cover of g with each pass's bonds in 1, 2 or 4 windows of 4 tile
+// bits (the kernel shares its waves among the windows evenly): as few as hold
+// the bonds at three each, and the bonds spread over them evenly (8 bonds: 4
+// windows of 2, not 3, 3, 2 and an idle quarter).
+std::vector<rdm_desc> cover_windows(const fl_geom& g);
+
 // Flatten a plan into int32 words (for inspection and host-side tests):
 // [C, W, R, npasses, {h, ngroups, flags, {u0, nops, {opi, opg, ops}*}*}*]
 void serialize_plan(const fl_geom& g, const std::vector<fl_pass>& plan, std::vector<int>& out);

@@ -279,6 +279,46 @@ def test_grouped_energy_cover_visits_every_bond_once(L):
 
 
 @pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("L", range(10, 35))
+def test_readout_windows_visit_every_bond_once(dtype, L):
+    """The passes of the bond reductions as they are launched: 1, 2 or 4 windows
+    inside the tile (4 below 12 tile bits, where fewer would leave waves without
+    a part), each bond once on two neighbouring bits of its window, the norm in
+    the first pass, and the same bonds per pass as the plan query reports."""
+    if dtype == "c128" and L == 34:
+        pytest.skip("L = 34 is complex64 only")
+    w = [int(x) for x in fl.fl_readout_windows(L, dtype)]
+    (C, W, npasses), w = w[:3], w[3:]
+    K = min(L, 13 if dtype == "c64" else 12)
+    assert (C, W) == (4, K - 4)
+    seen, per_pass = [], []
+    for k in range(npasses):
+        (h, flags, nwin), w = w[:3], w[3:]
+        assert flags == (1 if k == 0 else 0) and C <= h <= L - W
+        assert nwin in ((1, 2, 4) if K >= 12 else (4,))
+        bonds = []
+        for _ in range(nwin):
+            (u0, mask, *bond), w = w[:5], w[5:]
+            assert 0 <= u0 <= K - 4 and 0 <= mask < 8
+            for j in range(3):
+                if (mask >> j) & 1:
+                    p, p1 = pt.phys_bit(u0 + j, C, h), pt.phys_bit(u0 + j + 1, C, h)
+                    assert p1 == p + 1 and bond[j] == L - 2 - p
+                    bonds.append(bond[j])
+        seen += bonds
+        per_pass.append((h, flags, sorted(bonds)))
+    assert not w and sorted(seen) == list(range(L - 1))
+    _, _, _, passes = pt.parse_plan(fl.fl_plan_query(L, dtype, 2, 0, False))
+    assert per_pass == [(h, flags, sorted(op[2] for _, ops in groups for op in ops)) for h, flags, groups in passes]
+
+
+def test_readout_windows_start_at_ten_sites():
+    for bad in (9, 35):
+        with pytest.raises(fl.FloquetError):
+            fl.fl_readout_windows(bad, "c64")
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
 @pytest.mark.parametrize("L", range(2, 35))
 def test_h0_cover_visits_every_bond_once(dtype, L):
     """H0 psi: one bond per op on one tile; on longer chains windows of 4 tile
