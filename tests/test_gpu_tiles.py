@@ -205,3 +205,11 @@ def test_h0_psi_takes_every_entry_of_its_terms(dtype, L, size, asym):
         assert abs(E - np.vdot(ref, got).real) < 1e-12 * np.linalg.norm(ref) * np.linalg.norm(got)
         assert abs(E2 - np.vdot(got, got).real) < 1e-12 * E2
         assert abs(N - np.vdot(ref, ref).real) < 1e-12 * N
+
+
+def test_bond_density_matrices_over_several_flushes():
+    """As test_bond_density_matrices_in_windows, with its tolerance: 16384 tiles
+    on 512 workgroups, so that sums go on after a flush (every 16 tiles).  A lane
+    sums at most 16 tiles x 8 parts x 8 terms between two flushes: 1024 roundings
+    of 1.1e-16, of sums that are at most a quarter of the norm."""
+    test_bond_density_matrices_in_windows("c64", 27)
