@@ -213,3 +213,24 @@ def test_bond_density_matrices_over_several_flushes():
     sums at most 16 tiles x 8 parts x 8 terms between two flushes: 1024 roundings
     of 1.1e-16, of sums that are at most a quarter of the norm."""
     test_bond_density_matrices_in_windows("c64", 27)
+
+
+def test_gradient_with_several_tiles_per_workgroup():
+    """As test_gradient_at_the_edges_of_its_tile_sizes, with its tolerance: 1024
+    tiles on 512 workgroups, the second with the gate table and the sums of the
+    first.  Both precisions against one run of the oracle."""
+    L, n = 22, 1
+    w = fin.xyz_workload(L, seed=800 + L)
+    hs = O.xyz_bond_hamiltonians(L, w["J"], w["fields"])
+    gens = O.xyz_coupling_generators(L)
+    say(f"case: grad oracle L={L} n={n}")
+    ref, _ = O.adjoint_gradient(L, hs, gens, w["T"], O.product_state(w["spinors"]), n)
+    for dtype, ulp in (("c64", 6e-8), ("c128", 1.2e-16)):
+        say(f"case: grad {dtype} L={L} n={n}")
+        ctx = fl.fl_create(L, dtype)
+        fl.fl_set_bonds(ctx, hs, w["T"])
+        psi = fl.new_state(ctx)
+        fl.fl_init_state(ctx, psi, w["spinors"])
+        fl.fl_apply_period(ctx, psi, n)
+        g = fl.fl_grad(ctx, psi, [], n, 0, gens, torch.empty_like(psi))
+        assert np.max(np.abs(g - ref)) < 2 * n * (L - 1) * ulp * 4 * (L - 1)
