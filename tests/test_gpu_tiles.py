@@ -234,3 +234,27 @@ def test_gradient_with_several_tiles_per_workgroup():
         fl.fl_apply_period(ctx, psi, n)
         g = fl.fl_grad(ctx, psi, [], n, 0, gens, torch.empty_like(psi))
         assert np.max(np.abs(g - ref)) < 2 * n * (L - 1) * ulp * 4 * (L - 1)
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("L", [2, 4, 8])
+def test_gradient_over_two_launches_of_a_short_chain(dtype, L):
+    """300 periods in one segment are two launches, of 256 and 44, that add to
+    the same sums.  Each of the 300 terms of a component is off by as much as
+    test_gradient_at_the_edges_of_its_tile_sizes allows the whole: n times its
+    tolerance.  Without the 44 periods' terms the gradient would be off by 0.8
+    at L = 2, 9.8 at L = 4 and 5.7 at L = 8 (tolerances in complex64: 0.04, 0.4, 2.1)."""
+    n = 300
+    say(f"case: grad {dtype} L={L} n={n}")
+    w = fin.xyz_workload(L, seed=800 + L)
+    hs = O.xyz_bond_hamiltonians(L, w["J"], w["fields"])
+    gens = O.xyz_coupling_generators(L)
+    ref, _ = O.adjoint_gradient(L, hs, gens, w["T"], O.product_state(w["spinors"]), n)
+    ctx = fl.fl_create(L, dtype)
+    fl.fl_set_bonds(ctx, hs, w["T"])
+    psi = fl.new_state(ctx)
+    fl.fl_init_state(ctx, psi, w["spinors"])
+    fl.fl_apply_period(ctx, psi, n)
+    g = fl.fl_grad(ctx, psi, [], n, 0, gens, torch.empty_like(psi))
+    ulp = 6e-8 if dtype == "c64" else 1.2e-16
+    assert np.max(np.abs(g - ref)) < n * 2 * n * (L - 1) * ulp * 4 * (L - 1)
