@@ -435,7 +435,7 @@ int launch_cover_rdm(fl_ctx* c, const void* psi, double* partials, int maxgrid, 
         if (e != hipSuccess) return fail_hip(e, "k_rdm_windows launch");
     }
     for (const fl_pass& p : c->cover_rdm) {
-        hipError_t e = fl::launch_rdm(c->dtype, c->geom_rdm, psi, p, partials, grid, c->L, c->stream);
+        hipError_t e = fl::launch_rdm(c->dtype, c->geom_rdm, psi, p, partials, c->L, c->stream);
         if (e != hipSuccess) return fail_hip(e, "k_rdm launch");
     }
     *grid_out = grid;

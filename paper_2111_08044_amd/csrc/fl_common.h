@@ -37,8 +37,8 @@
 #define FL_KMAX_ADJ 12       // tile bits of the two-state adjoint pass (complex64)
 #define FL_WIN4_MAX_GROUPS 14  // register groups per pass of a 4-qubit-window plan (the reverse pass keeps one window-overlap sum per group)
 #define FL_WIN4_NT 512         // threads of the 4-qubit-window reverse pass (13-bit tiles of two states)
-#define FL_KMAX_RDM 12       // tile bits of the bond-by-bond reduction of the shortest chains
 #define FL_RDM_MIN_WINDOWS 10  // shortest chain whose bonds are reduced in windows
+#define FL_KMAX_RDM (FL_RDM_MIN_WINDOWS - 1)  // longest chain reduced bond by bond
 #define FL_MAX_SLOTS 16      // distinct reduction slots per pass
 #define FL_KMAX_ONE 10       // longest chain whose sweep runs in one workgroup
 #define FL_SWEEP_WORDS 144   // words of a sweep pass's descriptor in words form: groups + ops + 1

@@ -12,8 +12,8 @@ namespace fl {
 hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gates, const fl_pass& pd, int reps,
                         hipStream_t s);
 // bond reductions of shorter chains, one tile
-hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,
-                      int nslot, hipStream_t s);
+hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int nslot,
+                      hipStream_t s);
 // one pass of the bond reductions of chains from FL_RDM_MIN_WINDOWS sites on
 hipError_t launch_rdm_windows(int dtype, const fl_geom& g, const void* psi, const rdm_desc& pd, double* partials,
                               int grid, int nslot, hipStream_t s);

@@ -97,26 +97,17 @@ __device__ __forceinline__ void apply_pair_g(T (&vr)[1 << R], T (&vi)[1 << R], c
 // with the untouched values and cost register copies at the join.
 template <int R, typename F>
 __device__ __forceinline__ void with_bit(int i, F&& f) {
-    static_assert(R >= 2 && R <= 5, "register group size");
-    if constexpr (R == 2) {
-        f(std::integral_constant<int, 0>{});
-    } else if constexpr (R == 3) {
+    static_assert(R == 3 || R == 4, "register group size");
+    if constexpr (R == 3) {
         switch (i) {
             case 0: f(std::integral_constant<int, 0>{}); break;
             default: f(std::integral_constant<int, 1>{}); break;
-        }
-    } else if constexpr (R == 4) {
-        switch (i) {
-            case 0: f(std::integral_constant<int, 0>{}); break;
-            case 1: f(std::integral_constant<int, 1>{}); break;
-            default: f(std::integral_constant<int, 2>{}); break;
         }
     } else {
         switch (i) {
             case 0: f(std::integral_constant<int, 0>{}); break;
             case 1: f(std::integral_constant<int, 1>{}); break;
-            case 2: f(std::integral_constant<int, 2>{}); break;
-            default: f(std::integral_constant<int, 3>{}); break;
+            default: f(std::integral_constant<int, 2>{}); break;
         }
     }
 }
@@ -1012,86 +1003,59 @@ __global__ __launch_bounds__(1 << KT) void k_sweep_lanes(typename CT<T>::c* __re
 // [0..3] = rho_ii, then (re, im) of rho_01, rho_02, rho_03, rho_12, rho_13, rho_23.
 // partials layout: [gridDim.x][nslot][16] doubles, slot = bond, slot L-1 = norm.
 
-#define FL_RDM_MAXG 16
+#define FL_RDM_MAXG (FL_KMAX_RDM - 1)
 
-// Adds one quad (amplitudes a_0..a_3 of a bond's local index) to the 16
-// density-matrix sums: [0..3] |a_l|^2, then for each pair l < m the real and
-// imaginary parts of conj(a_l) a_m (as ar_l ar_m + ai_l ai_m and
-// ai_l ar_m - ar_l ai_m), pairs in the order 01, 02, 03, 12, 13, 23.
+// Chains below FL_RDM_MIN_WINDOWS sites, in one workgroup: bond by bond.
 template <typename T>
-__device__ __forceinline__ void rdm_quad(const T (&ar)[4], const T (&ai)[4], T (&r)[16]) {
-#pragma unroll
-    for (int l = 0; l < 4; ++l) r[l] = fma(ar[l], ar[l], fma(ai[l], ai[l], r[l]));
-    int k = 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = i + 1; j < 4; ++j) {
-            r[k] = fma(ar[i], ar[j], fma(ai[i], ai[j], r[k]));
-            r[k + 1] = fma(ai[i], ar[j], fma(-ar[i], ai[j], r[k + 1]));
-            k += 2;
-        }
-}
-
-template <typename T, int KT, int KMAX>
-__global__ __launch_bounds__(FL_NT) void k_rdm(const typename CT<T>::c* __restrict__ psi, int C, int W,
-                                               uint32_t ntiles, fl_pass pd, double* __restrict__ partials,
-                                               int nslot) {
+__global__ __launch_bounds__(FL_NT) void k_rdm(const typename CT<T>::c* __restrict__ psi, int K, fl_pass pd,
+                                               double* __restrict__ partials, int nslot) {
     typedef typename CT<T>::c cplx;
-    __shared__ cplx lds[1 << KMAX];
+    __shared__ cplx lds[1 << FL_KMAX_RDM];
     __shared__ double wacc[FL_NT / 64][FL_RDM_MAXG + 1][16];
-    const int K = KT > 0 ? KT : C + W;
-    const int h = pd.h;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double acc[FL_RDM_MAXG];
 #pragma unroll
     for (int g = 0; g < FL_RDM_MAXG; ++g) acc[g] = 0.0;
     double nrm = 0.0;
     const uint32_t ngrp = 1u << (K - 2);
-    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const uint64_t base = fl_tile_base(tile, C, W, h);
-        __syncthreads();
-        tile_load<T, KT>(psi, base, K, C, h, lds);
-        __syncthreads();
-        if (pd.flags & 1) {
-            for (uint32_t j = threadIdx.x; j < (1u << K); j += FL_NT) {
-                const cplx a = lds[fl_swz(j)];
-                nrm += (double)a.x * (double)a.x + (double)a.y * (double)a.y;
-            }
-        }
+    for (uint32_t j = threadIdx.x; j < (1u << K); j += FL_NT) {
+        const cplx a = psi[j];
+        lds[fl_swz(j)] = a;
+        nrm += (double)a.x * (double)a.x + (double)a.y * (double)a.y;
+    }
+    __syncthreads();
 #pragma unroll
-        for (int g = 0; g < FL_RDM_MAXG; ++g) {
-            if (g < pd.ngroups) {
-                const int u = pd.u0[g];
-                double r[16];
+    for (int g = 0; g < FL_RDM_MAXG; ++g) {
+        if (g < pd.ngroups) {
+            const int u = pd.u0[g];
+            double r[16];
 #pragma unroll
-                for (int k = 0; k < 16; ++k) r[k] = 0.0;
-                for (uint32_t o = threadIdx.x; o < ngrp; o += FL_NT) {
-                    const uint32_t b0 = fl_spread(o, u, 2);
-                    double ar[4], ai[4];
+            for (int k = 0; k < 16; ++k) r[k] = 0.0;
+            for (uint32_t o = threadIdx.x; o < ngrp; o += FL_NT) {
+                const uint32_t b0 = fl_spread(o, u, 2);
+                double ar[4], ai[4];
 #pragma unroll
-                    for (int l = 0; l < 4; ++l) {
-                        const cplx a = lds[fl_swz(b0 | ((uint32_t)l << u))];
-                        ar[l] = a.x;
-                        ai[l] = a.y;
-                    }
-#pragma unroll
-                    for (int l = 0; l < 4; ++l) r[l] = fma(ar[l], ar[l], fma(ai[l], ai[l], r[l]));
-                    int k = 4;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = i + 1; j < 4; ++j) {
-                            r[k] = fma(ar[i], ar[j], fma(ai[i], ai[j], r[k]));
-                            r[k + 1] = fma(ai[i], ar[j], fma(-ar[i], ai[j], r[k + 1]));
-                            k += 2;
-                        }
+                for (int l = 0; l < 4; ++l) {
+                    const cplx a = lds[fl_swz(b0 | ((uint32_t)l << u))];
+                    ar[l] = a.x;
+                    ai[l] = a.y;
                 }
-                acc[g] += wave_transpose_reduce<double, 16>(r);
+#pragma unroll
+                for (int l = 0; l < 4; ++l) r[l] = fma(ar[l], ar[l], fma(ai[l], ai[l], r[l]));
+                int k = 4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = i + 1; j < 4; ++j) {
+                        r[k] = fma(ar[i], ar[j], fma(ai[i], ai[j], r[k]));
+                        r[k + 1] = fma(ai[i], ar[j], fma(-ar[i], ai[j], r[k + 1]));
+                        k += 2;
+                    }
             }
+            acc[g] += wave_transpose_reduce<double, 16>(r);
         }
     }
-    // per-wave accumulators -> LDS -> one row of partials per workgroup
+    // per-wave accumulators -> LDS -> the sums
     double nv[1] = {nrm};
     const double ntot = wave_transpose_reduce<double, 1>(nv);
     if ((lane & 3) == 0) {
@@ -1106,11 +1070,10 @@ __global__ __launch_bounds__(FL_NT) void k_rdm(const typename CT<T>::c* __restri
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < FL_NT / 64; ++w) s += wacc[w][gg][v];
-        if (g < pd.ngroups) {
-            partials[((size_t)blockIdx.x * nslot + pd.ops[g][0]) * 16 + v] = s;
-        } else if ((pd.flags & 1) && v == 0) {
-            partials[((size_t)blockIdx.x * nslot + (nslot - 1)) * 16] = s;
-        }
+        if (g < pd.ngroups)
+            partials[(size_t)pd.ops[g][0] * 16 + v] = s;
+        else if (v == 0)
+            partials[(size_t)(nslot - 1) * 16] = s;
     }
 }
 
@@ -1230,7 +1193,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
         for (int s = 0; s < ITER; ++s) v[s] = __builtin_nontemporal_load(reinterpret_cast<const v16*>(src + s * tstride));
     };
-        if (PREF && blockIdx.x < ntiles) fetch(blockIdx.x);
+    if (PREF && blockIdx.x < ntiles) fetch(blockIdx.x);
     int held = 0;
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         if (!PREF) fetch(tile);
@@ -1452,17 +1415,17 @@ __global__ __launch_bounds__(64) void k_energy_contract(const double* __restrict
 // Bond by bond, with all 16 entries of each term as given: chains of one tile,
 // and longer ones whose terms are not Hermitian to rounding.
 
-template <typename T, int KT, int KMAX>
+template <typename T, int KMAX>
 __global__ __launch_bounds__(FL_NT) void k_apply_h(const typename CT<T>::c* __restrict__ psi,
                                                    typename CT<T>::c* __restrict__ lam, const T* __restrict__ hmat,
                                                    int C, int W, fl_pass pd, int first) {
     typedef typename CT<T>::c cplx;
     __shared__ cplx lp[1 << KMAX];
     __shared__ cplx ll[1 << KMAX];
-    const int K = KT > 0 ? KT : C + W;
+    const int K = C + W;
     const int h = pd.h;
     const uint64_t base = fl_tile_base(blockIdx.x, C, W, h);
-    tile_load<T, KT>(psi, base, K, C, h, lp);
+    tile_load<T, 0>(psi, base, K, C, h, lp);
     if (first) {
         for (uint32_t j = threadIdx.x; j < (1u << K); j += FL_NT) {
             cplx z;
@@ -1471,7 +1434,7 @@ __global__ __launch_bounds__(FL_NT) void k_apply_h(const typename CT<T>::c* __re
             ll[j] = z;
         }
     } else {
-        tile_load<T, KT>(lam, base, K, C, h, ll);
+        tile_load<T, 0>(lam, base, K, C, h, ll);
     }
     __syncthreads();
     const uint32_t ngrp = 1u << (K - 2);
@@ -1502,7 +1465,7 @@ __global__ __launch_bounds__(FL_NT) void k_apply_h(const typename CT<T>::c* __re
         }
         __syncthreads();
     }
-    tile_store<T, KT>(lam, base, K, C, h, ll);
+    tile_store<T, 0>(lam, base, K, C, h, ll);
 }
 
 // Full tiles (W > 0), Hermitian terms.  The bonds of a pass come packed into windows of 4
@@ -3040,15 +3003,13 @@ hipError_t launch_sweep(int dtype, const fl_geom& g, void* psi, const void* gate
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int grid,
-                      int nslot, hipStream_t s) {
-    const uint32_t nt = ntiles_of(g);
+hipError_t launch_rdm(int dtype, const fl_geom& g, const void* psi, const fl_pass& pd, double* partials, int nslot,
+                      hipStream_t s) {
+    if (g.W != 0 || g.K > FL_KMAX_RDM || pd.ngroups > FL_RDM_MAXG) return hipErrorInvalidValue;
     if (dtype == 0)
-        hipLaunchKernelGGL((k_rdm<float, 0, FL_KMAX_RDM>), dim3(grid), dim3(FL_NT), 0, s, (const float2*)psi, g.C, g.W,
-                           nt, pd, partials, nslot);
+        hipLaunchKernelGGL(k_rdm<float>, dim3(1), dim3(FL_NT), 0, s, (const float2*)psi, g.K, pd, partials, nslot);
     else
-        hipLaunchKernelGGL((k_rdm<double, 0, FL_KMAX_RDM>), dim3(grid), dim3(FL_NT), 0, s, (const double2*)psi, g.C,
-                           g.W, nt, pd, partials, nslot);
+        hipLaunchKernelGGL(k_rdm<double>, dim3(1), dim3(FL_NT), 0, s, (const double2*)psi, g.K, pd, partials, nslot);
     return hipGetLastError();
 }
 
@@ -3130,10 +3091,10 @@ hipError_t launch_apply_h(int dtype, const fl_geom& g, const void* psi, void* la
                           int first, hipStream_t s) {
     const dim3 grid(ntiles_of(g)), block(FL_NT);
     if (dtype == 0)
-        hipLaunchKernelGGL((k_apply_h<float, 0, FL_KMAX_C64>), grid, block, 0, s, (const float2*)psi, (float2*)lam,
+        hipLaunchKernelGGL((k_apply_h<float, FL_KMAX_C64>), grid, block, 0, s, (const float2*)psi, (float2*)lam,
                            (const float*)hmat, g.C, g.W, pd, first);
     else
-        hipLaunchKernelGGL((k_apply_h<double, 0, FL_KMAX_C128>), grid, block, 0, s, (const double2*)psi,
+        hipLaunchKernelGGL((k_apply_h<double, FL_KMAX_C128>), grid, block, 0, s, (const double2*)psi,
                            (double2*)lam, (const double*)hmat, g.C, g.W, pd, first);
     return hipGetLastError();
 }
