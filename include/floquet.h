@@ -256,18 +256,21 @@ int fl_host_window_matrix(const double *G, const int *pos, int nops, int mode, d
  * matrix, which the gradient of Sec. V's reverse replay needs).  FP64. */
 int fl_host_window_overlaps(const double *Q, const double *G, const int *pos, int nops, double *out);
 
-/* The plan fl_apply_period would run for n periods (kind 0 = sweep,
- * 1 = reverse sweep of the gradient (both in blocks of 16 periods and a
- * remainder; chains of at most 10 sites in blocks of one period, up to 256 of
- * them in one launch), 2 = energy / density-matrix cover (the
- * bonds of each launch; tiles with 4 low bits from L = 10 on, full ones from L =
- * 13 complex64, 12 complex128; windows: fl_readout_windows), 3 = cover used for H0 psi by a plain-sweep context
- * (Hermitian terms; bonds packed into 4-bit windows on chains longer than one
- * tile), 4 = dense
- * 6-qubit-window sweep, 5 = dense 4-qubit-window sweep, 6 = a cover that no
- * entry point runs: complex64 states with L >= 14 on 13-bit tiles with 6 low
- * bits, bonds packed into 5-bit register groups), flattened as int32:
- * [C, W, R, npasses, {h, ngroups, flags, {u0, nops, {i, gate, slot}*}*}*].
+/* The plan that runs for n periods, flattened as int32.  kind:
+ *   0  sweep, as fl_apply_period runs it: blocks of 16 periods and a remainder;
+ *      chains of at most 10 sites in blocks of one period, up to 256 of them in
+ *      one launch
+ *   1  reverse sweep of the gradient, in the same blocks
+ *   2  energy / density-matrix cover, the bonds of each launch: tiles with 4 low
+ *      bits from L = 10 on, full ones from L = 13 complex64, 12 complex128 (their
+ *      windows: fl_readout_windows)
+ *   3  cover used for H0 psi by a plain-sweep context (Hermitian terms): bonds
+ *      packed into 4-bit windows on chains longer than one tile
+ *   4  dense 6-qubit-window sweep
+ *   5  dense 4-qubit-window sweep
+ *   6  a cover that no entry point runs: complex64 states with L >= 14 on 13-bit
+ *      tiles with 6 low bits, bonds packed into 5-bit register groups
+ * Layout: [C, W, R, npasses, {h, ngroups, flags, {u0, nops, {i, gate, slot}*}*}*].
  * Writes at most cap words to buf (may be NULL) and the required count to
  * *needed. */
 int fl_plan_query(int L, int dtype, int kind, int64_t n_periods, int dagger, int32_t *buf, int64_t cap,

@@ -84,9 +84,12 @@ fl_geom plain_geom(int L, int dtype) {
 //  - Longer chains: full tiles (complex64 L = 21: 362 on 13 bits, 412 on 12).
 //  - complex128 on 12-bit tiles takes 3 low bits (128-byte runs, a 9-bit
 //    window) for calls of 3 periods and more: 15 passes instead of 27 for 16
-//    periods at L = 23, 2.12 against 2.42 ms.  For one or two periods the two
-//    are within 3 to 12% (L = 24, n = 2: 4 passes in 665 us, 5 in 686 us) and
-//    the call keeps 6.
+//    periods at L = 23, 2.12 against 2.42 ms.  Calls of one or two periods keep
+//    6, but not for speed: the geometry that fl_plan_query reports for two
+//    periods is held by a test.  3 low bits are the faster ones there too but
+//    for one period at some lengths (us with 3 / 6, one and two periods: L = 20
+//    38 / 46 and 62 / 66, 22 115 / 114 and 156 / 207, 24 390 / 443 and 666 / 693,
+//    28 9950 / 9570 and 12320 / 14910, 30 38200 / 43250 and 56400 / 66900).
 fl_geom sweep_geom(int L, int dtype, int64_t n) {
     if (L <= FL_KMAX_ONE) return fl::make_geom(L, FL_KMAX_ONE, 2, 3);
     const bool c64 = dtype == FL_C64;

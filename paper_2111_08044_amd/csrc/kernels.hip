@@ -1077,7 +1077,7 @@ __global__ __launch_bounds__(FL_NT) void k_rdm(const typename CT<T>::c* __restri
     }
 }
 
-// Full tiles (W > 0, or one tile of exactly 2^K amplitudes).  The bonds of a
+// Chains from FL_RDM_MIN_WINDOWS sites on, in tiles of 2^K amplitudes.  The bonds of a
 // pass come in 1, 2 or 4 windows of 4 consecutive tile bits (up to 3 bonds
 // each); wave w sums window w mod nwin over all tiles of its workgroup, so a
 // lane keeps a window's sums in registers from tile to tile and the wave trees
@@ -1095,9 +1095,10 @@ __global__ __launch_bounds__(FL_NT) void k_rdm(const typename CT<T>::c* __restri
 // most FL_RDM_FLUSH tiles and trees above them.
 //
 // Bound by the vector ALUs: at L = 27 the three passes issue 1.69e8, 1.35e8
-// and 0.86e8 instructions, 87%, 77% and 60% of their 437, 390 and 320 us at
-// the 2.3 ns a wave instruction takes here (the last pass, 6 bonds, waits for
-// its reads the rest).  Readout at L = 27: 1.09 ms (1.54 with 16 sums per bond
+// and 0.86e8 instructions, 87%, 79% and 61% of their 435, 383 and 316 us (medians
+// of 20 under a kernel trace, which runs them 4% longer than the untraced whole)
+// at the 2.3 ns a wave instruction takes here; the last pass, 6 bonds, waits for
+// its reads the rest.  Readout at L = 27: 1.09 ms (1.54 with 16 sums per bond
 // reduced per tile, on four passes of 7-bit windows), L = 30: 11.9 ms (13.4),
 // complex128 L = 26: 0.70 ms (1.21).  3 low bits (64-byte runs) would save a
 // pass at L = 30 but read slower: 11.8 ms there, 1.25 ms at L = 27.
