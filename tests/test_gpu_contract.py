@@ -113,7 +113,8 @@ def test_gradient_fp32_at_configured_depth_matches_oracle_adjoint(L):
 def test_gradient_c4_config_fp32_against_fp64_gpu():
     """The adjoint workload itself: L = 24, n = 200, K = 50, complex64
     gradient of all 3(L-1) couplings and T against the complex128 GPU
-    gradient (pinned to the oracle adjoint at 1e-10 by the FP64 tests):
+    gradient (the kernel of both is pinned to the oracle adjoint at L = 20 to
+    22 by test_gpu_tiles.py, that of shorter chains at 1e-10 by the FP64 tests):
     relative error <= 1e-3; E_n within 1e-5 per site."""
     L, n, K = 24, 200, 50
     say(f"case: grad C4 L={L} n={n} K={K}")

@@ -125,8 +125,8 @@ def test_small_chains_element_by_element(dtype, L):
 @pytest.mark.parametrize("L", [2, 6, 13, 14, 16, 21])
 def test_rdm_energy_and_spread_match_oracle(dtype, L):
     """Bond density matrices, energy, norm and spread against the oracle on a
-    random (non-product) state.  complex64 from L = 14 up runs the 13-bit-tile
-    register-group readout (L = 14: two tiles), below it the 12-bit forms."""
+    random (non-product) state.  From L = 10 on the readout sums the bonds in
+    windows (several tiles from L = 14 complex64, 13 complex128), below bond by bond."""
     say(f"case: rdm L={L} {dtype}")
     w, hs = _model(L, seed=7)
     rng = np.random.default_rng(L)
@@ -423,8 +423,8 @@ def test_gradient_fp32_L12_close_to_fp64():
 
 
 def test_gradient_fp32_L16_close_to_fp64():
-    # 12-bit tiles with first and last register groups moved straight
-    # between HBM and registers as well as through LDS
+    # 9-bit tiles, one per workgroup; the form of long chains (12-bit tiles,
+    # 4-bit groups) meets the oracle in test_gpu_tiles.py
     L, n, K = 16, 12, 4
     say("case: grad fp32 L=16")
     w, hs = _model(L, seed=43)
@@ -445,10 +445,10 @@ def test_gradient_fp32_L16_close_to_fp64():
 
 
 def test_gradient_fp32_L24_close_to_fp64_gpu():
-    # 4096 tiles of 12 bits: every workgroup of the complex64 reverse pass
-    # runs several tiles and copies the next one into LDS during the last
-    # register group; the complex128 reverse pass (the reference here) has
-    # no such copies.  Both start from the same product state.
+    # 4096 tiles of 12 bits: every workgroup runs eight.  The complex128 reverse
+    # pass (the reference here) is another instance of the same kernel; both meet
+    # the oracle with several tiles per workgroup in test_gpu_tiles.py.  Both
+    # start from the same product state.
     L, n, K = 24, 8, 4
     say("case: grad fp32 vs fp64 L=24")
     w, hs = _model(L, seed=47)

@@ -97,14 +97,14 @@ def test_sweep_with_several_threads_per_quad(dtype, L, n, dagger):
 
 
 # one tile of each size; 2 tiles; window shares of 1, 2 and 3 bonds, one and two bonds
-# left for a last pass, more tiles than fit between two flushes of the sums
+# left for a last pass, the 16 tiles a workgroup sums between two flushes
 @pytest.mark.parametrize("dtype,L", [("c64", 10), ("c64", 11), ("c64", 12), ("c128", 10), ("c128", 11),
                                      ("c64", 13), ("c64", 15), ("c64", 20), ("c64", 22), ("c64", 23), ("c64", 26),
                                      ("c128", 12), ("c128", 13), ("c128", 17), ("c128", 20), ("c128", 23)])
 def test_bond_density_matrices_in_windows(dtype, L):
     """Every bond density matrix and the norm of a random state, against plain
     torch FP64 sums over the same stored amplitudes.  FP64 chains of at most
-    16 tiles x 4 parts x 4 terms a lane, and trees above them: 1e-13 of the
+    16 tiles x 8 parts x 8 terms a lane, and trees above them: 1e-13 of the
     norm."""
     say(f"case: rdm windows {dtype} L={L}")
     ctx = fl.fl_create(L, dtype)

@@ -368,16 +368,16 @@ def test_plan_statistics_L30():
 
 @pytest.mark.parametrize("kind,dtype,geom", [
     (0, "c64", (4, 9, 4)),    # plain sweep: 4 low bits, 4-bit groups (512-thread workgroups)
-    (0, "c128", (6, 6, 4)),
+    (0, "c128", (6, 6, 4)),   # two periods; 3 low bits from three periods on
     (1, "c64", (4, 8, 4)),    # gradient reverse pass: 12-bit tiles with 4 low bits
     (3, "c64", (4, 9, 4)),    # H0 psi cover of the plain geometry
     (4, "c64", (4, 9, 6)),    # 6-qubit windows
     (5, "c64", (4, 9, 4)),    # 4-qubit windows (forward and reverse pass)
-    (6, "c64", (6, 7, 5)),    # energy reduction: 6 low bits, 5-bit groups
+    (6, "c64", (6, 7, 5)),    # a cover that no kernel runs: 6 low bits, 5-bit groups
 ])
 def test_tile_geometries(kind, dtype, geom):
     """The tile geometry (C low bits, W window bits, R register bits) each
-    kind of plan uses at L = 24; the kernels are built for exactly these."""
+    kind of plan uses at L = 24 for two periods."""
     C, W, R, _ = pt.parse_plan(fl.fl_plan_query(24, dtype, kind, 2, kind == 1))
     assert (C, W, R) == geom
 
